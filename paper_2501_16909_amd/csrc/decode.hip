@@ -147,8 +147,9 @@ ci_status_t exec_begin(ci_ctx* ctx, hipStream_t caller, hipStream_t xs) {
   return CI_OK;
 }
 
-ci_status_t exec_end(ci_ctx* ctx, hipStream_t caller, hipStream_t xs) {
-  HIPCHK(hipEventRecord(ctx->ev[9], xs));
+// `recorded`: the last launch records ev[9] at its end itself.
+ci_status_t exec_end(ci_ctx* ctx, hipStream_t caller, hipStream_t xs, bool recorded = false) {
+  if (!recorded) HIPCHK(hipEventRecord(ctx->ev[9], xs));
   if (caller) HIPCHK(hipStreamWaitEvent(caller, ctx->ev[9], 0));
   HIPCHK(hipEventSynchronize(ctx->ev[9]));
   return CI_OK;
@@ -330,7 +331,7 @@ ci_status_t run_decode(ci_ctx* ctx, const ci_decode_desc_t* d, hipStream_t calle
   st = stage_positions(ctx, d->pos, c.batch, c.max_ctx, xs, &max_pos);
   if (st != CI_OK) return st;
   volatile uint64_t* hr = ctx->hres;
-  hr[0] = hr[1] = hr[2] = hr[3] = 0;
+  hr[0] = hr[1] = 0;
   HIPCHK(launch_stamp((uint64_t*)&hr[0], xs));
   std::vector<int> kinds;
   if (graph) {
@@ -353,12 +354,10 @@ ci_status_t run_decode(ci_ctx* ctx, const ci_decode_desc_t* d, hipStream_t calle
     if (st != CI_OK) return st;
     HIPCHK(hipEventRecord(ctx->ev[8], xs));
   }
-  HIPCHK(launch_stamp((uint64_t*)&hr[1], xs));
   const float* res = c.vocab ? d->logits : d->x_out;
   const uint64_t len = (uint64_t)c.batch * (c.vocab ? c.vocab : c.hidden);
-  HIPCHK(launch_checksum_f32(res, len, ctx->part_bits, ctx->part_sum, ctx->nparts, (uint64_t*)&hr[2],
-                             (double*)&hr[3], xs));
-  st = exec_end(ctx, caller, xs);
+  HIPCHK(launch_checksum_f32(res, len, ctx->sum_parts, (uint64_t*)&hr[1], xs, ctx->ev[9]));
+  st = exec_end(ctx, caller, xs, true);
   if (st != CI_OK) return st;
   memset(out, 0, sizeof(*out));
   float ms = 0.0f;
@@ -374,9 +373,7 @@ ci_status_t run_decode(ci_ctx* ctx, const ci_decode_desc_t* d, hipStream_t calle
   out->step_ns = (double)ms * 1e6;
   out->t_begin = hr[0];
   out->t_end = hr[1];
-  out->checksum_bits = hr[2];
-  uint64_t sb = hr[3];
-  memcpy(&out->sum_f64, &sb, sizeof(double));
+  checksum_total(ctx->sum_parts, len, &out->checksum_bits, &out->sum_f64);
   return CI_OK;
 }
 

@@ -80,9 +80,18 @@ hipError_t launch_hog(const KCtrl& c, uint32_t lds_bytes, uint32_t threads, hipS
 hipError_t launch_probe(uint32_t nwg, uint32_t* out, hipStream_t s);
 hipError_t launch_mfma_probe(int dtype, const void* a, const void* b, const float* c, float* d,
                              uint32_t ntiles, hipStream_t s);
-hipError_t launch_checksum_f32(const float* x, uint64_t n, uint64_t* part_bits, double* part_sum,
-                               uint32_t nparts, uint64_t* out_bits, double* out_sum,
-                               hipStream_t s);
+// Checksum of n words: the kernel leaves checksum_parts(n) <= kSumParts pairs
+// in `parts` (pinned host memory); once it has finished, checksum_total adds
+// them.  `done` (optional) is recorded at the kernel's end.
+struct SumPart {
+  uint64_t bits;
+  double sum;
+};
+constexpr uint32_t kSumParts = 1024;
+uint32_t checksum_parts(uint64_t n);
+hipError_t launch_checksum_f32(const float* x, uint64_t n, SumPart* parts, uint64_t* stamp, hipStream_t s,
+                               hipEvent_t done);
+void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum);
 hipError_t launch_amax_f32(const float* x, uint64_t n, float* part, uint32_t nparts, float* out,
                            hipStream_t s);
 hipError_t launch_to_bf16(const float* x, uint64_t n, uint16_t* out, hipStream_t s);

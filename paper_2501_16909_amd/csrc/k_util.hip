@@ -5,59 +5,74 @@
 namespace ci {
 namespace {
 
-// Checksums in two fixed-shape stages so the FP64 sum is the same on every
-// run: stage 1 gives work-group p the contiguous range [p*len, (p+1)*len);
-// each thread sums a fixed stride of it, then a fixed tree over the 256
-// threads.  Stage 2 (one work-group) sums the partials the same way.
-__device__ void block_reduce(uint64_t& bits, double& sum) {
-  __shared__ uint64_t sb[256];
-  __shared__ double ss[256];
-  sb[threadIdx.x] = bits;
-  ss[threadIdx.x] = sum;
-  __syncthreads();
-  for (uint32_t s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      sb[threadIdx.x] += sb[threadIdx.x + s];
-      ss[threadIdx.x] += ss[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  bits = sb[0];
-  sum = ss[0];
+// Output checksum: work-group p sums the contiguous range [p * len,
+// (p + 1) * len) -- thread t the groups of four t, t + 256, ... of it, in
+// order, then a fixed tree over the work-group -- and stores one {bits, sum}
+// pair to pinned host memory, where the host adds the pairs in order
+// (checksum_total): no second kernel, and the FP64 sum is the same on every
+// run.  *stamp (optional) takes the device clock as the kernel starts, which
+// is the end of whatever ran before it in the stream.
+// Bound by HBM reads: four non-temporal 16-byte loads per thread in flight on
+// up to 1024 work-groups (four per CU) read 1 GiB in 153 us, 7.0 TB/s (cached
+// loads 177 us, 512 or 2048 work-groups the same); one 4-byte load per thread
+// took 503 us.  More work-groups only add stores to host memory (1 M words:
+// 4.0 us with 1024, 5.7 with 2048, 10 with 4096).  The loads need only 4-byte
+// alignment, so any FP32 pointer takes this path.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr uint32_t kSumThreads = 256;
+constexpr uint32_t kSumUnroll = 4;
+
+__device__ __forceinline__ void sum4(f4u v, uint64_t& bits, double& sum) {
+  bits += (uint64_t)__float_as_uint(v.x) + __float_as_uint(v.y);
+  bits += (uint64_t)__float_as_uint(v.z) + __float_as_uint(v.w);
+  sum += (double)v.x;
+  sum += (double)v.y;
+  sum += (double)v.z;
+  sum += (double)v.w;
 }
 
-__global__ void __launch_bounds__(256) checksum_stage1(const float* __restrict__ x, uint64_t n,
-                                                       uint64_t len, uint64_t* part_bits,
-                                                       double* part_sum) {
+__global__ void __launch_bounds__(kSumThreads) checksum_kernel(const float* __restrict__ x, uint64_t n,
+                                                               uint64_t len, SumPart* parts,
+                                                               uint64_t* stamp) {
+  __shared__ uint64_t sb[kSumThreads / 64];
+  __shared__ double ss[kSumThreads / 64];
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = dev_now();
   const uint64_t lo = (uint64_t)blockIdx.x * len;
   const uint64_t hi = lo + len < n ? lo + len : n;
   uint64_t bits = 0;
   double sum = 0.0;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += 256) {
-    const float v = x[i];
-    bits += (uint64_t)__float_as_uint(v);
-    sum += (double)v;
+  if (lo < hi) {
+    const uint64_t n4 = (hi - lo) / 4;
+    const f4u* x4 = reinterpret_cast<const f4u*>(x + lo);
+    uint64_t i = threadIdx.x;
+    for (; i + (kSumUnroll - 1) * kSumThreads < n4; i += kSumUnroll * kSumThreads) {
+      f4u v[kSumUnroll];
+#pragma unroll
+      for (uint32_t u = 0; u < kSumUnroll; ++u) v[u] = __builtin_nontemporal_load(x4 + i + u * kSumThreads);
+#pragma unroll
+      for (uint32_t u = 0; u < kSumUnroll; ++u) sum4(v[u], bits, sum);
+    }
+    for (; i < n4; i += kSumThreads) sum4(x4[i], bits, sum);
+    const uint64_t rest = lo + 4 * n4 + threadIdx.x;   // fewer than four words, in the last range only
+    if (rest < hi) {
+      const float v = x[rest];
+      bits += (uint64_t)__float_as_uint(v);
+      sum += (double)v;
+    }
   }
-  block_reduce(bits, sum);
+  for (int off = 32; off > 0; off >>= 1) {
+    bits += __shfl_xor(bits, off, 64);
+    sum += __shfl_xor(sum, off, 64);
+  }
+  if ((threadIdx.x & 63u) == 0) {
+    sb[threadIdx.x >> 6] = bits;
+    ss[threadIdx.x >> 6] = sum;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    part_bits[blockIdx.x] = bits;
-    part_sum[blockIdx.x] = sum;
-  }
-}
-
-__global__ void __launch_bounds__(256) checksum_stage2(const uint64_t* part_bits,
-                                                       const double* part_sum, uint32_t nparts,
-                                                       uint64_t* out_bits, double* out_sum) {
-  uint64_t bits = 0;
-  double sum = 0.0;
-  for (uint32_t i = threadIdx.x; i < nparts; i += 256) {
-    bits += part_bits[i];
-    sum += part_sum[i];
-  }
-  block_reduce(bits, sum);
-  if (threadIdx.x == 0) {
-    *out_bits = bits;
-    *out_sum = sum;
+    parts[blockIdx.x].bits = (sb[0] + sb[1]) + (sb[2] + sb[3]);
+    parts[blockIdx.x].sum = (ss[0] + ss[1]) + (ss[2] + ss[3]);
   }
 }
 
@@ -170,15 +185,29 @@ uint32_t grid_for(uint64_t n) {
 
 }  // namespace
 
-hipError_t launch_checksum_f32(const float* x, uint64_t n, uint64_t* part_bits, double* part_sum,
-                               uint32_t nparts, uint64_t* out_bits, double* out_sum,
-                               hipStream_t s) {
-  const uint64_t len = n ? (n + nparts - 1) / nparts : 1;
-  hipError_t e = xlaunch(checksum_stage1, dim3(nparts), dim3(256), 0, s, nullptr, nullptr, x, n, len,
-                         part_bits, part_sum);
-  if (e != hipSuccess) return e;
-  return xlaunch(checksum_stage2, dim3(1), dim3(256), 0, s, nullptr, nullptr, part_bits, part_sum, nparts,
-                 out_bits, out_sum);
+uint32_t checksum_parts(uint64_t n) {
+  // at least sixteen words per thread, at most four work-groups per CU
+  const uint64_t p = (n + 4095) / 4096;
+  return (uint32_t)(p < 1 ? 1 : p > kSumParts ? kSumParts : p);
+}
+
+hipError_t launch_checksum_f32(const float* x, uint64_t n, SumPart* parts, uint64_t* stamp, hipStream_t s,
+                               hipEvent_t done) {
+  const uint32_t np = checksum_parts(n);
+  const uint64_t len = ((n + np - 1) / np + 3) & ~3ull;   // whole groups of four
+  return xlaunch(checksum_kernel, dim3(np), dim3(kSumThreads), 0, s, nullptr, done, x, n, len, parts, stamp);
+}
+
+void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum) {
+  const uint32_t np = checksum_parts(n);
+  uint64_t b = 0;
+  double t = 0.0;
+  for (uint32_t i = 0; i < np; ++i) {
+    b += parts[i].bits;
+    t += parts[i].sum;
+  }
+  *bits = b;
+  *sum = t;
 }
 
 hipError_t launch_amax_f32(const float* x, uint64_t n, float* part, uint32_t nparts, float* out,

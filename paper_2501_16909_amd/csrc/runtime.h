@@ -14,9 +14,8 @@ struct ci_ctx {
   int device = 0;
   ci_device_info_t info{};
   ci::HostCtrl* host = nullptr;        // pinned: stop / started words
-  volatile uint64_t* hres = nullptr;   // pinned: stamps and checksums written by kernels
-  uint64_t* part_bits = nullptr;       // device scratch for reductions
-  double* part_sum = nullptr;
+  volatile uint64_t* hres = nullptr;   // pinned: stamps written by kernels
+  ci::SumPart* sum_parts = nullptr;    // pinned: kSumParts checksum partials
   float* amax_part = nullptr;
   float* amax_out = nullptr;
   uint32_t* probe_buf = nullptr;

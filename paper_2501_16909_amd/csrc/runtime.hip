@@ -198,16 +198,15 @@ extern "C" ci_status_t ci_init(int device, ci_ctx_t** out) {
 
   // pinned control block and result slots (host-coherent)
   if (hipHostMalloc((void**)&ctx->host, sizeof(HostCtrl), hipHostMallocCoherent) != hipSuccess ||
-      hipHostMalloc((void**)&ctx->hres, 64 * sizeof(uint64_t), hipHostMallocCoherent) != hipSuccess) {
+      hipHostMalloc((void**)&ctx->hres, 64 * sizeof(uint64_t), hipHostMallocCoherent) != hipSuccess ||
+      hipHostMalloc((void**)&ctx->sum_parts, kSumParts * sizeof(SumPart), hipHostMallocCoherent) != hipSuccess) {
     ci_shutdown(ctx);
     return set_err(CI_ERR_OOM, "ci_init: pinned host allocation");
   }
   memset((void*)ctx->host, 0, sizeof(HostCtrl));
   memset((void*)ctx->hres, 0, 64 * sizeof(uint64_t));
   ctx->nparts = 1024;
-  if (hipMalloc((void**)&ctx->part_bits, ctx->nparts * sizeof(uint64_t)) != hipSuccess ||
-      hipMalloc((void**)&ctx->part_sum, ctx->nparts * sizeof(double)) != hipSuccess ||
-      hipMalloc((void**)&ctx->amax_part, ctx->nparts * sizeof(float)) != hipSuccess ||
+  if (hipMalloc((void**)&ctx->amax_part, ctx->nparts * sizeof(float)) != hipSuccess ||
       hipMalloc((void**)&ctx->amax_out, 256) != hipSuccess ||
       hipMalloc((void**)&ctx->probe_buf, 65536 * sizeof(uint32_t)) != hipSuccess) {
     ci_shutdown(ctx);
@@ -277,8 +276,7 @@ extern "C" ci_status_t ci_shutdown(ci_ctx_t* ctx) {
   // that pinned block is left allocated
   if (ctx->host && !ctx->drain_failed) (void)hipHostFree((void*)ctx->host);
   if (ctx->hres) (void)hipHostFree((void*)ctx->hres);
-  if (ctx->part_bits) (void)hipFree(ctx->part_bits);
-  if (ctx->part_sum) (void)hipFree(ctx->part_sum);
+  if (ctx->sum_parts) (void)hipHostFree(ctx->sum_parts);
   if (ctx->amax_part) (void)hipFree(ctx->amax_part);
   if (ctx->amax_out) (void)hipFree(ctx->amax_out);
   if (ctx->probe_buf) (void)hipFree(ctx->probe_buf);
@@ -1164,7 +1162,7 @@ ci_status_t ci::launch_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_
 ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs,
                            ci_victim_result_t* out) {
   volatile uint64_t* hr = ctx->hres;
-  hr[0] = hr[1] = hr[2] = hr[3] = 0;
+  hr[0] = hr[1] = 0;
   if (caller) {
     HIPCHK(hipEventRecord(ctx->ev[6], caller));
     HIPCHK(hipStreamWaitEvent(xs, ctx->ev[6], 0));
@@ -1172,11 +1170,8 @@ ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t c
   HIPCHK(launch_stamp((uint64_t*)&hr[0], xs));
   ci_status_t st = launch_victim(ctx, d, xs, ctx->ev[7], ctx->ev[8]);
   if (st != CI_OK) return st;
-  HIPCHK(launch_stamp((uint64_t*)&hr[1], xs));
   const uint64_t len = victim_out_len(d);
-  HIPCHK(launch_checksum_f32((const float*)d->out, len, ctx->part_bits, ctx->part_sum, ctx->nparts,
-                             (uint64_t*)&hr[2], (double*)&hr[3], xs));
-  HIPCHK(hipEventRecord(ctx->ev[9], xs));
+  HIPCHK(launch_checksum_f32((const float*)d->out, len, ctx->sum_parts, (uint64_t*)&hr[1], xs, ctx->ev[9]));
   if (caller) HIPCHK(hipStreamWaitEvent(caller, ctx->ev[9], 0));
   HIPCHK(hipEventSynchronize(ctx->ev[9]));
   float ms = 0.0f;
@@ -1184,9 +1179,7 @@ ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t c
   out->time_ns = (double)ms * 1e6;
   out->t_begin = hr[0];
   out->t_end = hr[1];
-  out->checksum_bits = hr[2];
-  uint64_t sb = hr[3];
-  memcpy(&out->sum_f64, &sb, sizeof(double));
+  checksum_total(ctx->sum_parts, len, &out->checksum_bits, &out->sum_f64);
   return CI_OK;
 }
 
@@ -1224,13 +1217,9 @@ extern "C" ci_status_t ci_checksum_f32(ci_ctx_t* ctx, const void* x, uint64_t n,
   if (!ctx || (!x && n) || !bits || !sum) return set_err(CI_ERR_INVALID_ARG, "ci_checksum_f32: NULL argument");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t s = (hipStream_t)stream;
-  volatile uint64_t* hr = ctx->hres;
-  HIPCHK(launch_checksum_f32((const float*)x, n, ctx->part_bits, ctx->part_sum, ctx->nparts,
-                             (uint64_t*)&hr[4], (double*)&hr[5], s));
+  HIPCHK(launch_checksum_f32((const float*)x, n, ctx->sum_parts, nullptr, s, nullptr));
   HIPCHK(hipStreamSynchronize(s));
-  *bits = hr[4];
-  uint64_t sb = hr[5];
-  memcpy(sum, &sb, sizeof(double));
+  checksum_total(ctx->sum_parts, n, bits, sum);
   return CI_OK;
 }
 

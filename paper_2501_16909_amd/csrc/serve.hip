@@ -146,6 +146,8 @@ uint64_t footprint(const ci_request_t& q) {
   }
 }
 
+uint64_t out_words(const ci_request_t& q) { return q.kind == CI_VICTIM_GEMM ? q.m * q.n : q.n; }
+
 struct Running {
   int idx = -1;
   uint64_t off = 0, bytes = 0;
@@ -431,19 +433,14 @@ ci_status_t serve_impl(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci
   HIPCHK(hipSetDevice(ctx->device));
   uint8_t* arena_base = nullptr;
   HIPCHK(hipMalloc((void**)&arena_base, p->hbm_budget));
-  // per-slot streams, events and checksum scratch
+  // per-slot streams, events and checksum partials
   const int S = p->slots;
   std::vector<hipStream_t> streams(S, nullptr);
   std::vector<Running> slot(S);
-  uint64_t* part_bits = nullptr;
-  double* part_sum = nullptr;
-  uint64_t* res = nullptr;  // pinned: [slot][2]
-  const uint32_t nparts = 256;
+  SumPart* parts = nullptr;  // pinned: [slot][kSumParts]
   ci_status_t st = CI_OK;
   auto fail = [&](ci_status_t s2) { if (st == CI_OK) st = s2; };
-  if (hipMalloc((void**)&part_bits, (size_t)S * nparts * 8) != hipSuccess ||
-      hipMalloc((void**)&part_sum, (size_t)S * nparts * 8) != hipSuccess ||
-      hipHostMalloc((void**)&res, (size_t)S * 2 * 8, hipHostMallocCoherent) != hipSuccess)
+  if (hipHostMalloc((void**)&parts, (size_t)S * kSumParts * sizeof(SumPart), hipHostMallocCoherent) != hipSuccess)
     fail(set_err(CI_ERR_OOM, "serve_run: scratch"));
   for (int s = 0; s < S && st == CI_OK; ++s) {
     if (hipStreamCreateWithFlags(&streams[s], hipStreamNonBlocking) != hipSuccess ||
@@ -491,8 +488,7 @@ ci_status_t serve_impl(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci
       float ms = 0.0f;
       (void)hipEventElapsedTime(&ms, r.ev0, r.ev1);
       o.service_ns = (double)ms * 1e6;
-      o.checksum_bits = res[2 * s];
-      memcpy(&o.sum_f64, (const void*)&res[2 * s + 1], 8);
+      checksum_total(parts + (size_t)s * kSumParts, out_words(trace[r.idx]), &o.checksum_bits, &o.sum_f64);
       o.status = CI_OK;
       arena.release(r.off, r.bytes);
       r.idx = -1;
@@ -527,10 +523,9 @@ ci_status_t serve_impl(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci
       out[r.idx].slot = s;
       ci_status_t ls = start_request(ctx, q, arena_base + off, streams[s], r);
       if (ls == CI_OK) {
-        const uint64_t out_len = q.kind == CI_VICTIM_GEMM ? q.m * q.n : q.n;
-        hipError_t e = launch_checksum_f32((const float*)r.d.out, out_len,
-                                           part_bits + (size_t)s * nparts, part_sum + (size_t)s * nparts,
-                                           nparts, &res[2 * s], (double*)&res[2 * s + 1], streams[s]);
+        const uint64_t out_len = out_words(q);
+        hipError_t e = launch_checksum_f32((const float*)r.d.out, out_len, parts + (size_t)s * kSumParts, nullptr,
+                                           streams[s], nullptr);
         if (e == hipSuccess && q.out_copy)
           e = hipMemcpyAsync(q.out_copy, r.d.out, out_len * sizeof(float), hipMemcpyDeviceToDevice,
                              streams[s]);
@@ -559,9 +554,7 @@ ci_status_t serve_impl(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci
     if (slot[s].done) (void)hipEventDestroy(slot[s].done);
     if (streams[s]) (void)hipStreamDestroy(streams[s]);
   }
-  if (res) (void)hipHostFree(res);
-  if (part_bits) (void)hipFree(part_bits);
-  if (part_sum) (void)hipFree(part_sum);
+  if (parts) (void)hipHostFree(parts);
   (void)hipFree(arena_base);
   return st;
 }
