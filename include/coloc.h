@@ -690,10 +690,9 @@ ci_status_t ci_silu_mul_bf16(ci_ctx_t* ctx, const float* gu, uint32_t batch, uin
 
 /* ci_attention_decode without the `part` workspace, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc).  It allocates nothing: positions and
- * partial results live in a static device array of 256 +
- * CI_NOALLOC_PART_BYTES bytes that each device holds for the life of the
- * process (its address is fetched once per device in ci_init).  Same
+ * harnesses that forbid hipMalloc).  It allocates nothing: partial results
+ * live in a static device array of CI_NOALLOC_PART_BYTES bytes that each
+ * device holds for the life of the process (its address is fetched once per device in ci_init).  Same
  * arguments, kernels and bit-identical output as ci_attention_decode.
  * CI_ERR_INVALID_ARG when the partial results, batch x n_q x
  * ceil(max_ctx / 64) x (head_dim + 2) x 4 bytes, exceed

@@ -89,10 +89,7 @@ ci_decode_layout_t layout_of(const ci_decode_config_t& c) {
 }
 
 ci_status_t ensure_decode_state(ci_ctx* ctx, size_t nevents) {
-  if (!ctx->dec_pos_host) {
-    HIPCHK(hipHostMalloc((void**)&ctx->dec_pos_host, kDecodeMaxBatch * sizeof(int32_t)));
-    HIPCHK(hipMalloc((void**)&ctx->dec_pos_dev, 256));
-  }
+  if (!ctx->dec_pos_dev) HIPCHK(hipMalloc((void**)&ctx->dec_pos_dev, 256));
   while (ctx->dec_ev.size() < nevents) {
     hipEvent_t e = nullptr;
     HIPCHK(hipEventCreate(&e));
@@ -101,23 +98,29 @@ ci_status_t ensure_decode_state(ci_ctx* ctx, size_t nevents) {
   return CI_OK;
 }
 
-// Validate host positions and queue their copy to the device on `s`.
-ci_status_t stage_positions(ci_ctx* ctx, const int32_t* pos, uint32_t batch, uint32_t max_ctx,
-                            hipStream_t s, uint32_t* max_pos) {
+static_assert(sizeof(Positions::val) / sizeof(int32_t) >= kDecodeMaxBatch, "a position per sequence");
+
+// Validated host positions by value, and the largest of them.
+ci_status_t take_positions(const int32_t* pos, uint32_t batch, uint32_t max_ctx, Positions* out,
+                           uint32_t* max_pos) {
   if (!pos) return set_err(CI_ERR_INVALID_ARG, "decode: NULL positions");
-  uint32_t mp = 0;
+  *out = Positions{};
+  *max_pos = 0;
   for (uint32_t b = 0; b < batch; ++b) {
     if (pos[b] < 0 || (uint32_t)pos[b] >= max_ctx)
       return set_err(CI_ERR_INVALID_ARG, "decode: position %d of sequence %u not in [0, %u)", pos[b], b, max_ctx);
-    mp = std::max(mp, (uint32_t)pos[b]);
+    out->val[b] = pos[b];
+    *max_pos = std::max(*max_pos, (uint32_t)pos[b]);
   }
-  ci_status_t st = ensure_decode_state(ctx, 0);
-  if (st != CI_OK) return st;
-  memcpy(ctx->dec_pos_host, pos, batch * sizeof(int32_t));
-  HIPCHK(hipMemcpyAsync(ctx->dec_pos_dev, ctx->dec_pos_host, batch * sizeof(int32_t),
-                        hipMemcpyHostToDevice, s));
-  *max_pos = mp;
   return CI_OK;
+}
+
+// Opens a call on the device: its start stamp (optional) and the positions
+// for kernels that read them from memory, in one launch of one wave (a copy
+// from pinned memory is an operation of its own, about 4 us with its gap).
+__global__ void __launch_bounds__(64) begin_kernel(Positions p, uint32_t batch, int32_t* dst, uint64_t* stamp) {
+  if (stamp && threadIdx.x == 0) *stamp = dev_now();
+  if (threadIdx.x < batch) dst[threadIdx.x] = p.val[threadIdx.x];
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -138,19 +141,8 @@ ci_status_t check_desc(const ci_decode_desc_t* d) {
   return CI_OK;
 }
 
-// Order `xs` after the caller's queued work (NULL caller: no ordering).
-ci_status_t exec_begin(ci_ctx* ctx, hipStream_t caller, hipStream_t xs) {
-  if (caller) {
-    HIPCHK(hipEventRecord(ctx->ev[6], caller));
-    HIPCHK(hipStreamWaitEvent(xs, ctx->ev[6], 0));
-  }
-  return CI_OK;
-}
-
-// `recorded`: the last launch records ev[9] at its end itself.
-ci_status_t exec_end(ci_ctx* ctx, hipStream_t caller, hipStream_t xs, bool recorded = false) {
-  if (!recorded) HIPCHK(hipEventRecord(ctx->ev[9], xs));
-  if (caller) HIPCHK(hipStreamWaitEvent(caller, ctx->ev[9], 0));
+// Wait for the call's work; its last launch records ev[9] at its end.
+ci_status_t exec_end(ci_ctx* ctx) {
   HIPCHK(hipEventSynchronize(ctx->ev[9]));
   return CI_OK;
 }
@@ -158,7 +150,7 @@ ci_status_t exec_end(ci_ctx* ctx, hipStream_t caller, hipStream_t xs, bool recor
 // Queue the step's kernels on `xs`.  ev(kind) gives the event pair of the
 // next launch (both null for untimed launches).
 template <class EvFn>
-ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* pos, uint32_t used, hipStream_t xs,
+ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* dpos, uint32_t used, hipStream_t xs,
                          EvFn ev) {
   const ci_decode_config_t& c = d->cfg;
   const ci_decode_layout_t L = layout_of(c);
@@ -172,6 +164,8 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* pos, uint32_t
   const uint32_t B = c.batch, hid = c.hidden, dh = c.head_dim, f = c.ffn;
   const uint64_t cache_layer = (uint64_t)B * c.n_kv * c.max_ctx * dh;
   const uint16_t* wts = (const uint16_t*)d->weights;
+  Positions pos{};
+  pos.dev = dpos;
 #define STEP(kind, call)                                                                       \
   do {                                                                                         \
     hipEvent_t e0_, e1_;                                                                       \
@@ -188,7 +182,7 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* pos, uint32_t
     q.x = xres;
     q.g = wl + L.g_attn;
     q.eps = c.eps;
-    q.pos = pos;
+    q.pos = dpos;
     q.q_out = qrot;
     q.kc = (uint16_t*)d->k_cache + l * cache_layer;
     q.vc = (uint16_t*)d->v_cache + l * cache_layer;
@@ -312,27 +306,22 @@ ci_status_t run_decode(ci_ctx* ctx, const ci_decode_desc_t* d, hipStream_t calle
   const bool timed = d->flags & CI_DECODE_KERNEL_TIMES;
   ci_status_t st = ensure_decode_state(ctx, timed ? 2 * (size_t)nk : 0);
   if (st != CI_OK) return st;
-  if (!d->pos) return set_err(CI_ERR_INVALID_ARG, "decode: NULL positions");
   uint32_t max_pos = 0;
-  for (uint32_t b = 0; b < c.batch; ++b) {   // before any capture or launch
-    if (d->pos[b] < 0 || (uint32_t)d->pos[b] >= c.max_ctx)
-      return set_err(CI_ERR_INVALID_ARG, "decode: position %d of sequence %u not in [0, %u)", d->pos[b], b,
-                     c.max_ctx);
-    max_pos = std::max(max_pos, (uint32_t)d->pos[b]);
-  }
+  Positions pos;
+  st = take_positions(d->pos, c.batch, c.max_ctx, &pos, &max_pos);   // before any capture or launch
+  if (st != CI_OK) return st;
   const uint32_t used = max_pos / kChunk + 1;
   hipGraphExec_t graph = nullptr;
   if (d->flags & CI_DECODE_GRAPH) {
     st = step_graph(ctx, d, used, xs, &graph);
     if (st != CI_OK) return st;
   }
-  st = exec_begin(ctx, caller, xs);
-  if (st != CI_OK) return st;
-  st = stage_positions(ctx, d->pos, c.batch, c.max_ctx, xs, &max_pos);
+  st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
   volatile uint64_t* hr = ctx->hres;
   hr[0] = hr[1] = 0;
-  HIPCHK(launch_stamp((uint64_t*)&hr[0], xs));
+  HIPCHK(xlaunch(begin_kernel, dim3(1), dim3(64), 0, xs, nullptr, nullptr, pos, c.batch, ctx->dec_pos_dev,
+                 (uint64_t*)&hr[0]));
   std::vector<int> kinds;
   if (graph) {
     HIPCHK(hipEventRecord(ctx->ev[7], xs));
@@ -357,7 +346,7 @@ ci_status_t run_decode(ci_ctx* ctx, const ci_decode_desc_t* d, hipStream_t calle
   const float* res = c.vocab ? d->logits : d->x_out;
   const uint64_t len = (uint64_t)c.batch * (c.vocab ? c.vocab : c.hidden);
   HIPCHK(launch_checksum_f32(res, len, ctx->sum_parts, (uint64_t*)&hr[1], xs, ctx->ev[9]));
-  st = exec_end(ctx, caller, xs, true);
+  st = exec_end(ctx);
   if (st != CI_OK) return st;
   memset(out, 0, sizeof(*out));
   float ms = 0.0f;
@@ -528,10 +517,10 @@ extern "C" ci_status_t ci_rmsnorm_bf16(ci_ctx_t* ctx, const float* x, const uint
     return set_err(CI_ERR_INVALID_ARG, "ci_rmsnorm_bf16: misaligned buffer");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t caller = (hipStream_t)stream, xs = ctx->vstream;
-  ci_status_t st = exec_begin(ctx, caller, xs);
+  ci_status_t st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
-  HIPCHK(launch_rmsnorm_bf16(x, g, y, rows, n, eps, xs, nullptr, nullptr));
-  return exec_end(ctx, caller, xs);
+  HIPCHK(launch_rmsnorm_bf16(x, g, y, rows, n, eps, xs, nullptr, ctx->ev[9]));
+  return exec_end(ctx);
 }
 
 extern "C" ci_status_t ci_gemv_bf16_rows(ci_ctx_t* ctx, const uint16_t* w, const uint16_t* v,
@@ -543,7 +532,7 @@ extern "C" ci_status_t ci_gemv_bf16_rows(ci_ctx_t* ctx, const uint16_t* w, const
   if (!aligned16(w) || !aligned16(v)) return set_err(CI_ERR_INVALID_ARG, "ci_gemv_bf16_rows: w and v must be 16-byte aligned");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t caller = (hipStream_t)stream, xs = ctx->vstream;
-  ci_status_t st = exec_begin(ctx, caller, xs);
+  ci_status_t st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
   GemvArgs a{};
   a.w = w;
@@ -553,8 +542,8 @@ extern "C" ci_status_t ci_gemv_bf16_rows(ci_ctx_t* ctx, const uint16_t* w, const
   a.rows = rows;
   a.k = k;
   a.batch = batch;
-  HIPCHK(launch_gemv_fused(a, 0, kEpiPlain, xs, nullptr, nullptr));
-  return exec_end(ctx, caller, xs);
+  HIPCHK(launch_gemv_fused(a, 0, kEpiPlain, xs, nullptr, ctx->ev[9]));
+  return exec_end(ctx);
 }
 
 extern "C" ci_status_t ci_fused_gemv(ci_ctx_t* ctx, const ci_gemv_args_t* in, void* stream) {
@@ -600,16 +589,22 @@ extern "C" ci_status_t ci_fused_gemv(ci_ctx_t* ctx, const ci_gemv_args_t* in, vo
   }
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t caller = (hipStream_t)stream, xs = ctx->vstream;
-  ci_status_t st = exec_begin(ctx, caller, xs);
-  if (st != CI_OK) return st;
+  ci_status_t st = CI_OK;
+  Positions pos;
   if (a.epilogue == CI_GEMV_ROPE) {
     uint32_t mp = 0;
-    st = stage_positions(ctx, a.pos, a.batch, a.max_ctx, xs, &mp);
+    st = take_positions(a.pos, a.batch, a.max_ctx, &pos, &mp);
+    if (st == CI_OK) st = ensure_decode_state(ctx, 0);
     if (st != CI_OK) return st;
     g.pos = ctx->dec_pos_dev;
   }
-  HIPCHK(launch_gemv_fused(g, a.v ? 0 : 1, a.epilogue, xs, nullptr, nullptr));
-  return exec_end(ctx, caller, xs);
+  st = order_after(ctx, caller, xs);
+  if (st != CI_OK) return st;
+  if (g.pos)
+    HIPCHK(xlaunch(begin_kernel, dim3(1), dim3(64), 0, xs, nullptr, nullptr, pos, a.batch, ctx->dec_pos_dev,
+                   (uint64_t*)nullptr));
+  HIPCHK(launch_gemv_fused(g, a.v ? 0 : 1, a.epilogue, xs, nullptr, ctx->ev[9]));
+  return exec_end(ctx);
 }
 
 extern "C" ci_status_t ci_rope_append(ci_ctx_t* ctx, const float* qkv, const int32_t* pos, uint32_t batch,
@@ -622,14 +617,15 @@ extern "C" ci_status_t ci_rope_append(ci_ctx_t* ctx, const float* qkv, const int
   if (st != CI_OK) return st;
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t caller = (hipStream_t)stream, xs = ctx->vstream;
-  st = exec_begin(ctx, caller, xs);
-  if (st != CI_OK) return st;
   uint32_t mp = 0;
-  st = stage_positions(ctx, pos, batch, max_ctx, xs, &mp);
+  Positions pv;
+  st = take_positions(pos, batch, max_ctx, &pv, &mp);
   if (st != CI_OK) return st;
-  HIPCHK(launch_rope_append(qkv, ctx->dec_pos_dev, q_out, k_cache, v_cache, batch, n_q, n_kv, head_dim,
-                            max_ctx, rope_base, xs, nullptr, nullptr));
-  return exec_end(ctx, caller, xs);
+  st = order_after(ctx, caller, xs);
+  if (st != CI_OK) return st;
+  HIPCHK(launch_rope_append(qkv, pv, q_out, k_cache, v_cache, batch, n_q, n_kv, head_dim,
+                            max_ctx, rope_base, xs, nullptr, ctx->ev[9]));
+  return exec_end(ctx);
 }
 
 extern "C" ci_status_t ci_attention_decode(ci_ctx_t* ctx, const float* q, const uint16_t* k_cache,
@@ -649,45 +645,32 @@ extern "C" ci_status_t ci_attention_decode(ci_ctx_t* ctx, const float* q, const 
   if (!aligned16(k_cache) || !aligned16(v_cache)) return set_err(CI_ERR_INVALID_ARG, "ci_attention_decode: misaligned cache");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t caller = (hipStream_t)stream, xs = ctx->vstream;
-  st = exec_begin(ctx, caller, xs);
-  if (st != CI_OK) return st;
   uint32_t mp = 0;
-  st = stage_positions(ctx, pos, batch, max_ctx, xs, &mp);
+  Positions pv;
+  st = take_positions(pos, batch, max_ctx, &pv, &mp);
+  if (st != CI_OK) return st;
+  st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
   const uint32_t nchunks = (max_ctx + kChunk - 1) / kChunk;
-  HIPCHK(launch_attn_partial(q, k_cache, v_cache, ctx->dec_pos_dev, (float*)part, batch, n_q, n_kv, head_dim,
+  HIPCHK(launch_attn_partial(q, k_cache, v_cache, pv, (float*)part, batch, n_q, n_kv, head_dim,
                              max_ctx, nchunks, mp / kChunk + 1, xs, nullptr, nullptr));
-  HIPCHK(launch_attn_combine((const float*)part, ctx->dec_pos_dev, out, batch, n_q, head_dim, nchunks, xs,
-                             nullptr, nullptr));
-  return exec_end(ctx, caller, xs);
+  HIPCHK(launch_attn_combine((const float*)part, pv, out, batch, n_q, head_dim, nchunks, xs,
+                             nullptr, ctx->ev[9]));
+  return exec_end(ctx);
 }
 
 // ------------------------------------------------ no-allocation attention
-// ci_attention_decode_noalloc works in this array instead of a caller's
-// workspace and the context's lazily allocated position buffer: the first
-// 256 bytes hold the positions, the rest the partial results.  Each device
-// holds its own copy for the life of the process.  Host code never passes
-// the array's name to a kernel (on the host it is only a stand-in for the
-// symbol): it uses the address hipGetSymbolAddress gives per device.
+// ci_attention_decode_noalloc keeps its partial results in this array instead
+// of a caller's workspace.  Each device holds its own copy for the life of
+// the process.  Host code never passes the array's name to a kernel (on the
+// host it is only a stand-in for the symbol): it uses the address
+// hipGetSymbolAddress gives per device.
 namespace {
-constexpr size_t kScratchPosBytes = 256;
-constexpr size_t kScratchBytes = kScratchPosBytes + CI_NOALLOC_PART_BYTES;
-static_assert(kDecodeMaxBatch * sizeof(int32_t) <= kScratchPosBytes, "positions must fit the header");
-
-static __device__ __align__(256) uint8_t scratch[kScratchBytes];
+static __device__ __align__(256) uint8_t scratch[CI_NOALLOC_PART_BYTES];
 
 constexpr int kScratchMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kScratchMaxDevices];
-
-struct PosArg {
-  int32_t v[kDecodeMaxBatch];
-};
-
-// Positions reach the device as a kernel argument (no staging buffer).
-__global__ void __launch_bounds__(64) store_positions_kernel(PosArg p, uint32_t batch, int32_t* dst) {
-  if (threadIdx.x < batch) dst[threadIdx.x] = p.v[threadIdx.x];
-}
 }  // namespace
 
 ci_status_t ci::static_scratch_init(int device) {
@@ -724,31 +707,24 @@ extern "C" ci_status_t ci_attention_decode_noalloc(ci_ctx_t* ctx, const float* q
                    (unsigned long long)L.attn_part_bytes, (unsigned long long)CI_NOALLOC_PART_BYTES);
   if (!aligned16(k_cache) || !aligned16(v_cache))
     return set_err(CI_ERR_INVALID_ARG, "ci_attention_decode_noalloc: misaligned cache");
-  PosArg pa{};
   uint32_t mp = 0;
-  for (uint32_t b = 0; b < batch; ++b) {
-    if (pos[b] < 0 || (uint32_t)pos[b] >= max_ctx)
-      return set_err(CI_ERR_INVALID_ARG, "ci_attention_decode_noalloc: position %d of sequence %u not in [0, %u)",
-                     pos[b], b, max_ctx);
-    pa.v[b] = pos[b];
-    mp = std::max(mp, (uint32_t)pos[b]);
-  }
+  Positions pv;
+  st = take_positions(pos, batch, max_ctx, &pv, &mp);
+  if (st != CI_OK) return st;
   void* base = (ctx->device >= 0 && ctx->device < kScratchMaxDevices) ? g_scratch_ptr[ctx->device] : nullptr;
   if (!base) return set_err(CI_ERR_UNSUPPORTED, "ci_attention_decode_noalloc: static scratch not set up");
-  int32_t* dpos = (int32_t*)base;
-  float* part = (float*)((uint8_t*)base + kScratchPosBytes);
+  float* part = (float*)base;
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t caller = (hipStream_t)stream, xs = ctx->vstream;
-  st = exec_begin(ctx, caller, xs);
+  st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
-  // every partial entry the combine reads is written by the partial kernel,
-  // and the positions are rewritten here: nothing needs clearing
-  HIPCHK(xlaunch(store_positions_kernel, dim3(1), dim3(64), 0, xs, nullptr, nullptr, pa, batch, dpos));
+  // every partial entry the combine reads is written by the partial kernel:
+  // nothing needs clearing
   const uint32_t nchunks = (max_ctx + kChunk - 1) / kChunk;
-  HIPCHK(launch_attn_partial(q, k_cache, v_cache, dpos, part, batch, n_q, n_kv, head_dim, max_ctx, nchunks,
+  HIPCHK(launch_attn_partial(q, k_cache, v_cache, pv, part, batch, n_q, n_kv, head_dim, max_ctx, nchunks,
                              mp / kChunk + 1, xs, nullptr, nullptr));
-  HIPCHK(launch_attn_combine(part, dpos, out, batch, n_q, head_dim, nchunks, xs, nullptr, nullptr));
-  return exec_end(ctx, caller, xs);
+  HIPCHK(launch_attn_combine(part, pv, out, batch, n_q, head_dim, nchunks, xs, nullptr, ctx->ev[9]));
+  return exec_end(ctx);
 }
 
 extern "C" ci_status_t ci_silu_mul_bf16(ci_ctx_t* ctx, const float* gu, uint32_t batch, uint32_t ffn,
@@ -757,8 +733,8 @@ extern "C" ci_status_t ci_silu_mul_bf16(ci_ctx_t* ctx, const float* gu, uint32_t
   if (batch == 0 || ffn == 0) return set_err(CI_ERR_INVALID_ARG, "ci_silu_mul_bf16: empty shape");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t caller = (hipStream_t)stream, xs = ctx->vstream;
-  ci_status_t st = exec_begin(ctx, caller, xs);
+  ci_status_t st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
-  HIPCHK(launch_silu_mul(gu, h, ffn, batch, xs, nullptr, nullptr));
-  return exec_end(ctx, caller, xs);
+  HIPCHK(launch_silu_mul(gu, h, ffn, batch, xs, nullptr, ctx->ev[9]));
+  return exec_end(ctx);
 }

@@ -126,15 +126,23 @@ struct GemvArgs {
 constexpr int kEpiPlain = 0, kEpiSilu = 1, kEpiRope = 2;
 hipError_t launch_gemv_fused(const GemvArgs& a, int input_norm, int epilogue, hipStream_t s,
                              hipEvent_t e0, hipEvent_t e1);
-hipError_t launch_rope_append(const float* qkv, const int32_t* pos, float* q_out, uint16_t* kc,
+// Positions of the batch's sequences: by value in the kernel's arguments (no
+// copy to wait for), or in device memory (dev != NULL: a captured graph reads
+// each replay's own).
+struct Positions {
+  const int32_t* dev;
+  int32_t val[8];
+  __device__ __forceinline__ int32_t at(uint32_t b) const { return dev ? dev[b] : val[b]; }
+};
+hipError_t launch_rope_append(const float* qkv, const Positions& pos, float* q_out, uint16_t* kc,
                               uint16_t* vc, uint32_t batch, uint32_t nq, uint32_t nkv, uint32_t d,
                               uint32_t max_ctx, float base, hipStream_t s, hipEvent_t e0,
                               hipEvent_t e1);
 hipError_t launch_attn_partial(const float* q, const uint16_t* kc, const uint16_t* vc,
-                               const int32_t* pos, float* part, uint32_t batch, uint32_t nq,
+                               const Positions& pos, float* part, uint32_t batch, uint32_t nq,
                                uint32_t nkv, uint32_t d, uint32_t max_ctx, uint32_t nchunks,
                                uint32_t used_chunks, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-hipError_t launch_attn_combine(const float* part, const int32_t* pos, uint16_t* out, uint32_t batch,
+hipError_t launch_attn_combine(const float* part, const Positions& pos, uint16_t* out, uint32_t batch,
                                uint32_t nq, uint32_t d, uint32_t nchunks, hipStream_t s, hipEvent_t e0,
                                hipEvent_t e1);
 hipError_t launch_silu_mul(const float* gu, uint16_t* h, uint32_t f, uint32_t batch, hipStream_t s,

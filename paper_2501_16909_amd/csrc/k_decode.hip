@@ -400,14 +400,14 @@ __global__ void __launch_bounds__(256) gemv_fused_kernel(GemvArgs a, uint32_t un
 // qkv: batch x (n_q + 2 n_kv) heads x head_dim FP32 (query heads, key heads,
 // value heads).  Cache (one layer): batch x n_kv x max_ctx x head_dim BF16.
 __global__ void __launch_bounds__(128) rope_append_kernel(const float* __restrict__ qkv,
-                                                          const int32_t* __restrict__ pos,
+                                                          Positions pos,
                                                           float* __restrict__ q_out,
                                                           uint16_t* __restrict__ kc,
                                                           uint16_t* __restrict__ vc, uint32_t nq,
                                                           uint32_t nkv, uint32_t d,
                                                           uint32_t max_ctx, float base) {
   const uint32_t b = blockIdx.x, h = blockIdx.y, i = threadIdx.x, half = d / 2;
-  const uint32_t p = (uint32_t)pos[b];
+  const uint32_t p = (uint32_t)pos.at(b);
   const float* src = qkv + ((size_t)b * (nq + 2 * nkv) + h) * d;
   const float x1 = src[i], x2 = src[i + half];
   if (h >= nq + nkv) {
@@ -441,7 +441,7 @@ template <int D>
 __global__ void __launch_bounds__(1024) attn_partial_kernel(const float* __restrict__ q,
                                                             const uint16_t* __restrict__ kc,
                                                             const uint16_t* __restrict__ vc,
-                                                            const int32_t* __restrict__ pos,
+                                                            Positions pos,
                                                             float* __restrict__ part, uint32_t nq,
                                                             uint32_t nkv, uint32_t max_ctx,
                                                             uint32_t nchunks, float scale) {
@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(1024) attn_partial_kernel(const float* __restr
   const uint32_t chunk = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   const uint32_t group = blockDim.x >> 6, lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
   const uint32_t h = kvh * group + w;
-  const int32_t T = pos[b] + 1;
+  const int32_t T = pos.at(b) + 1;
   const uint32_t t0 = chunk * 64u;
   float* dst = part + (((size_t)b * nq + h) * nchunks + chunk) * (D + 2);
   if ((int32_t)t0 >= T) {
@@ -551,7 +551,7 @@ __global__ void __launch_bounds__(1024) attn_partial_kernel(const float* __restr
 // partial sums of the chunk groups are added in a fixed order.
 template <int D>
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ part,
-                                                           const int32_t* __restrict__ pos,
+                                                           Positions pos,
                                                            uint16_t* __restrict__ out, uint32_t nq,
                                                            uint32_t nchunks) {
   constexpr uint32_t kPairs = D / 2;            // dimension pairs
@@ -560,7 +560,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   __shared__ float s_red[4];
   __shared__ float2 s_o[kGroups][kPairs];
   const uint32_t h = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
-  const uint32_t nc = (uint32_t)pos[b] / 64u + 1u;
+  const uint32_t nc = (uint32_t)pos.at(b) / 64u + 1u;
   const float* src = part + ((size_t)b * nq + h) * nchunks * (D + 2);
   float mx = -INFINITY;
   for (uint32_t c = t; c < nc; c += 256) mx = fmaxf(mx, src[(size_t)c * (D + 2)]);
@@ -692,7 +692,7 @@ hipError_t launch_rmsnorm_bf16(const float* x, const uint16_t* g, uint16_t* y, u
   return xlaunch(rmsnorm_kernel, dim3(rows), dim3(256), 0, s, e0, e1, x, g, y, n, eps);
 }
 
-hipError_t launch_rope_append(const float* qkv, const int32_t* pos, float* q_out, uint16_t* kc,
+hipError_t launch_rope_append(const float* qkv, const Positions& pos, float* q_out, uint16_t* kc,
                               uint16_t* vc, uint32_t batch, uint32_t nq, uint32_t nkv, uint32_t d,
                               uint32_t max_ctx, float base, hipStream_t s, hipEvent_t e0,
                               hipEvent_t e1) {
@@ -701,7 +701,7 @@ hipError_t launch_rope_append(const float* qkv, const int32_t* pos, float* q_out
 }
 
 hipError_t launch_attn_partial(const float* q, const uint16_t* kc, const uint16_t* vc,
-                               const int32_t* pos, float* part, uint32_t batch, uint32_t nq,
+                               const Positions& pos, float* part, uint32_t batch, uint32_t nq,
                                uint32_t nkv, uint32_t d, uint32_t max_ctx, uint32_t nchunks,
                                uint32_t used_chunks, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid(used_chunks, nkv, batch), block(64 * (nq / nkv));
@@ -715,7 +715,7 @@ hipError_t launch_attn_partial(const float* q, const uint16_t* kc, const uint16_
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_attn_combine(const float* part, const int32_t* pos, uint16_t* out, uint32_t batch,
+hipError_t launch_attn_combine(const float* part, const Positions& pos, uint16_t* out, uint32_t batch,
                                uint32_t nq, uint32_t d, uint32_t nchunks, hipStream_t s, hipEvent_t e0,
                                hipEvent_t e1) {
   if (d == 128)

@@ -48,8 +48,7 @@ struct ci_ctx {
   hipEvent_t ev[12] = {};
   struct ci_stressor* active = nullptr;
   uint64_t rot = 0;                    // GEMV weight-copy rotation
-  // decode step: positions staged host -> device, events per kernel launch
-  int32_t* dec_pos_host = nullptr;     // pinned, kDecodeMaxBatch entries
+  // decode step: positions in device memory, events per kernel launch
   int32_t* dec_pos_dev = nullptr;
   std::vector<hipEvent_t> dec_ev;
   std::map<std::string, hipGraphExec_t> dec_graphs;   // captured decode steps
@@ -117,6 +116,8 @@ struct HeldStream {
 void mask_for(const ci_ctx* ctx, int k, int complement, uint32_t mask[8]);
 ci_status_t launch_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1);
+// Orders `xs` after the work already queued on `caller` (NULL: no ordering).
+ci_status_t order_after(ci_ctx* ctx, hipStream_t caller, hipStream_t xs);
 ci_status_t run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs,
                        ci_victim_result_t* out);
 // Fetches, once per device, the device address of the static scratch array
