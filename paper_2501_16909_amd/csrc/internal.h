@@ -92,11 +92,10 @@ uint32_t checksum_parts(uint64_t n);
 hipError_t launch_checksum_f32(const float* x, uint64_t n, SumPart* parts, uint64_t* stamp, hipStream_t s,
                                hipEvent_t done);
 void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum);
-hipError_t launch_amax_f32(const float* x, uint64_t n, float* part, uint32_t nparts, float* out,
-                           hipStream_t s);
 hipError_t launch_to_bf16(const float* x, uint64_t n, uint16_t* out, hipStream_t s);
-hipError_t launch_to_fp8(const float* x, uint64_t n, const float* amax, uint8_t* out,
-                         hipStream_t s);
+// n > 0; part: kSumParts floats of device scratch; *amax (pinned) = max |x|
+hipError_t launch_quantize_fp8(const float* x, uint64_t n, float* part, float* amax, uint8_t* out,
+                               hipStream_t s);
 hipError_t launch_gemm(int dtype, const void* a, const void* b, float* c, uint64_t m, uint64_t n,
                        uint64_t k, float scale, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_gemv_bf16(const uint16_t* w, const uint16_t* x, float* y, uint64_t n,

@@ -76,33 +76,39 @@ __global__ void __launch_bounds__(kSumThreads) checksum_kernel(const float* __re
   }
 }
 
-__global__ void __launch_bounds__(256) amax_stage1(const float* __restrict__ x, uint64_t n,
-                                                   uint64_t len, float* part) {
-  __shared__ float sm[256];
+// Per-tensor quantisation in two kernels, both bound by HBM: amax_kernel
+// leaves one maximum per work-group (the checksum's ranges and loads), and
+// every work-group of to_fp8_kernel reduces those (4 KiB, from L2) before it
+// converts, so no launch sits between them.  For 8192 x 8192 values the
+// maximum takes 43 us (6.3 TB/s; 116 us with 4-byte loads) and the conversion
+// 54 us (6.2 TB/s read and written; 86 us with 1-byte stores and integer
+// rounding).
+__global__ void __launch_bounds__(256) amax_kernel(const float* __restrict__ x, uint64_t n, uint64_t len,
+                                                   float* part) {
+  __shared__ float sm[4];
   const uint64_t lo = (uint64_t)blockIdx.x * len;
   const uint64_t hi = lo + len < n ? lo + len : n;
   float m = 0.0f;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += 256) m = fmaxf(m, fabsf(x[i]));
-  sm[threadIdx.x] = m;
-  __syncthreads();
-  for (uint32_t s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sm[threadIdx.x] = fmaxf(sm[threadIdx.x], sm[threadIdx.x + s]);
-    __syncthreads();
+  auto max4 = [&m](f4u v) { m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w))); };
+  if (lo < hi) {
+    const uint64_t n4 = (hi - lo) / 4;
+    const f4u* x4 = reinterpret_cast<const f4u*>(x + lo);
+    uint64_t i = threadIdx.x;
+    for (; i + 3 * 256 < n4; i += 4 * 256) {
+      f4u v[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(x4 + i + u * 256);
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) max4(v[u]);
+    }
+    for (; i < n4; i += 256) max4(x4[i]);
+    const uint64_t rest = lo + 4 * n4 + threadIdx.x;
+    if (rest < hi) m = fmaxf(m, fabsf(x[rest]));
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = sm[0];
-}
-
-__global__ void __launch_bounds__(256) amax_stage2(const float* part, uint32_t nparts, float* out) {
-  __shared__ float sm[256];
-  float m = 0.0f;
-  for (uint32_t i = threadIdx.x; i < nparts; i += 256) m = fmaxf(m, part[i]);
-  sm[threadIdx.x] = m;
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if ((threadIdx.x & 63u) == 0) sm[threadIdx.x >> 6] = m;
   __syncthreads();
-  for (uint32_t s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sm[threadIdx.x] = fmaxf(sm[threadIdx.x], sm[threadIdx.x + s]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = sm[0];
+  if (threadIdx.x == 0) part[blockIdx.x] = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
 }
 
 // FP32 -> BF16, round to nearest even by integer arithmetic on the bit
@@ -113,11 +119,49 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
   return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
+// Four at once with the conversion instruction, which rounds as to_bf16 does
+// for every FP32 value but NaN (all 2^32 patterns compared); a sum that is
+// NaN sends the four through to_bf16 (a NaN among them, or opposite
+// infinities).
+typedef uint16_t us4 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ us4 to_bf16_4(f4u v) {
+  const float s = (v.x + v.y) + (v.z + v.w);
+  if (__builtin_expect(s != s, 0)) return us4{to_bf16(v.x), to_bf16(v.y), to_bf16(v.z), to_bf16(v.w)};
+  const f4v a = v;
+  return __builtin_bit_cast(us4, __builtin_convertvector(a, bf4v));
+}
+
+// Tiles of kTile elements per work-group, four 16-byte loads per thread in
+// flight; the last, partial tile is walked four elements, then one, at a time.
+constexpr uint32_t kTile = 256 * 16;
+
+template <typename F4, typename F1>
+__device__ __forceinline__ void for_tiles(const float* __restrict__ x, uint64_t n, F4 four, F1 one) {
+  const f4u* x4 = reinterpret_cast<const f4u*>(x);
+  for (uint64_t t = blockIdx.x; t * kTile < n; t += gridDim.x) {
+    const uint64_t i0 = t * (kTile / 4) + threadIdx.x;
+    if ((t + 1) * kTile <= n) {
+      f4u v[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(x4 + i0 + u * 256);
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) four(i0 + u * 256, v[u]);
+    } else {
+      for (uint64_t i = i0; i < n / 4; i += 256) four(i, x4[i]);
+      const uint64_t rest = (n & ~3ull) + threadIdx.x;
+      if (rest < n) one(rest, x[rest]);
+    }
+  }
+}
+
 __global__ void __launch_bounds__(256) to_bf16_kernel(const float* __restrict__ x, uint64_t n,
                                                       uint16_t* __restrict__ out) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-    out[i] = to_bf16(x[i]);
+  us4* o4 = reinterpret_cast<us4*>(out);
+  for_tiles(x, n, [o4](uint64_t i, f4u v) { o4[i] = to_bf16_4(v); },
+            [out](uint64_t i, float v) { out[i] = to_bf16(v); });
 }
 
 // FP32 -> OCP E4M3FN with round-to-nearest-even and saturation at +-448.
@@ -144,14 +188,38 @@ __device__ __forceinline__ uint8_t to_e4m3(float y) {
   return sign | (uint8_t)q;
 }
 
+// Four products x * inv at once: clamped to +-448, the conversion instruction
+// gives to_e4m3's code for every FP32 value but NaN (all 2^32 patterns
+// compared), which takes to_e4m3 itself.
+typedef uint32_t u32u __attribute__((aligned(1)));
+
+__device__ __forceinline__ uint32_t to_e4m3_4(f4u v, float inv) {
+  const float a = __fmul_rn(v.x, inv), b = __fmul_rn(v.y, inv);   // lone products: nothing to contract
+  const float c = __fmul_rn(v.z, inv), d = __fmul_rn(v.w, inv);
+  const float s = (a + b) + (c + d);
+  if (__builtin_expect(s != s, 0))
+    return (uint32_t)to_e4m3(a) | (uint32_t)to_e4m3(b) << 8 | (uint32_t)to_e4m3(c) << 16 | (uint32_t)to_e4m3(d) << 24;
+  const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(a, -448.0f, 448.0f),
+                                                 __builtin_amdgcn_fmed3f(b, -448.0f, 448.0f), 0, false);
+  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(c, -448.0f, 448.0f),
+                                                   __builtin_amdgcn_fmed3f(d, -448.0f, 448.0f), lo, true);
+}
+
 __global__ void __launch_bounds__(256) to_fp8_kernel(const float* __restrict__ x, uint64_t n,
-                                                     const float* __restrict__ amax,
-                                                     uint8_t* __restrict__ out) {
-  const float m = *amax;
+                                                     const float* __restrict__ part, uint32_t nparts,
+                                                     float* amax, uint8_t* __restrict__ out) {
+  __shared__ float sm[4];
+  float m = 0.0f;
+  for (uint32_t i = threadIdx.x; i < nparts; i += 256) m = fmaxf(m, part[i]);
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if ((threadIdx.x & 63u) == 0) sm[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+  if (blockIdx.x == 0 && threadIdx.x == 0) *amax = m;
   const float inv = (m > 0.0f && m <= 3.402823466e38f) ? __fdiv_rn(448.0f, m) : 1.0f;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-    out[i] = to_e4m3(__fmul_rn(x[i], inv));  // a lone product: nothing to contract
+  u32u* o4 = reinterpret_cast<u32u*>(out);
+  for_tiles(x, n, [o4, inv](uint64_t i, f4u v) { o4[i] = to_e4m3_4(v, inv); },
+            [out, inv](uint64_t i, float v) { out[i] = to_e4m3(__fmul_rn(v, inv)); });
 }
 
 __device__ __forceinline__ float uniform_from_word(uint64_t z) {
@@ -210,23 +278,26 @@ void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, d
   *sum = t;
 }
 
-hipError_t launch_amax_f32(const float* x, uint64_t n, float* part, uint32_t nparts, float* out,
-                           hipStream_t s) {
-  const uint64_t len = n ? (n + nparts - 1) / nparts : 1;
-  hipError_t e = xlaunch(amax_stage1, dim3(nparts), dim3(256), 0, s, nullptr, nullptr, x, n, len, part);
-  if (e != hipSuccess) return e;
-  return xlaunch(amax_stage2, dim3(1), dim3(256), 0, s, nullptr, nullptr, part, nparts, out);
+namespace {
+// Work-groups of the tiled kernels: four per CU walk whatever is more (the
+// FP8 conversion of 8192 x 8192 ran 3-5 us slower with 2048 to 16384).
+uint32_t tile_grid(uint64_t n) {
+  const uint64_t t = (n + kTile - 1) / kTile;
+  return (uint32_t)(t > 1024 ? 1024 : t);
 }
+}  // namespace
 
 hipError_t launch_to_bf16(const float* x, uint64_t n, uint16_t* out, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  return xlaunch(to_bf16_kernel, dim3(grid_for(n)), dim3(256), 0, s, nullptr, nullptr, x, n, out);
+  return xlaunch(to_bf16_kernel, dim3(tile_grid(n)), dim3(256), 0, s, nullptr, nullptr, x, n, out);
 }
 
-hipError_t launch_to_fp8(const float* x, uint64_t n, const float* amax, uint8_t* out,
-                         hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  return xlaunch(to_fp8_kernel, dim3(grid_for(n)), dim3(256), 0, s, nullptr, nullptr, x, n, amax, out);
+hipError_t launch_quantize_fp8(const float* x, uint64_t n, float* part, float* amax, uint8_t* out, hipStream_t s) {
+  const uint32_t np = checksum_parts(n);
+  const uint64_t len = ((n + np - 1) / np + 3) & ~3ull;
+  const hipError_t e = xlaunch(amax_kernel, dim3(np), dim3(256), 0, s, nullptr, nullptr, x, n, len, part);
+  if (e != hipSuccess) return e;
+  return xlaunch(to_fp8_kernel, dim3(tile_grid(n)), dim3(256), 0, s, nullptr, nullptr, x, n, part, np, amax, out);
 }
 
 hipError_t launch_fill_uniform(float* dst, uint64_t n, uint64_t seed, hipStream_t s) {

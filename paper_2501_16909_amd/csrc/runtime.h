@@ -16,10 +16,8 @@ struct ci_ctx {
   ci::HostCtrl* host = nullptr;        // pinned: stop / started words
   volatile uint64_t* hres = nullptr;   // pinned: stamps written by kernels
   ci::SumPart* sum_parts = nullptr;    // pinned: kSumParts checksum partials
-  float* amax_part = nullptr;
-  float* amax_out = nullptr;
+  float* amax_part = nullptr;          // device: kSumParts partial maxima
   uint32_t* probe_buf = nullptr;
-  uint32_t nparts = 0;
   std::map<std::array<uint32_t, 8>, hipStream_t> masked;  // CU-masked streams by mask
   std::map<std::array<uint32_t, 8>, uint64_t> masked_used; // last use (use_clock) per mask
   uint64_t use_clock = 0;

@@ -205,9 +205,7 @@ extern "C" ci_status_t ci_init(int device, ci_ctx_t** out) {
   }
   memset((void*)ctx->host, 0, sizeof(HostCtrl));
   memset((void*)ctx->hres, 0, 64 * sizeof(uint64_t));
-  ctx->nparts = 1024;
-  if (hipMalloc((void**)&ctx->amax_part, ctx->nparts * sizeof(float)) != hipSuccess ||
-      hipMalloc((void**)&ctx->amax_out, 256) != hipSuccess ||
+  if (hipMalloc((void**)&ctx->amax_part, kSumParts * sizeof(float)) != hipSuccess ||
       hipMalloc((void**)&ctx->probe_buf, 65536 * sizeof(uint32_t)) != hipSuccess) {
     ci_shutdown(ctx);
     return set_err(CI_ERR_OOM, "ci_init: device scratch");
@@ -278,7 +276,6 @@ extern "C" ci_status_t ci_shutdown(ci_ctx_t* ctx) {
   if (ctx->hres) (void)hipHostFree((void*)ctx->hres);
   if (ctx->sum_parts) (void)hipHostFree(ctx->sum_parts);
   if (ctx->amax_part) (void)hipFree(ctx->amax_part);
-  if (ctx->amax_out) (void)hipFree(ctx->amax_out);
   if (ctx->probe_buf) (void)hipFree(ctx->probe_buf);
   for (auto& kv : ctx->dec_graphs) (void)hipGraphExecDestroy(kv.second);
   ctx->dec_graphs.clear();
@@ -1260,11 +1257,11 @@ extern "C" ci_status_t ci_quantize(ci_ctx_t* ctx, const void* src, uint64_t n, i
     return CI_OK;
   }
   if (dtype != CI_DT_FP8E4M3) return set_err(CI_ERR_INVALID_ARG, "ci_quantize: dtype %d", dtype);
-  HIPCHK(launch_amax_f32((const float*)src, n, ctx->amax_part, ctx->nparts, ctx->amax_out, s));
-  HIPCHK(launch_to_fp8((const float*)src, n, ctx->amax_out, (uint8_t*)dst, s));
-  float amax = 0.0f;
-  HIPCHK(hipMemcpyAsync(&amax, ctx->amax_out, sizeof(float), hipMemcpyDeviceToHost, s));
+  volatile float* hm = (volatile float*)&ctx->hres[4];
+  *hm = 0.0f;
+  if (n) HIPCHK(launch_quantize_fp8((const float*)src, n, ctx->amax_part, (float*)hm, (uint8_t*)dst, s));
   HIPCHK(hipStreamSynchronize(s));
+  const float amax = *hm;
   if (scale_out) {
     volatile float m = amax, q = 448.0f;
     *scale_out = (amax > 0.0f && std::isfinite(amax)) ? (float)(m / q) : 1.0f;
