@@ -149,6 +149,5 @@ hipError_t launch_silu_mul(const float* gu, uint16_t* h, uint32_t f, uint32_t ba
 
 // Victim constraints checked on the host before any launch.
 constexpr uint32_t kTriadThreads = 256;
-constexpr uint32_t kGemmTile = 128;
 
 }  // namespace ci

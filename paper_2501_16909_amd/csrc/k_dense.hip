@@ -6,18 +6,13 @@
 // GEMM layout: A is M x K and B is N x K, both row-major (K contiguous), C is
 // M x N FP32 row-major.  Three kernels, one summation order (each output is
 // the MFMA chain over K in increasing order, so they agree bit for bit):
-//   gemm256d_kernel  256 x 256 tiles, direct global -> LDS loads into a
-//                    4-stage ring; shapes with >= 256 tiles and K * element
-//                    size a multiple of 64 bytes;
-//   gemm256_kernel   256 x 256 tiles staged through registers, other
-//                    shapes with >= 256 tiles;
-//   gemm_kernel      128 x 128 tiles for smaller shapes: a 256-thread
-//                    work-group, four waves of 64 x 64 (2 x 2 MFMA tiles of
-//                    32 x 32), K in stages of 128 bytes per row
-//                    double-buffered in LDS through registers.
-// Rows and K chunks past the matrix edges read as zero (register-staged
-// kernels) or only feed outputs that are not stored (ring kernel), so any M
-// and N work; K * element size must be a multiple of 16.
+//   gemm_tile_kernel  tiles of 64 x 64, 128 x 64 or 128 x 128, four waves;
+//                     every shape;
+//   gemm256d_kernel   BF16 and FP8, 256 x 256 tiles, eight waves in two
+//                     alternating groups;
+//   gemm256f_kernel   FP32, 256 x 256 tiles, eight waves.
+// All move operands straight from global memory into LDS, 16 bytes per lane.
+// K * element size must be a multiple of 16; any M and N work.
 #include <type_traits>
 
 #include "internal.h"
@@ -25,58 +20,99 @@
 namespace ci {
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBM = 128, kBN = 128;
-constexpr int kStageBytes = 128;                 // K bytes per stage per row
-constexpr int kRowPitch = kStageBytes + 16;      // LDS row pitch (bank spread)
-constexpr int kTileLds = 128 * kRowPitch;        // one operand, one stage
+// A K-stage in LDS: 128 bytes of each row, so that every row of a load is a
+// whole cache line (64-byte stages reached three quarters of the rate from
+// L2).  The 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7): the 16
+// rows a fragment read touches at a time fall on 16 distinct chunk positions
+// of the banks, and a 1 KiB load (eight rows, lane l filling bytes 16 l) still
+// fills its rows in place.
+constexpr uint32_t kStage = 128;
 
+__device__ __forceinline__ uint32_t stage_at(uint32_t row, uint32_t byte) {
+  return row * kStage + ((((byte >> 4) ^ (row >> 1)) & 7u) << 4) + (byte & 15u);
+}
+
+// Logical chunk that lane `lane` of a load carries for row `row`.
+__device__ __forceinline__ uint32_t lane_chunk(uint32_t lane, uint32_t row) {
+  return ((lane & 7u) ^ (row >> 1)) & 7u;
+}
+
+__device__ __forceinline__ void load16_lds(const uint8_t* g, uint8_t* l) {
+  __builtin_amdgcn_global_load_lds(g, l, 16, 0, 0);
+}
+
+// Operand fragments and products.  kStep: K bytes one fragment covers (k-step);
+// off: the lane's byte offset inside it; cut: zero what lies past `rem` bytes.
 template <int DT>
-struct Gemm;
+struct Op;
 
+// FP32: a fragment is one 16-byte chunk, four k and two instructions; both
+// halves of the wave read it whole and half h takes k = 2 t + h.
 template <>
-struct Gemm<CI_DT_F32> {
+struct Op<CI_DT_F32> {
+  using T = f32x4;
   static constexpr int kElem = 4;
-  static constexpr int kFragBytes = 4;     // per lane per MFMA operand
-  static constexpr int kSub = kStageBytes / (2 * kFragBytes);
-  __device__ static f32x16 mma(const uint8_t* pa, const uint8_t* pb, f32x16 acc) {
-    const float a = *reinterpret_cast<const float*>(pa);
-    const float b = *reinterpret_cast<const float*>(pb);
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+  static constexpr int kStep = 16;
+  __device__ static uint32_t off(uint32_t) { return 0; }
+  __device__ static T ld(const uint8_t* p, uint32_t row, uint32_t kb) {
+    return *reinterpret_cast<const f32x4*>(p + stage_at(row, kb));
+  }
+  __device__ static void cut(T& f, uint32_t kb, uint32_t rem) {
+    if (kb + 16 > rem) f = f32x4{0, 0, 0, 0};
+  }
+  __device__ static f32x16 mma(const T& a, const T& b, f32x16 c, uint32_t lane) {
+    const bool h = lane >= 32;
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(h ? a.y : a.x, h ? b.y : b.x, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(h ? a.w : a.z, h ? b.w : b.z, c, 0, 0, 0);
   }
 };
 
 template <>
-struct Gemm<CI_DT_BF16> {
+struct Op<CI_DT_BF16> {
+  using T = bf16x8;
   static constexpr int kElem = 2;
-  static constexpr int kFragBytes = 16;
-  static constexpr int kSub = kStageBytes / (2 * kFragBytes);
-  __device__ static f32x16 mma(const uint8_t* pa, const uint8_t* pb, f32x16 acc) {
-    const bf16x8 a = *reinterpret_cast<const bf16x8*>(pa);
-    const bf16x8 b = *reinterpret_cast<const bf16x8*>(pb);
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+  static constexpr int kStep = 32;
+  __device__ static uint32_t off(uint32_t lane) { return (lane >> 5) * 16; }
+  __device__ static T ld(const uint8_t* p, uint32_t row, uint32_t kb) {
+    return *reinterpret_cast<const bf16x8*>(p + stage_at(row, kb));
+  }
+  __device__ static void cut(T& f, uint32_t kb, uint32_t rem) {
+    if (kb + 16 > rem) f = __builtin_bit_cast(bf16x8, i32x4{0, 0, 0, 0});
+  }
+  __device__ static f32x16 mma(const T& a, const T& b, f32x16 c, uint32_t) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
 };
 
 template <>
-struct Gemm<CI_DT_FP8E4M3> {
+struct Op<CI_DT_FP8E4M3> {
+  using T = i32x8;
   static constexpr int kElem = 1;
-  static constexpr int kFragBytes = 32;
-  static constexpr int kSub = kStageBytes / (2 * kFragBytes);
-  __device__ static f32x16 mma(const uint8_t* pa, const uint8_t* pb, f32x16 acc) {
-    const i32x4 a0 = *reinterpret_cast<const i32x4*>(pa);
-    const i32x4 a1 = *reinterpret_cast<const i32x4*>(pa + 16);
-    const i32x4 b0 = *reinterpret_cast<const i32x4*>(pb);
-    const i32x4 b1 = *reinterpret_cast<const i32x4*>(pb + 16);
-    const i32x8 a = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-    const i32x8 b = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 0, 0, 0, 0, 0, 0);
+  static constexpr int kStep = 64;
+  __device__ static uint32_t off(uint32_t lane) { return (lane >> 5) * 32; }
+  __device__ static T ld(const uint8_t* p, uint32_t row, uint32_t kb) {
+    const i32x4 a0 = *reinterpret_cast<const i32x4*>(p + stage_at(row, kb));
+    const i32x4 a1 = *reinterpret_cast<const i32x4*>(p + stage_at(row, kb + 16));
+    return i32x8{a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
+  }
+  __device__ static void cut(T& f, uint32_t kb, uint32_t rem) {
+    const int lo = kb + 16 <= rem ? -1 : 0, hi = kb + 32 <= rem ? -1 : 0;
+    f = f & i32x8{lo, lo, lo, lo, hi, hi, hi, hi};
+  }
+  __device__ static f32x16 mma(const T& a, const T& b, f32x16 c, uint32_t) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
   }
 };
+
+// s_waitcnt operands: vector-memory count n with no other wait, and LDS reads.
+constexpr int kWaitLds = 0xC07F;
+constexpr int wait_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
 // Map the work-group index to a C tile.  Work-groups are dealt to the 8
 // XCDs round-robin, so first each XCD gets a contiguous range of tile
@@ -96,253 +132,366 @@ __device__ __forceinline__ void tile_of(uint32_t bid, uint32_t nbm, uint32_t nbn
   tn = r / rows;
 }
 
-template <int DT>
-__global__ void __launch_bounds__(256, 2) gemm_kernel(const uint8_t* __restrict__ A,
-                                                      const uint8_t* __restrict__ B,
-                                                      float* __restrict__ C, uint32_t M, uint32_t N,
-                                                      uint32_t K, float scale) {
-  using G = Gemm<DT>;
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  uint8_t* sA = smem;                  // [2][128][kRowPitch]
-  uint8_t* sB = smem + 2 * kTileLds;   // [2][128][kRowPitch]
-  const uint32_t nbm = (M + kBM - 1) / kBM, nbn = (N + kBN - 1) / kBN;
+// General tile kernel: a work-group of four waves (2 x 2, each TM/2 x TN/2)
+// owns a TM x TN tile of C, two K-stages in LDS.  A stage is two halves of
+// k-steps with a fragment buffer each: while one half multiplies, the other's
+// fragments are read, across stage boundaries too.  One barrier per stage:
+// after it the next stage is in LDS and the finished one's slot takes the
+// stage after.  LDS per work-group is 32, 48 or 64 KiB, so two to five share a
+// CU and cover each other's barriers and load latency; a third slot instead of
+// the second work-group was slower (BF16 4096^3 166 against 135 us).
+// What bounds it: at one work-group per CU the chain of load, barrier and
+// fragment read of every stage (BF16 512^3: 4.7 us against 10.6 us for the
+// register-staged 128 x 128 kernel it replaces, 1024^3 7.5 against 18.2); with
+// several, the matrix core (FP32 1416 x 1402 x 1416 65 against 115 us, where
+// 132 tiles of 128 x 128 left half the CUs idle; floor 36 us).
+// Rows past the edge repeat the last one and feed outputs that are not
+// stored; in a short last stage, chunks past its end repeat its last one and
+// the fragments there are zeroed.
+template <int DT, int TM, int TN>
+__global__ void __launch_bounds__(256, TM * TN >= 128 * 128 ? 2 : 1)
+gemm_tile_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, float* __restrict__ C, uint32_t M,
+                 uint32_t N, uint32_t K, float scale) {
+  using F = Op<DT>;
+  constexpr int W = 4, IN = TM / 64, JN = TN / 64;                 // waves; 32 x 32 tiles per wave
+  constexpr int kOpA = TM * kStage, kSlot = (TM + TN) * kStage;
+  constexpr int OA = TM / 8 / W, OPS = (TM + TN) / 8 / W;          // 1 KiB loads per wave and stage: A, all
+  constexpr int NS = kStage / F::kStep / 2;                        // k-steps per half stage
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const uint32_t nbm = (M + TM - 1) / TM, nbn = (N + TN - 1) / TN;
   uint32_t tm, tn;
-  tile_of(blockIdx.x, nbm, nbn, tm, tn);
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
-  const uint32_t wm = wid >> 1, wn = wid & 1u;   // wave's 64x64 sub-tile
-  const uint64_t rowBytes = (uint64_t)K * G::kElem;
-  const uint32_t nstages = (uint32_t)((rowBytes + kStageBytes - 1) / kStageBytes);
-
-  // global -> register staging: thread loads 16 B at (row = tid/8 + 32 j, chunk = tid%8)
-  const uint32_t lrow = tid >> 3, lchunk = tid & 7u;
-  i32x4 ra[4], rb[4];
-  auto gload = [&](uint32_t st) {
-    const uint64_t kb = (uint64_t)st * kStageBytes + lchunk * 16u;
-    const bool kin = kb + 16 <= rowBytes;
+  tile_of<8>(blockIdx.x, nbm, nbn, tm, tn);
+  const uint32_t lane = threadIdx.x & 63u, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t wm = wid >> 1, wn = wid & 1u;
+  const uint64_t rowBytes = (uint64_t)K * F::kElem;
+  const uint32_t nst = (uint32_t)((rowBytes + kStage - 1) / kStage);
+  const uint32_t rem = (uint32_t)(rowBytes - (uint64_t)(nst - 1) * kStage);   // bytes of the last stage, 16..128
+  // load o of a wave fills rows 8 (wid + W o) .. + 7 of an operand, lane l row l / 8
+  auto load_row = [&](int o) { return 8u * (wid + W * (o < OA ? o : o - OA)) + (lane >> 3); };
+  const uint8_t* src[OPS];      // this lane's 16 bytes of the next stage to load
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t r = lrow + 32u * j;
-      const uint32_t gm = tm * kBM + r, gn = tn * kBN + r;
-      ra[j] = (kin && gm < M) ? *reinterpret_cast<const i32x4*>(A + gm * rowBytes + kb) : i32x4{0, 0, 0, 0};
-      rb[j] = (kin && gn < N) ? *reinterpret_cast<const i32x4*>(B + gn * rowBytes + kb) : i32x4{0, 0, 0, 0};
-    }
-  };
-  auto sstore = [&](uint32_t buf) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t r = lrow + 32u * j;
-      *reinterpret_cast<i32x4*>(sA + buf * kTileLds + r * kRowPitch + lchunk * 16u) = ra[j];
-      *reinterpret_cast<i32x4*>(sB + buf * kTileLds + r * kRowPitch + lchunk * 16u) = rb[j];
-    }
-  };
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  const uint32_t frow = lane & 31u, fk = (lane >> 5) * G::kFragBytes;
-  for (uint32_t st = 0; st < nstages; ++st) {
-    const uint32_t buf = st & 1u;
-    if (st + 1 < nstages) gload(st + 1);
-    const uint8_t* a0 = sA + buf * kTileLds + (wm * 64 + frow) * kRowPitch + fk;
-    const uint8_t* b0 = sB + buf * kTileLds + (wn * 64 + frow) * kRowPitch + fk;
-#pragma unroll
-    for (int s = 0; s < G::kSub; ++s) {
-      const uint32_t ko = s * 2 * G::kFragBytes;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = G::mma(a0 + i * 32 * kRowPitch + ko, b0 + j * 32 * kRowPitch + ko, acc[i][j]);
-    }
-    if (st + 1 < nstages) sstore(buf ^ 1u);
-    __syncthreads();
+  for (int o = 0; o < OPS; ++o) {
+    const uint32_t r = load_row(o);
+    const uint64_t g = o < OA ? min(tm * TM + r, M - 1) : min(tn * TN + r, N - 1);
+    src[o] = (o < OA ? A : B) + g * rowBytes + lane_chunk(lane, r) * 16u;
   }
-
+  auto issue = [&](uint32_t st) {
+    uint8_t* slot = smem + (st & 1u) * kSlot;
+    if (st + 1 == nst && rem < kStage) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t col = tn * kBN + wn * 64 + j * 32 + (lane & 31u);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const uint32_t row = tm * kBM + wm * 64 + i * 32 + 8u * (v / 4) + 4u * (lane >> 5) + (v % 4);
-        if (row < M && col < N) C[(uint64_t)row * N + col] = acc[i][j][v] * scale;
+      for (int o = 0; o < OPS; ++o) {
+        const uint32_t c = lane_chunk(lane, load_row(o));
+        src[o] -= (c - min(c, rem / 16 - 1)) * 16u;
       }
     }
-}
-
-// Large-tile GEMM: one work-group per CU owns a 256 x 256 tile of C, with
-// WAVES waves in a 2 x WAVES/2 grid: each wave owns 128 x (512/WAVES)
-// (4 x 1024/(32 WAVES) MFMA tiles of 32 x 32), so every A fragment read from
-// LDS feeds several MFMAs.  With 8 waves two share each SIMD, so one wave's
-// LDS reads and barrier waits overlap the other's MFMAs.  Two 72 KiB
-// K-stages of A and B are double-buffered in LDS (144 KiB of the CU's
-// 160 KiB), filled through registers while the other stage computes.
-constexpr int kBig = 256;
-constexpr int kBigTileLds = kBig * kRowPitch;    // one operand, one stage
-constexpr int kBigWaves = 8;
-
-template <int DT, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES, 1) gemm256_kernel(const uint8_t* __restrict__ A,
-                                                                const uint8_t* __restrict__ B,
-                                                                float* __restrict__ C, uint32_t M,
-                                                                uint32_t N, uint32_t K, float scale) {
-  using G = Gemm<DT>;
-  constexpr int NT = 64 * WAVES;          // threads
-  constexpr int WN = WAVES / 2;           // waves along N
-  constexpr int JN = kBig / WN / 32;      // 32-wide MFMA tiles per wave along N
-  constexpr int LR = kBig / (NT / 8);     // rows each thread stages per operand
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  uint8_t* sA = smem;                     // [2][256][kRowPitch]
-  uint8_t* sB = smem + 2 * kBigTileLds;   // [2][256][kRowPitch]
-  const uint32_t nbm = (M + kBig - 1) / kBig, nbn = (N + kBig - 1) / kBig;
-  uint32_t tm, tn;
-  tile_of(blockIdx.x, nbm, nbn, tm, tn);
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
-  const uint32_t wm = wid / WN, wn = wid % WN;   // wave's 128 x (256/WN) sub-tile
-  const uint64_t rowBytes = (uint64_t)K * G::kElem;
-  const uint32_t nstages = (uint32_t)((rowBytes + kStageBytes - 1) / kStageBytes);
-  // global -> register staging: thread loads 16 B at (row = tid/8 + NT/8 j, chunk = tid%8)
-  const uint32_t lrow = tid >> 3, lchunk = tid & 7u;
-  i32x4 ra[LR], rb[LR];
-  auto gload = [&](uint32_t st) {
-    const uint64_t kb = (uint64_t)st * kStageBytes + lchunk * 16u;
-    const bool kin = kb + 16 <= rowBytes;
 #pragma unroll
-    for (int j = 0; j < LR; ++j) {
-      const uint32_t r = lrow + (NT / 8) * j;
-      const uint32_t gm = tm * kBig + r, gn = tn * kBig + r;
-      ra[j] = (kin && gm < M) ? *reinterpret_cast<const i32x4*>(A + gm * rowBytes + kb) : i32x4{0, 0, 0, 0};
-      rb[j] = (kin && gn < N) ? *reinterpret_cast<const i32x4*>(B + gn * rowBytes + kb) : i32x4{0, 0, 0, 0};
+    for (int o = 0; o < OPS; ++o) {
+      load16_lds(src[o], slot + (o < OA ? (wid + W * o) * 1024u : kOpA + (wid + W * (o - OA)) * 1024u));
+      src[o] += kStage;
     }
   };
-  auto sstore = [&](uint32_t buf) {
+  f32x16 acc[IN][JN];
 #pragma unroll
-    for (int j = 0; j < LR; ++j) {
-      const uint32_t r = lrow + (NT / 8) * j;
-      *reinterpret_cast<i32x4*>(sA + buf * kBigTileLds + r * kRowPitch + lchunk * 16u) = ra[j];
-      *reinterpret_cast<i32x4*>(sB + buf * kBigTileLds + r * kRowPitch + lchunk * 16u) = rb[j];
-    }
-  };
-  f32x16 acc[4][JN];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < IN; ++i)
 #pragma unroll
     for (int j = 0; j < JN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  const uint32_t frow = lane & 31u, fk = (lane >> 5) * G::kFragBytes;
-  for (uint32_t st = 0; st < nstages; ++st) {
-    const uint32_t buf = st & 1u;
-    if (st + 1 < nstages) gload(st + 1);
-    const uint8_t* a0 = sA + buf * kBigTileLds + (wm * 128 + frow) * kRowPitch + fk;
-    const uint8_t* b0 = sB + buf * kBigTileLds + (wn * (kBig / WN) + frow) * kRowPitch + fk;
+  const uint32_t frow = lane & 31u, fk = F::off(lane);
+  typename F::T fa[2][NS][IN], fb[2][NS][JN];
+  auto read_ks = [&](uint32_t st, auto half, int s) {
+    constexpr int b = decltype(half)::value;
+    const uint8_t* slot = smem + (st & 1u) * kSlot;
+    const uint32_t kb = b * (kStage / 2) + fk + s * F::kStep;
 #pragma unroll
-    for (int s = 0; s < G::kSub; ++s) {
-      const uint32_t ko = s * 2 * G::kFragBytes;
+    for (int i = 0; i < IN; ++i) fa[b][s][i] = F::ld(slot, wm * (TM / 2) + i * 32 + frow, kb);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < JN; ++j) fb[b][s][j] = F::ld(slot + kOpA, wn * (TN / 2) + j * 32 + frow, kb);
+  };
+  auto mma_ks = [&](auto half, int s) {
+    constexpr int b = decltype(half)::value;
 #pragma unroll
-        for (int j = 0; j < JN; ++j)
-          acc[i][j] = G::mma(a0 + i * 32 * kRowPitch + ko, b0 + j * 32 * kRowPitch + ko, acc[i][j]);
+    for (int i = 0; i < IN; ++i)
+#pragma unroll
+      for (int j = 0; j < JN; ++j) acc[i][j] = F::mma(fa[b][s][i], fb[b][s][j], acc[i][j], lane);
+  };
+  using H0 = std::integral_constant<int, 0>;
+  using H1 = std::integral_constant<int, 1>;
+  issue(0);
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));
+  __builtin_amdgcn_s_barrier();
+  if (nst > 1) issue(1);
+#pragma unroll
+  for (int s = 0; s < NS; ++s) read_ks(0, H0{}, s);
+  uint32_t st = 0;
+  for (; st + 1 < nst; ++st) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      read_ks(st, H1{}, s);
+      mma_ks(H0{}, s);
     }
-    if (st + 1 < nstages) sstore(buf ^ 1u);
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitLds);     // this wave's reads of the slot are done
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));   // its part of stage st + 1 has landed
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      read_ks(st + 1, H0{}, s);
+      if (s == NS - 1 && st + 2 < nst) issue(st + 2);
+      mma_ks(H1{}, s);
+    }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int s = 0; s < NS; ++s) read_ks(st, H1{}, s);
+  if (rem < kStage) {
+    auto cut_half = [&](auto half) {
+      constexpr int b = decltype(half)::value;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const uint32_t kb = b * (kStage / 2) + fk + s * F::kStep;
+#pragma unroll
+        for (int i = 0; i < IN; ++i) F::cut(fa[b][s][i], kb, rem);
+#pragma unroll
+        for (int j = 0; j < JN; ++j) F::cut(fb[b][s][j], kb, rem);
+      }
+    };
+    cut_half(H0{});
+    cut_half(H1{});
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) mma_ks(H0{}, s);
+  if (rem > kStage / 2)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) mma_ks(H1{}, s);
+#pragma unroll
+  for (int i = 0; i < IN; ++i)
 #pragma unroll
     for (int j = 0; j < JN; ++j) {
-      const uint32_t col = tn * kBig + wn * (kBig / WN) + j * 32 + (lane & 31u);
+      const uint32_t col = tn * TN + wn * (TN / 2) + j * 32 + (lane & 31u);
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const uint32_t row = tm * kBig + wm * 128 + i * 32 + 8u * (v / 4) + 4u * (lane >> 5) + (v % 4);
+        const uint32_t row = tm * TM + wm * (TM / 2) + i * 32 + 8u * (v / 4) + 4u * (lane >> 5) + (v % 4);
         if (row < M && col < N) C[(uint64_t)row * N + col] = acc[i][j][v] * scale;
       }
     }
 }
 
+// Large-tile kernel of BF16 and FP8: one work-group per CU owns a 256 x 256
+// tile, eight waves in a 2 x 4 grid, each 128 x 64 (4 x 2 MFMA tiles), two
+// K-stages of 64 KiB in LDS.  The two rows of waves (wm 0 and 1, one wave of
+// each per SIMD) run one phase apart: in a phase one row reads half a stage's
+// fragments and issues loads while the other multiplies its half, and a
+// barrier ends the phase, so the matrix core of every SIMD always has one
+// wave's sixteen (FP8: eight) MFMAs ahead of it.
+//   Loads of stage st + 1 go into the slot of st - 1, free once the later row
+// has read its second half: half of them with the first fragment reads of st,
+// half behind the first MFMAs, which spreads them over the load path.
+//   FAR (more tiles than CUs): each stage also touches its share of the lines
+// that the XCD's block of tiles needs kAhead stages later.  The 32 tiles an
+// XCD computes at a time share their panels, so without this only two stages
+// of each panel are ever on their way into its L2, and their latency, not a
+// bandwidth, sets the rate (loads alone: 8192^3 780 us without, 567 with).
+// Edge tiles start early and overlap their neighbour, so every row read
+// exists; rows or columns that are the neighbour's are not stored.
+// What bounds it: with random operands the part lowers its clock under MFMA
+// load (1.6-1.9 GHz measured in the loop), and the loop with its loads left out
+// runs 8192^3 BF16 in 737 us; with them a phase takes 705 clocks instead of
+// 566, the load path being shared with the fragment reads.  BF16 8192^3
+// 880 us (1250 TF; 1005-1110 us for the one-group ring before it), FP8
+// 412 us (2670 TF; 500-610), BF16 4096^3 114-120 us (128-146).
+// At most 192 registers per wave and 129 KiB of LDS, so that two 64-register
+// stressor waves per SIMD and their LDS still fit beside it.
+constexpr uint32_t kBig = 256;
+constexpr uint32_t kBigOp = kBig * kStage;          // one operand of a stage
+constexpr uint32_t kBigSlot = 2 * kBigOp;
+constexpr uint32_t kBigLds = 2 * kBigSlot + 256;    // and 256 bytes that FAR's touches land in
+constexpr uint32_t kAhead = 4;
+static_assert(kBigLds <= 129 * 1024, "the slots must leave LDS for a co-resident work-group");
 
-// Large-tile GEMM with direct global -> LDS loads (16 bytes per lane,
-// lane l of a wave instruction filling bytes 16 l of a 1 KiB block) into a
-// 4-deep ring of K-stages of 64 bytes per row: two or three later stages
-// are in flight while a stage computes, without staging registers.  Rows are
+template <int DT, bool FAR>
+__global__ void __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(192)))
+gemm256d_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, float* __restrict__ C, uint32_t M,
+                uint32_t N, uint32_t K, float scale) {
+  using F = Op<DT>;
+  constexpr int IN = 4, JN = 2, NS = kStage / F::kStep / 2;
+  constexpr uint32_t BAND = FAR ? 4 : 8;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const uint32_t nbm = (M + kBig - 1) / kBig, nbn = (N + kBig - 1) / kBig;
+  uint32_t tm, tn;
+  tile_of<BAND>(blockIdx.x, nbm, nbn, tm, tn);
+  const uint32_t lane = threadIdx.x & 63u, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t wm = wid >> 2, wn = wid & 3u;
+  const uint32_t rowBytes = K * F::kElem;           // at most kBigMaxRow
+  const uint32_t nhalf = (rowBytes + kStage / 2 - 1) / (kStage / 2), nst = (nhalf + 1) / 2;
+  const uint32_t last = (rowBytes - (nst - 1) * kStage) / 16 - 1;      // last chunk of the last stage
+  const bool cut_last = rowBytes % (kStage / 2) != 0;
+  const uint32_t m0 = min(tm * kBig, M - kBig), n0 = min(tn * kBig, N - kBig);
+  const uint8_t* baseA = A + (uint64_t)m0 * rowBytes;
+  const uint8_t* baseB = B + (uint64_t)n0 * rowBytes;
+  // load h of a wave and operand fills rows 8 (wid + 8 h) .. + 7: one lane
+  // offset serves all, the rest of the address is uniform
+  const uint32_t lrow = 8u * wid + (lane >> 3);
+  uint32_t vo = lrow * rowBytes + lane_chunk(lane, lrow) * 16u;
+  const uint64_t step = 64ull * rowBytes;
+  auto issue = [&](uint32_t st, int h0, int h1) {
+    uint8_t* slot = smem + (st & 1u) * kBigSlot;
+    const uint64_t k = (uint64_t)st * kStage;
+    if (h0 == 0 && st + 1 == nst && last < 7) {   // chunks past the end of a short last stage repeat its last one
+      const uint32_t t = threadIdx.x & 63u, c = lane_chunk(t, 8u * wid + (t >> 3));
+      vo -= (c - min(c, last)) * 16u;
+    }
+#pragma unroll
+    for (int h = h0; h < h1; ++h) {
+      const uint32_t blk = (wid + 8u * h) * 1024u;
+      load16_lds(baseA + k + h * step + vo, slot + blk);
+      load16_lds(baseB + k + h * step + vo, slot + kBigOp + blk);
+    }
+  };
+  // touched per stage: 32 rows of A (its panel is shared by the 8 tiles of a
+  // band's row that run together) and 64 of B (shared by 4), waves 0-3 and 4-7
+  const uint8_t* far = wid < 4 ? baseA : baseB;
+  const uint32_t far_n = wid < 4 ? 8u : 16u;
+  const uint32_t far_o = ((wid < 4 ? (tn & 7u) * 32u : (tm & 3u) * 64u) + (wid & 3u) * far_n + min(lane, far_n - 1)) * rowBytes;
+  auto touch = [&](uint32_t st) {
+    if constexpr (FAR)
+      __builtin_amdgcn_global_load_lds(far + min(st * kStage, rowBytes - 16u) + far_o, smem + 2 * kBigSlot, 4, 0, 0);
+  };
+  f32x16 acc[IN][JN];
+#pragma unroll
+  for (int i = 0; i < IN; ++i)
+#pragma unroll
+    for (int j = 0; j < JN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+  const uint32_t frow = lane & 31u, fk = F::off(lane);
+  typename F::T fa[NS][IN], fb[NS][JN];
+  auto read_half = [&](uint32_t st, uint32_t half) {
+    const uint8_t* slot = smem + (st & 1u) * kBigSlot;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint32_t kb = half * (kStage / 2) + fk + s * F::kStep;
+#pragma unroll
+      for (int i = 0; i < IN; ++i) fa[s][i] = F::ld(slot, wm * 128 + i * 32 + frow, kb);
+#pragma unroll
+      for (int j = 0; j < JN; ++j) fb[s][j] = F::ld(slot + kBigOp, wn * 64 + j * 32 + frow, kb);
+    }
+  };
+  // zero what a short last stage holds past the end of the rows
+  auto clear_tail = [&](uint32_t st) {
+    uint8_t* slot = smem + (st & 1u) * kBigSlot;
+    int z;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(z));     // made here: a constant would hold four registers through the loop
+    for (uint32_t row = threadIdx.x & (kBig - 1); row < 2 * kBig; row += kBig)     // rows of A, then of B
+      for (uint32_t c = last + 1; c < 8; ++c)
+        *reinterpret_cast<i32x4*>(slot + stage_at(row, c * 16u)) = i32x4{z, z, z, z};
+    __builtin_amdgcn_s_waitcnt(kWaitLds);
+  };
+  auto multiply = [&] {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int i = 0; i < IN; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j) acc[i][j] = F::mma(fa[s][i], fb[s][j], acc[i][j], lane);
+  };
+  // The phases are fenced: nothing moves across a barrier.
+  auto phase_end = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int kTouch = FAR ? 1 : 0;     // the newest load of a stage is its touch, which nobody waits for
+  const bool late = wm != 0;
+  issue(0, 0, 4);
+  if constexpr (FAR)
+#pragma unroll
+    for (uint32_t q = 2; q <= kAhead; ++q) touch(q);
+  __builtin_amdgcn_s_waitcnt(wait_vm(FAR ? kAhead - 1 : 0));
+  phase_end();
+  if (late) phase_end();
+  for (uint32_t st = 0; st < nst; ++st) {
+    const bool more = st + 1 < nst;
+    if (cut_last && !more) {      // one phase more: the earlier row clears, the later one waits
+      if (!late) clear_tail(st);
+      phase_end();
+    }
+    read_half(st, 0);
+    if (more) issue(st + 1, 0, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitLds);
+    phase_end();
+    __builtin_amdgcn_s_setprio(1);
+    if (more) issue(st + 1, 2, 4);
+    touch(st + kAhead + 1);
+    multiply();
+    __builtin_amdgcn_s_setprio(0);
+    phase_end();
+    if (2 * st + 1 < nhalf) {
+      read_half(st, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      // stage st + 1 must have landed, for both rows, before the earlier row reads it
+      if (late) __builtin_amdgcn_s_waitcnt(wait_vm(kTouch));
+      __builtin_amdgcn_s_waitcnt(kWaitLds);
+      phase_end();
+      __builtin_amdgcn_s_setprio(1);
+      multiply();
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!late) __builtin_amdgcn_s_waitcnt(wait_vm(kTouch));
+      phase_end();
+    }
+  }
+  if (!late) phase_end();
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));   // no load may reach LDS after this work-group's end
+  const uint32_t row0 = m0 + wm * 128 + 4u * (lane >> 5), col0 = n0 + wn * 64 + (lane & 31u);
+  const bool whole = m0 == tm * kBig && n0 == tn * kBig;
+#pragma unroll
+  for (int i = 0; i < IN; ++i)
+#pragma unroll
+    for (int j = 0; j < JN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint32_t row = row0 + i * 32 + 8u * (v / 4) + (v % 4), col = col0 + j * 32;
+        if (whole || (row >= tm * kBig && col >= tn * kBig)) C[(uint64_t)row * N + col] = acc[i][j][v] * scale;
+      }
+}
+
+// Large-tile kernel of FP32: 256 x 256 tiles, eight waves (2 x 4, each 128 x
+// 64; two per SIMD) and a ring of four K-stages of 64 bytes per row.  Rows are
 // stored unpadded; the 16-byte chunk c of row r sits at chunk
-// c ^ ((r >> 2) & 3), so the 32 rows a fragment read touches fall on
-// distinct banks.  Eight waves (2 x 4, each 128 x 64; two per SIMD) read
-// fragments into registers and issue the MFMAs; with two MFMA k-steps per
-// stage or more (FP32, BF16) the reads of the next k-step overlap the
-// current one's MFMAs.  One bare barrier per stage: each wave first waits
-// for its own loads of the stage (s_waitcnt on the vector-memory counter),
-// so after the barrier the whole stage is in LDS; a fence there would also
-// wait for the later stages' loads.  Needs K * element size to be a
-// multiple of 64 bytes; the register-staged kernel above takes the rest.
-// What bounds it: while MFMAs run, a SIMD takes in about one 1 KiB fragment
-// load from LDS per 64 cycles, and a 128 x 64 wave tile issues six per eight
-// 32 x 32 MFMAs, which caps the matrix core near two thirds of its rate even
-// with no memory traffic or barriers (measured); larger wave tiles need more
-// registers than two waves per SIMD have.
+// c ^ ((r >> 2) & 3).  Two fragment buffers of one k-step (two k) each: a
+// k-step's block is its first MFMA, then the next k-step's reads, then its
+// other MFMAs, fenced in that order, so that the reads have seven MFMAs to
+// land (4 % over the compiler's order).  One bare barrier per stage: each wave
+// first waits for its own loads of the stage, so after the barrier the whole
+// stage is in LDS; the reads of a stage's last k-step are waited for after the
+// next stage's barrier, so that barrier frees the slot of the stage before:
+// stage t + 2 is issued at the barrier of stage t into the slot of t - 2.
+// A short last stage ends after its last whole chunk (two k-steps); its loads
+// past the row's end repeat the row's last chunk.
+// What bounds it: the matrix core, at 86 % of its rate (4096^3 1010 us, 136
+// TF; tiles of 128 x 128 take 1130 us).  Its MFMAs are four times as long as
+// BF16's for the same bytes, so neither loads nor barriers weigh enough for the
+// alternating groups of the other types (1237 us).
 // Four slots of 32 KiB: 128 KiB of the CU's 160 KiB, leaving 32 KiB for a
-// co-resident stressor work-group.  Five slots (loads three stages ahead)
-// ran at the same rate within run-to-run spread, but fill the whole LDS, so
-// no work-group holding any LDS could share a CU with the victim.
+// co-resident stressor work-group.
 constexpr int kRingStages = 4;
 constexpr int kDStage = 64;                         // K bytes per stage per row
 constexpr int kDOperand = kBig * kDStage;           // one operand, one stage (16 KiB)
 constexpr int kDSlot = 2 * kDOperand;               // A and B of one stage
 static_assert(kRingStages * kDSlot <= 128 * 1024, "the ring must leave LDS for a co-resident work-group");
 
-__device__ __forceinline__ uint32_t dswz(uint32_t row, uint32_t byte) {
-  return row * kDStage + ((((byte >> 4) ^ (row >> 2)) & 3u) << 4) + (byte & 15u);
+__device__ __forceinline__ float ring_ld(const uint8_t* p, uint32_t row, uint32_t byte) {
+  return *reinterpret_cast<const float*>(p + row * kDStage + ((((byte >> 4) ^ (row >> 2)) & 3u) << 4) + (byte & 15u));
 }
 
-// One MFMA operand fragment per lane, read from a swizzled LDS stage.
-template <int DT> struct Frag;
-template <> struct Frag<CI_DT_F32> {
-  using T = float;
-  __device__ static T ld(const uint8_t* p, uint32_t row, uint32_t kb) {
-    return *reinterpret_cast<const float*>(p + dswz(row, kb));
-  }
-  __device__ static f32x16 mma(T a, T b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
-};
-template <> struct Frag<CI_DT_BF16> {
-  using T = bf16x8;
-  __device__ static T ld(const uint8_t* p, uint32_t row, uint32_t kb) {
-    return *reinterpret_cast<const bf16x8*>(p + dswz(row, kb));
-  }
-  __device__ static f32x16 mma(T a, T b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
-};
-template <> struct Frag<CI_DT_FP8E4M3> {
-  using T = i32x8;
-  __device__ static T ld(const uint8_t* p, uint32_t row, uint32_t kb) {
-    const i32x4 a0 = *reinterpret_cast<const i32x4*>(p + dswz(row, kb));
-    const i32x4 a1 = *reinterpret_cast<const i32x4*>(p + dswz(row, kb + 16));
-    return i32x8{a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-  }
-  __device__ static f32x16 mma(T a, T b, f32x16 c) {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
-  }
-};
-
 // BAND: tile rows per band of the tile order (tile_of).
-template <int DT, uint32_t BAND>
-__global__ void __launch_bounds__(512, 1) gemm256d_kernel(const uint8_t* __restrict__ A,
+template <uint32_t BAND>
+__global__ void __launch_bounds__(512, 1) gemm256f_kernel(const uint8_t* __restrict__ A,
                                                           const uint8_t* __restrict__ B,
                                                           float* __restrict__ C, uint32_t M,
                                                           uint32_t N, uint32_t K, float scale) {
-  using G = Gemm<DT>;
   constexpr int WN = 4, JN = 2;           // 8 waves: 2 x 4, each 128 x 64
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const uint32_t nbm = (M + kBig - 1) / kBig, nbn = (N + kBig - 1) / kBig;
@@ -350,8 +499,8 @@ __global__ void __launch_bounds__(512, 1) gemm256d_kernel(const uint8_t* __restr
   tile_of<BAND>(blockIdx.x, nbm, nbn, tm, tn);
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
   const uint32_t wm = wid / WN, wn = wid % WN;
-  const uint64_t rowBytes = (uint64_t)K * G::kElem;
-  const uint32_t nstages = (uint32_t)(rowBytes / kDStage);
+  const uint32_t rowBytes = K * 4;                  // at most kBigMaxRow
+  const uint32_t nstages = (rowBytes + kDStage - 1) / kDStage;
   // Wave w fills 1 KiB blocks w and w + 8 of each operand (16 blocks of 16
   // rows); lane l lands on row 16 q + l / 4, physical chunk l % 4.
   uint32_t lrow[2], lchunk[2];
@@ -363,16 +512,17 @@ __global__ void __launch_bounds__(512, 1) gemm256d_kernel(const uint8_t* __restr
     lrow[h] = 16u * q + (lane >> 2);
     lchunk[h] = ((lane & 3u) ^ (lrow[h] >> 2)) & 3u;    // logical chunk for this slot
     const uint32_t gm = min(tm * kBig + lrow[h], M - 1), gn = min(tn * kBig + lrow[h], N - 1);
-    srcA[h] = A + (uint64_t)gm * rowBytes + lchunk[h] * 16u;
-    srcB[h] = B + (uint64_t)gn * rowBytes + lchunk[h] * 16u;
+    srcA[h] = A + (uint64_t)gm * rowBytes;
+    srcB[h] = B + (uint64_t)gn * rowBytes;
   }
   auto issue = [&](uint32_t st) {
     uint8_t* slot = smem + (st % kRingStages) * kDSlot;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const uint32_t blk = (wid + 8u * h) * 1024u;
-      __builtin_amdgcn_global_load_lds(srcA[h] + (uint64_t)st * kDStage, slot + blk, 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(srcB[h] + (uint64_t)st * kDStage, slot + kDOperand + blk, 16, 0, 0);
+      const uint32_t k = min(st * kDStage + lchunk[h] * 16u, rowBytes - 16u);    // past a row's end: not multiplied
+      load16_lds(srcA[h] + k, slot + blk);
+      load16_lds(srcB[h] + k, slot + kDOperand + blk);
     }
   };
   f32x16 acc[4][JN];
@@ -382,122 +532,74 @@ __global__ void __launch_bounds__(512, 1) gemm256d_kernel(const uint8_t* __restr
     for (int j = 0; j < JN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-  const uint32_t frow = lane & 31u, fk = (lane >> 5) * G::kFragBytes;
-  constexpr int NS = kDStage / (2 * G::kFragBytes);   // MFMA k-steps per stage
-  using F = Frag<DT>;
-  // Wait until this wave's loads of stage t are done (at most `ahead`
-  // later stages of 4 instructions each may be pending), then a bare
-  // barrier: every wave's part of stage t is in LDS.  A fence would also
-  // wait for the later stages' loads.
-  auto wait_stage = [&](uint32_t t, uint32_t ahead) {
-    const uint32_t after = min(nstages - 1, t + ahead) - t;
-    if (after >= 3) __builtin_amdgcn_s_waitcnt(0x0F7C);        // vmcnt(12)
-    else if (after == 2) __builtin_amdgcn_s_waitcnt(0x0F78);   // vmcnt(8)
-    else if (after == 1) __builtin_amdgcn_s_waitcnt(0x0F74);   // vmcnt(4)
-    else __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0)
+  const uint32_t frow = lane & 31u, fk = (lane >> 5) * 4u;
+  constexpr int NS = kDStage / 8;         // k-steps per stage
+  // Wait until this wave's loads of stage t are done (at most one later stage
+  // of 4 instructions may be pending), then a bare barrier: a fence would also
+  // wait for the later stage's loads.
+  auto wait_stage = [&](uint32_t t) {
+    if (t + 1 < nstages) __builtin_amdgcn_s_waitcnt(wait_vm(4));
+    else __builtin_amdgcn_s_waitcnt(wait_vm(0));
     __builtin_amdgcn_s_barrier();
   };
-  if constexpr (NS % 2 == 0) {
-    // Two fragment buffers of one k-step each: k-step g + 1 is read from LDS
-    // while the MFMAs of k-step g run, across stage boundaries too.  The
-    // reads of a stage's last k-step are waited for after the next stage's
-    // barrier, so that barrier frees the slot of the stage before: stage
-    // t + P is issued at the barrier of stage t into the slot of t - 2.
-    constexpr uint32_t P = kRingStages - 2;
-    for (uint32_t st = 0; st < P && st < nstages; ++st) issue(st);
-    typename F::T fa[2][4], fb[2][JN];
-    auto read_ks = [&](uint32_t t, int s, auto buf) {
-      constexpr int b = decltype(buf)::value;
-      const uint8_t* slot = smem + (t % kRingStages) * kDSlot;
-      const uint32_t kb = fk + s * 2 * G::kFragBytes;
+  for (uint32_t st = 0; st < 2 && st < nstages; ++st) issue(st);
+  float fa[2][4], fb[2][JN];
+  auto read_ks = [&](uint32_t t, int s, auto buf) {
+    constexpr int b = decltype(buf)::value;
+    const uint8_t* slot = smem + (t % kRingStages) * kDSlot;
+    const uint32_t kb = fk + s * 8;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) fa[b][i] = F::ld(slot, wm * 128 + i * 32 + frow, kb);
+    for (int i = 0; i < 4; ++i) fa[b][i] = ring_ld(slot, wm * 128 + i * 32 + frow, kb);
 #pragma unroll
-      for (int j = 0; j < JN; ++j) fb[b][j] = F::ld(slot + kDOperand, wn * 64 + j * 32 + frow, kb);
-    };
-    // MFMAs of one k-step: the first (first = true), the others (rest = true)
-    auto mma_part = [&](auto buf, bool first, bool rest) {
-      constexpr int b = decltype(buf)::value;
+    for (int j = 0; j < JN; ++j) fb[b][j] = ring_ld(slot + kDOperand, wn * 64 + j * 32 + frow, kb);
+  };
+  // MFMAs of one k-step: the first, or the others
+  auto mma_part = [&](auto buf, bool first) {
+    constexpr int b = decltype(buf)::value;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < JN; ++j)
-          if ((i == 0 && j == 0) ? first : rest) acc[i][j] = F::mma(fa[b][i], fb[b][j], acc[i][j]);
-    };
-    // FP32 (eight k-steps per stage): each k-step's block is its first MFMA,
-    // then the next k-step's reads, then its other MFMAs, fenced in that
-    // order, so that the reads have seven MFMAs to land; left to itself the
-    // compiler issues them after the block and waits for them at once.
-    // Measured 4 % faster for FP32, 1-2 % slower for BF16, which keeps the
-    // compiler's order.  Results are bit-identical either way.
-    constexpr bool kPinReads = DT == CI_DT_F32;
-    auto fence = [] {
-      if constexpr (kPinReads) __builtin_amdgcn_sched_barrier(0);
-    };
-    using B0 = std::integral_constant<int, 0>;
-    using B1 = std::integral_constant<int, 1>;
-    // stage t, its first k-step already in buffer 0; with `more`, the last
-    // k-step's MFMAs overlap the next stage's barrier and first reads
-    auto stage_body = [&](uint32_t t, bool more) {
+      for (int j = 0; j < JN; ++j)
+        if ((i == 0 && j == 0) == first)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[b][i], fb[b][j], acc[i][j], 0, 0, 0);
+  };
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+  using B0 = std::integral_constant<int, 0>;
+  using B1 = std::integral_constant<int, 1>;
+  // stage t, its first k-step already in buffer 0; with `more`, the last
+  // k-step's MFMAs overlap the next stage's barrier and first reads
+  auto stage_body = [&](uint32_t t, bool more) {
 #pragma unroll
-      for (int s = 0; s < NS; s += 2) {
-        if constexpr (kPinReads) {
-          mma_part(B0{}, true, false);
-          fence();
-        }
-        read_ks(t, s + 1, B1{});
-        fence();
-        mma_part(B0{}, !kPinReads, true);
-        fence();
-        if constexpr (kPinReads) {
-          mma_part(B1{}, true, false);
-          fence();
-        }
-        if (s + 2 < NS) {
-          read_ks(t, s + 2, B0{});
-        } else if (more) {
-          wait_stage(t + 1, P - 1);
-          if (t + 1 + P < nstages) issue(t + 1 + P);
-          read_ks(t + 1, 0, B0{});
-        }
-        fence();
-        mma_part(B1{}, !kPinReads, true);
-        fence();
+    for (int s = 0; s < NS; s += 2) {
+      if (!more && t * kDStage + s * 8 >= rowBytes) break;     // a short last stage: whole chunks, two k-steps each
+      mma_part(B0{}, true);
+      fence();
+      read_ks(t, s + 1, B1{});
+      fence();
+      mma_part(B0{}, false);
+      fence();
+      mma_part(B1{}, true);
+      fence();
+      if (s + 2 < NS) {
+        read_ks(t, s + 2, B0{});
+      } else if (more) {
+        wait_stage(t + 1);
+        if (t + 3 < nstages) issue(t + 3);
+        read_ks(t + 1, 0, B0{});
       }
-    };
-    wait_stage(0, P - 1);
-    if (P < nstages) issue(P);
-    read_ks(0, 0, B0{});
-    // no branch around the reads in the steady state, so that each MFMA
-    // block waits only for its own buffer's reads
-    uint32_t st = 0;
-    for (; st + 1 < nstages; ++st) stage_body(st, true);
-    stage_body(st, false);
-  } else {
-    // One k-step per stage (FP8): a single buffer, read then multiplied;
-    // the barrier of stage st frees the slot of st - 1.
-    for (uint32_t st = 0; st < kRingStages - 1 && st < nstages; ++st) issue(st);
-    for (uint32_t st = 0; st < nstages; ++st) {
-      wait_stage(st, kRingStages - 2);
-      if (st + kRingStages - 1 < nstages) issue(st + kRingStages - 1);
-      const uint8_t* slot = smem + (st % kRingStages) * kDSlot;
-      typename F::T fa[NS][4], fb[NS][JN];
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const uint32_t kb = fk + s * 2 * G::kFragBytes;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) fa[s][i] = F::ld(slot, wm * 128 + i * 32 + frow, kb);
-#pragma unroll
-        for (int j = 0; j < JN; ++j) fb[s][j] = F::ld(slot + kDOperand, wn * 64 + j * 32 + frow, kb);
-      }
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < JN; ++j) acc[i][j] = F::mma(fa[s][i], fb[s][j], acc[i][j]);
+      fence();
+      mma_part(B1{}, false);
+      fence();
     }
-  }
+  };
+  wait_stage(0);
+  if (2 < nstages) issue(2);
+  read_ks(0, 0, B0{});
+  // no branch around the reads in the steady state, so that each MFMA block
+  // waits only for its own buffer's reads
+  uint32_t st = 0;
+  for (; st + 1 < nstages; ++st) stage_body(st, true);
+  stage_body(st, false);
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -559,64 +661,101 @@ __global__ void __launch_bounds__(256) gemv_bf16_kernel(const uint16_t* __restri
 
 }  // namespace
 
+namespace {
+
+// Tile choice.  A work-group per CU at a time costs about u per tile and K,
+// and v once (its share of launch, first loads and last stores); tiles that
+// fill the last round of CUs poorly cost the whole round.  Rows that are not
+// whole 128-byte lines straddle two per stage, which costs the smaller tiles,
+// with more bytes per product, the most: a second set.  Fitted in microseconds
+// per K = 1024 to all four tilings on 81 square shapes from 512 to 8192:
+//   BF16, whole lines  64 x 64: 512^3 4.6, 1024^3 7.4, 1536^3 16; 128 x 64:
+//              2048^3 26 (64 x 64 28, 128 x 128 27); 128 x 128: 2560^3 41 (59,
+//              54; 256 x 256 59), 4352^3 188 (204); 256 x 256: 3328^3 80 (94),
+//              5120^3 248 (290), 8192^3 880 (1060);
+//   BF16, others  128 x 128: 2488^3 46 (85, 76; 256 x 256 71); 256 x 256:
+//              3080^3 89 (154, 109, 114), 8184^3 930 (2940, 1760, 1250);
+//   FP32       64 x 64: 1024^3 29 (128 x 64 48), 3072^3 534 (573, 643; 256 x
+//              256 785), 4004^3 990 with 256 x 256 (1067 with 128 x 128).
+// FP8 follows BF16 at half the time.
+struct TileCost {
+  float u, v;
+};
+constexpr uint32_t kTileM[4] = {64, 128, 128, 256}, kTileN[4] = {64, 64, 128, 256};
+constexpr uint32_t kCus = 256;
+constexpr TileCost kCost16[2][4] = {{{2.95f, 2.0f}, {4.4f, 3.6f}, {8.2f, 4.6f}, {26.2f, 1.0f}},
+                                    {{5.2f, 0.5f}, {7.1f, 4.0f}, {10.4f, 2.5f}, {29.5f, 0.5f}}};
+constexpr TileCost kCost32[2][4] = {{{18.7f, 9.0f}, {37.5f, 4.0f}, {70.0f, 8.0f}, {250.0f, 2.0f}},
+                                    {{19.4f, 8.0f}, {36.0f, 10.0f}, {66.0f, 10.0f}, {250.0f, 2.0f}}};
+constexpr uint64_t kBigMaxRow = 1u << 23;   // row bytes whose tile offsets fit 32 bits
+
+int tile_choice(bool f32, bool whole_lines, uint64_t m, uint64_t n, bool big_ok) {
+  const TileCost* t = (f32 ? kCost32 : kCost16)[whole_lines ? 0 : 1];
+  int best = 0;
+  float cost = 0.0f;
+  bool prev_over = false;   // the best so far is beyond what a launch can hold
+  for (int i = 0; i < (big_ok ? 4 : 3); ++i) {
+    const uint64_t tiles = ((m + kTileM[i] - 1) / kTileM[i]) * ((n + kTileN[i] - 1) / kTileN[i]);
+    const float c = (float)((tiles + kCus - 1) / kCus) * t[i].u + t[i].v;
+    const bool fits = tiles * (i < 3 ? 256 : 512) < (1ull << 32);   // a launch's work-items are 32 bits
+    if (i == 0 || (fits && c <= cost) || prev_over) {
+      best = i;
+      cost = c;
+      prev_over = !fits;
+    }
+  }
+  return best;
+}
+
+struct GemmCall {
+  const uint8_t *a, *b;
+  float* c;
+  uint32_t m, n, k;
+  float scale;
+  hipStream_t s;
+  hipEvent_t e0, e1;
+};
+
+template <typename Kernel>
+hipError_t launch_tiles(Kernel kernel, uint32_t tm, uint32_t tn, uint32_t threads, uint32_t lds, const GemmCall& g) {
+  const uint64_t nb = (uint64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn);
+  return xlaunch(kernel, dim3((uint32_t)nb), dim3(threads), lds, g.s, g.e0, g.e1, g.a, g.b, g.c, g.m, g.n, g.k, g.scale);
+}
+
+template <int DT>
+hipError_t launch_gemm_dt(const GemmCall& g) {
+  const uint64_t row = (uint64_t)g.k * Op<DT>::kElem;
+  constexpr bool f32 = DT == CI_DT_F32;
+  const bool big_ok = g.m >= kBig && g.n >= kBig && row <= kBigMaxRow;
+  switch (tile_choice(f32, row % kStage == 0, g.m, g.n, big_ok)) {
+    case 0: return launch_tiles(gemm_tile_kernel<DT, 64, 64>, 64, 64, 256, 2 * 128 * kStage, g);
+    case 1: return launch_tiles(gemm_tile_kernel<DT, 128, 64>, 128, 64, 256, 2 * 192 * kStage, g);
+    case 2: return launch_tiles(gemm_tile_kernel<DT, 128, 128>, 128, 128, 256, 2 * 256 * kStage, g);
+    default: break;
+  }
+  // Every tile at once or not: bands of 8 tile rows when it is (BF16 4096^3
+  // 114 us against 116 with FAR), of 4 with FAR otherwise (8192^3 881 against
+  // 926 us, FP8 412 against 465).
+  const bool far = (uint64_t)((g.m + kBig - 1) / kBig) * ((g.n + kBig - 1) / kBig) > kCus;
+  if constexpr (f32) {
+    const uint32_t lds = kRingStages * kDSlot;
+    return far ? launch_tiles(gemm256f_kernel<4>, kBig, kBig, 512, lds, g)
+               : launch_tiles(gemm256f_kernel<8>, kBig, kBig, 512, lds, g);
+  } else {
+    return far ? launch_tiles(gemm256d_kernel<DT, true>, kBig, kBig, 512, kBigLds, g)
+               : launch_tiles(gemm256d_kernel<DT, false>, kBig, kBig, 512, kBigLds, g);
+  }
+}
+
+}  // namespace
+
 hipError_t launch_gemm(int dtype, const void* a, const void* b, float* c, uint64_t m, uint64_t n,
                        uint64_t k, float scale, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  // Large tiles once they fill the chip (>= one 256x256 tile per CU).
-  const uint64_t nbig = ((m + kBig - 1) / kBig) * ((n + kBig - 1) / kBig);
-  if (nbig >= 256 && (k * (dtype == CI_DT_F32 ? 4 : dtype == CI_DT_BF16 ? 2 : 1)) % kDStage == 0) {
-    const uint32_t shm = kRingStages * kDSlot;
-    const uint8_t* A = (const uint8_t*)a;
-    const uint8_t* B = (const uint8_t*)b;
-    // Tile order: bands of 8 tile rows when every tile runs at once (one
-    // tile per CU), of 4 otherwise -- the faster of the two in each case
-    // (BF16 4096^3: 1042-1048 against 847-989 TF; 8192^3: 1108-1130
-    // against 1074-1079 TF).
-    const bool one_wave = nbig <= 256;
-#define CI_GEMM_RING(DT)                                                                                  \
-  return one_wave ? xlaunch(gemm256d_kernel<DT, 8>, dim3((uint32_t)nbig), dim3(512), shm, s, e0, e1, A, B, c, \
-                            (uint32_t)m, (uint32_t)n, (uint32_t)k, scale)                                 \
-                  : xlaunch(gemm256d_kernel<DT, 4>, dim3((uint32_t)nbig), dim3(512), shm, s, e0, e1, A, B, c, \
-                            (uint32_t)m, (uint32_t)n, (uint32_t)k, scale)
-    switch (dtype) {
-      case CI_DT_F32: CI_GEMM_RING(CI_DT_F32);
-      case CI_DT_BF16: CI_GEMM_RING(CI_DT_BF16);
-      case CI_DT_FP8E4M3: CI_GEMM_RING(CI_DT_FP8E4M3);
-      default: return hipErrorInvalidValue;
-    }
-#undef CI_GEMM_RING
-  }
-  if (nbig >= 256) {
-    const uint32_t shm = 4 * kBigTileLds;
-    const uint8_t* A = (const uint8_t*)a;
-    const uint8_t* B = (const uint8_t*)b;
-    constexpr int W = kBigWaves;
-    switch (dtype) {
-      case CI_DT_F32:
-        return xlaunch(gemm256_kernel<CI_DT_F32, W>, dim3((uint32_t)nbig), dim3(64 * W), shm, s, e0, e1, A,
-                       B, c, (uint32_t)m, (uint32_t)n, (uint32_t)k, scale);
-      case CI_DT_BF16:
-        return xlaunch(gemm256_kernel<CI_DT_BF16, W>, dim3((uint32_t)nbig), dim3(64 * W), shm, s, e0, e1, A,
-                       B, c, (uint32_t)m, (uint32_t)n, (uint32_t)k, scale);
-      case CI_DT_FP8E4M3:
-        return xlaunch(gemm256_kernel<CI_DT_FP8E4M3, W>, dim3((uint32_t)nbig), dim3(64 * W), shm, s, e0, e1,
-                       A, B, c, (uint32_t)m, (uint32_t)n, (uint32_t)k, scale);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  const uint64_t nb = ((m + kBM - 1) / kBM) * ((n + kBN - 1) / kBN);
-  const uint32_t shm = 4 * kTileLds;
-  const uint8_t* A = (const uint8_t*)a;
-  const uint8_t* B = (const uint8_t*)b;
+  const GemmCall g{(const uint8_t*)a, (const uint8_t*)b, c, (uint32_t)m, (uint32_t)n, (uint32_t)k, scale, s, e0, e1};
   switch (dtype) {
-    case CI_DT_F32:
-      return xlaunch(gemm_kernel<CI_DT_F32>, dim3((uint32_t)nb), dim3(256), shm, s, e0, e1, A, B, c,
-                     (uint32_t)m, (uint32_t)n, (uint32_t)k, scale);
-    case CI_DT_BF16:
-      return xlaunch(gemm_kernel<CI_DT_BF16>, dim3((uint32_t)nb), dim3(256), shm, s, e0, e1, A, B, c,
-                     (uint32_t)m, (uint32_t)n, (uint32_t)k, scale);
-    case CI_DT_FP8E4M3:
-      return xlaunch(gemm_kernel<CI_DT_FP8E4M3>, dim3((uint32_t)nb), dim3(256), shm, s, e0, e1, A, B,
-                     c, (uint32_t)m, (uint32_t)n, (uint32_t)k, scale);
+    case CI_DT_F32: return launch_gemm_dt<CI_DT_F32>(g);
+    case CI_DT_BF16: return launch_gemm_dt<CI_DT_BF16>(g);
+    case CI_DT_FP8E4M3: return launch_gemm_dt<CI_DT_FP8E4M3>(g);
     default: return hipErrorInvalidValue;
   }
 }

@@ -75,3 +75,59 @@ def test_quantize_nan_and_inf_lanes(ctx, dev):
     ok = np.ones(64, bool)
     ok[5:7] = False
     assert np.all(np.abs(t[got[ok]] - h[ok]) <= 2.0 ** -4 * np.abs(h[ok]) + 2.0 ** -10)
+
+
+# One shape (or more) for every tiling: 64 x 64, 128 x 64, 128 x 128 and 256 x
+# 256 in one round of CUs and in several, with ragged edges; K from a single
+# 16-byte chunk through every remainder of a 128-byte stage to several stages.
+GEMM_EDGES = ([(m, n, kb) for m, n in ((1, 1), (70, 65), (513, 300)) for kb in (16, 48, 64, 80, 112, 128, 144, 400)] +
+              [(2000, 2047, kb) for kb in (32, 176, 384)] + [(2500, 2561, kb) for kb in (16, 96, 320)] +
+              [(4001, 3900, kb) for kb in (64, 128, 192, 576, 1088)] +
+              [(5001, 5100, kb) for kb in (64, 192, 320, 832)] + [(256, 66000, 192), (4001, 3900, 272)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("m,n,kb", GEMM_EDGES)
+def test_gemm_tilings(ctx, dev, dtype, m, n, kb):
+    """Every entry of small products and 4096 fixed-seed entries (with the
+    last row and column) of large ones, within the accumulation bound of the
+    input type; nothing outside the output is written."""
+    import torch
+    elem = {"f32": 4, "bf16": 2, "fp8": 1}[dtype]
+    k = kb // elem
+    a = synth.normal_f32(5000 + m + kb, m * k).reshape(m, k)
+    b = synth.normal_f32(6000 + n + kb, n * k).reshape(n, k)
+    if dtype == "f32":
+        qa, qb, fa, fb, s = a, b, a.astype(np.float64), b.astype(np.float64), 1.0
+    elif dtype == "bf16":
+        qa, qb = (oracle.f32_to_bf16(x).view(np.int16) for x in (a, b))
+        fa, fb, s = oracle.bf16_to_f64(qa.view(np.uint16)), oracle.bf16_to_f64(qb.view(np.uint16)), 1.0
+    else:
+        (qa, sa), (qb, sb) = oracle.quantize_fp8(a), oracle.quantize_fp8(b)
+        fa, fb, s = oracle.e4m3_to_f64(qa), oracle.e4m3_to_f64(qb), float(sa) * float(sb)
+    fa, fb = fa.reshape(m, k), fb.reshape(n, k)
+    qa, qb = qa.reshape(m, k), qb.reshape(n, k)
+    guard = 64
+    buf = torch.full((m * n + 2 * guard,), float("nan"), dtype=torch.float32, device=dev)
+    out = buf[guard:guard + m * n]
+    ctx.victim_run(ctx.gemm_desc(torch.from_numpy(np.ascontiguousarray(qa)).to(dev),
+                                 torch.from_numpy(np.ascontiguousarray(qb)).to(dev), out, dtype, m, n, k,
+                                 s if dtype == "fp8" else 1.0, 1.0))
+    assert torch.isnan(buf[:guard]).all() and torch.isnan(buf[-guard:]).all()
+    assert not torch.isnan(out).any()
+    got = out.view(m, n)
+    if m * n <= 1 << 18:
+        rows, cols = np.repeat(np.arange(m), n), np.tile(np.arange(n), m)
+    else:
+        idx = synth.words(7000 + kb, 4096)
+        rows, cols = (idx % np.uint64(m)).astype(np.int64), ((idx >> np.uint64(32)) % np.uint64(n)).astype(np.int64)
+        rows[:64], cols[64:128] = m - 1, n - 1
+    want = s * np.einsum("ij,ij->i", fa[rows], fb[cols])
+    if dtype == "fp8":
+        bound = np.concatenate([oracle.mfma_fp8_error_bound(qa[rows[i:i + 4096]], qb[cols[i:i + 4096]], s)
+                                for i in range(0, len(rows), 4096)])
+    else:
+        absw = np.einsum("ij,ij->i", np.abs(fa[rows]), np.abs(fb[cols]))
+        bound = oracle.accumulation_bound(k + 1, absw, 2.0 ** -23)
+    g = got[torch.from_numpy(rows).to(dev), torch.from_numpy(cols).to(dev)].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(g - want) <= bound + 1e-300)
