@@ -10,6 +10,8 @@
 // write-only forms move the same arrays in other read/write proportions.
 // The cache forms re-read a region sized to one level of the CDNA4
 // hierarchy.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace ci {
@@ -21,10 +23,6 @@ __device__ __forceinline__ float triad1(float b, float c) {
 #pragma clang fp contract(off)
   const float t = 3.0f * c;
   return b + t;
-}
-
-__device__ __forceinline__ float4 triad4(float4 b, float4 c) {
-  return make_float4(triad1(b.x, c.x), triad1(b.y, c.y), triad1(b.z, c.z), triad1(b.w, c.w));
 }
 
 typedef float vf4 __attribute__((ext_vector_type(4)));
@@ -301,18 +299,25 @@ stream_stressor(KCtrl c, const float* __restrict__ b,
   }
 }
 
-// Victim triad: one sweep of the whole array per launch (grid-stride over
-// wave-chunks of 1024 elements); `passes` sweeps are `passes` launches, so
-// that every sweep reads the whole array however many work-groups are
-// resident (a loop over sweeps inside the kernel would let resident waves
-// re-read their own chunks from the L2 while the others wait).
-// With `passes` > 1 (the in-kernel form) every wave sweeps its own chunks
-// that many times.
+// Victim triad.  A sweep is one launch (`passes` sweeps are `passes`
+// launches), so that every sweep reads the whole array however many
+// work-groups are resident: a loop over sweeps inside the kernel would let
+// resident waves re-read their own chunks from the L2 while the others wait.
+// What bounds it is memory.  A sweep takes one wave per chunk of 256 elements,
+// one 16-byte access per lane and stream: work-groups are dealt out in address
+// order as others end, so the chip works on a narrow window of each stream,
+// and every wave has its loads in flight from its start.  2^28 elements:
+// 474 us (6.8 TB/s) against 595 us for 2048 work-groups that stride over the
+// array with four accesses per lane (2^20: 7.0 and 7.3 us).
+// NTL: non-temporal loads, for operands that no cache can hold.
+// The in-kernel form is the loop over sweeps: every wave sweeps its own chunks
+// of 1024 elements (U = 4) `passes` times.
+template <int U, bool NTL>
 __global__ void __launch_bounds__(256) triad_victim(const float* __restrict__ b,
                                                     const float* __restrict__ c,
                                                     float* __restrict__ a, uint64_t n,
                                                     uint32_t passes) {
-  constexpr uint64_t kChunk = 1024;
+  constexpr uint64_t kChunk = 256ull * U;
   const uint32_t lane = threadIdx.x & 63u;
   const uint64_t gw = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x >> 6);
@@ -321,14 +326,14 @@ __global__ void __launch_bounds__(256) triad_victim(const float* __restrict__ b,
   for (uint64_t ch = gw; ch < nchunks; ch += nw) {
     const uint64_t base = ch * kChunk;
     if (base + kChunk <= n) {
-      const float4* b4 = reinterpret_cast<const float4*>(b + base);
-      const float4* c4 = reinterpret_cast<const float4*>(c + base);
-      float4* a4 = reinterpret_cast<float4*>(a + base);
-      float4 vb[4], vc[4];
+      const vf4* b4 = reinterpret_cast<const vf4*>(b + base);
+      const vf4* c4 = reinterpret_cast<const vf4*>(c + base);
+      vf4* a4 = reinterpret_cast<vf4*>(a + base);
+      vf4 vb[U], vc[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { vb[u] = b4[u * 64 + lane]; vc[u] = c4[u * 64 + lane]; }
+      for (int u = 0; u < U; ++u) { vb[u] = ld<NTL>(b4 + u * 64 + lane); vc[u] = ld<NTL>(c4 + u * 64 + lane); }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a4[u * 64 + lane] = triad4(vb[u], vc[u]);
+      for (int u = 0; u < U; ++u) a4[u * 64 + lane] = triad_v(vb[u], vc[u]);
     } else {
       for (uint64_t i = base + lane; i < n && i < base + kChunk; i += 64) a[i] = triad1(b[i], c[i]);
     }
@@ -482,13 +487,26 @@ hipError_t launch_stream_stressor(const KCtrl& c, uint32_t mix, uint32_t chunk, 
 #undef CI_STREAM_LAUNCH_F
 }
 
+// Non-temporal loads from 384 MiB of operands and result on: the Infinity
+// Cache holds 256 MiB.  A sweep and a read of its result, repeated: 2^24
+// elements 43 us cached, 49 non-temporal; 2^24.5 58 and 63; 2^25 (the line) 85
+// and 83; 2^25.5 123 and 114; 2^28 720 and 681.  Non-temporal stores too: 2^25
+// 91 us, 2^26 173 against 156.
+constexpr uint64_t kTriadStream = 1ull << 25;
+
 hipError_t launch_triad_victim(const float* b, const float* c, float* a, uint64_t n,
-                               uint32_t passes, bool in_kernel, uint32_t grid, hipStream_t s,
+                               uint32_t passes, bool in_kernel, uint32_t num_cus, hipStream_t s,
                                hipEvent_t e0, hipEvent_t e1) {
-  if (in_kernel)
-    return xlaunch(triad_victim, dim3(grid), dim3(kTriadThreads), 0, s, e0, e1, b, c, a, n, passes);
+  const dim3 threads(kTriadThreads);
+  if (in_kernel) {
+    const uint32_t grid = (uint32_t)std::min<uint64_t>((n + 4095) / 4096, (uint64_t)num_cus * 8);
+    return xlaunch(triad_victim<4, false>, dim3(grid), threads, 0, s, e0, e1, b, c, a, n, passes);
+  }
+  // work-items of a launch are 32 bits: beyond 2^32 elements waves take several chunks
+  const dim3 grid((uint32_t)std::min<uint64_t>((n + 1023) / 1024, 1u << 22));
+  const auto kernel = n < kTriadStream ? triad_victim<1, false> : triad_victim<1, true>;
   for (uint32_t p = 0; p < passes; ++p) {
-    const hipError_t e = xlaunch(triad_victim, dim3(grid), dim3(kTriadThreads), 0, s, p == 0 ? e0 : nullptr,
+    const hipError_t e = xlaunch(kernel, grid, threads, 0, s, p == 0 ? e0 : nullptr,
                                  p + 1 == passes ? e1 : nullptr, b, c, a, n, 1u);
     if (e != hipSuccess) return e;
   }

@@ -1129,11 +1129,8 @@ ci_status_t ci::launch_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_
         if (e == hipSuccess && e1) e = hipEventRecord(e1, s);
         break;
       }
-      uint64_t g = (d->n + 4095) / 4096;
-      const uint64_t cap = (uint64_t)ctx->info.num_cus * 8;
-      if (g > cap) g = cap;
       e = launch_triad_victim((const float*)d->a, (const float*)d->b, (float*)d->out, d->n, d->passes,
-                              (d->flags & CI_VICTIM_TRIAD_IN_KERNEL) != 0, (uint32_t)g, s, e0, e1);
+                              (d->flags & CI_VICTIM_TRIAD_IN_KERNEL) != 0, ctx->info.num_cus, s, e0, e1);
       break;
     }
     case CI_VICTIM_GEMM: {

@@ -131,3 +131,21 @@ def test_gemm_tilings(ctx, dev, dtype, m, n, kb):
         bound = oracle.accumulation_bound(k + 1, absw, 2.0 ** -23)
     g = got[torch.from_numpy(rows).to(dev), torch.from_numpy(cols).to(dev)].cpu().numpy().astype(np.float64)
     assert np.all(np.abs(g - want) <= bound + 1e-300)
+
+
+# Both sides of the length from which loads are non-temporal, whole chunks of
+# 256 and not, and (compared on the device) more elements than one launch has
+# work-items.
+@pytest.mark.parametrize("n", [255, 256, 257, (1 << 25) - 1, 1 << 25, (1 << 25) + 257, (1 << 32) + 333])
+def test_triad_victim_lengths(ctx, dev, n):
+    import torch
+    b = torch.empty(n, dtype=torch.float32, device=dev)
+    c, out = torch.empty_like(b), torch.full((n + 1,), -1.0, device=dev)
+    for i, t in enumerate((b, c)):
+        synth.device_fill_uniform_f32(t.data_ptr(), n, 700 + i)
+    torch.cuda.synchronize()
+    ctx.victim_triad(b, c, out[:n], passes=1)
+    assert out[n].item() == -1.0
+    for i in range(0, n, 1 << 28):
+        x, y, z = (t[i:min(n, i + (1 << 28))] for t in (b, c, out))
+        assert torch.equal(z, x + y * 3.0)     # two roundings in both
