@@ -38,7 +38,7 @@ inline hipError_t xlaunch(void (*kernel)(KArgs...), dim3 grid, dim3 block, uint3
 }
 // Each returns hipSuccess or the launch error.  `grid` work-groups.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
-hipError_t launch_stamp(uint64_t* slot, hipStream_t s);
+hipError_t launch_stamp(uint64_t* slot, hipStream_t s, hipEvent_t e1 = nullptr);
 // mix: CI_HBM_TRIAD / READ / COPY / WRITE (anything else: triad); chunk:
 // 16-byte accesses per lane and stream in one wave-chunk (1, 2 or 4)
 // strided: the read-only mix takes fixed per-wave strides instead of tickets

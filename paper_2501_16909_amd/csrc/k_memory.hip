@@ -442,8 +442,8 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
                  (uint8_t*)p + n16 * 16, ntail);
 }
 
-hipError_t launch_stamp(uint64_t* slot, hipStream_t s) {
-  return xlaunch(stamp_kernel, dim3(1), dim3(64), 0, s, nullptr, nullptr, slot);
+hipError_t launch_stamp(uint64_t* slot, hipStream_t s, hipEvent_t e1) {
+  return xlaunch(stamp_kernel, dim3(1), dim3(64), 0, s, nullptr, e1, slot);
 }
 
 hipError_t launch_stream_stressor(const KCtrl& c, uint32_t mix, uint32_t chunk, const float* b,
