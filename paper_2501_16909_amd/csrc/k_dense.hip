@@ -616,6 +616,10 @@ __global__ void __launch_bounds__(512, 1) gemm256f_kernel(const uint8_t* __restr
 // GEMV: wave w handles rows w, w + W, ...; lane l reads 16-byte chunks
 // l, l + 64, ... of the row (8 BF16 each), four chunks in flight, and keeps
 // an FP32 running sum; the 64 partial sums are combined by a fixed butterfly.
+// Memory bounds it: 8192 x 8192 25.3 us (5.3 TB/s), 16384 x 16384 86 us (6.2
+// TB/s); eight chunks in flight, two or four rows a wave and loads that run
+// ahead over rows are no faster (25-32 and 84-109 us).
+// NTL: non-temporal weight loads, for matrices that no cache can hold.
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
@@ -631,6 +635,17 @@ __device__ __forceinline__ float dot8(uint4 w, uint4 x, float acc) {
   return acc;
 }
 
+template <bool NTL>
+__device__ __forceinline__ uint4 ld_chunk(const uint4* p) {
+  if constexpr (NTL) {
+    const i32x4 v = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+  } else {
+    return *p;
+  }
+}
+
+template <bool NTL>
 __global__ void __launch_bounds__(256) gemv_bf16_kernel(const uint16_t* __restrict__ W,
                                                         const uint16_t* __restrict__ x,
                                                         float* __restrict__ y, uint64_t n,
@@ -647,13 +662,13 @@ __global__ void __launch_bounds__(256) gemv_bf16_kernel(const uint16_t* __restri
     for (; c + 192 < nch; c += 256) {
       uint4 w[4], xv[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) w[u] = w4[c + 64 * u];
+      for (int u = 0; u < 4; ++u) w[u] = ld_chunk<NTL>(w4 + c + 64 * u);
 #pragma unroll
       for (int u = 0; u < 4; ++u) xv[u] = x4[c + 64 * u];
 #pragma unroll
       for (int u = 0; u < 4; ++u) acc = dot8(w[u], xv[u], acc);
     }
-    for (; c < nch; c += 64) acc = dot8(w4[c], x4[c], acc);
+    for (; c < nch; c += 64) acc = dot8(ld_chunk<NTL>(w4 + c), x4[c], acc);
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if (lane == 0) y[r] = acc;
   }
@@ -760,12 +775,17 @@ hipError_t launch_gemm(int dtype, const void* a, const void* b, float* c, uint64
   }
 }
 
+// Non-temporal weight loads when the copies that the launches rotate over are
+// more than the 256 MiB Infinity Cache: 3 x 8192^2 25.3 us against 27.0, one
+// 16384^2 86 against 94; below it the cache serves: 3 x 5888^2 16.0 us against
+// 17.7, one 8192^2 22.7 against 23.8.
 hipError_t launch_gemv_bf16(const uint16_t* w, const uint16_t* x, float* y, uint64_t n, uint64_t k,
-                            hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+                            uint64_t copies, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   uint64_t g = (n + 3) / 4;   // one wave per row, four waves per work-group
   if (g > 8192) g = 8192;
   if (g == 0) g = 1;
-  return xlaunch(gemv_bf16_kernel, dim3((uint32_t)g), dim3(256), 0, s, e0, e1, w, x, y, n, k);
+  const bool cached = (double)copies * (double)n * (double)k * 2.0 <= 256.0 * 1048576.0;
+  return xlaunch(cached ? gemv_bf16_kernel<false> : gemv_bf16_kernel<true>, dim3((uint32_t)g), dim3(256), 0, s, e0, e1, w, x, y, n, k);
 }
 
 }  // namespace ci

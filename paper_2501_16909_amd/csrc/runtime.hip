@@ -1141,7 +1141,7 @@ ci_status_t ci::launch_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_
     case CI_VICTIM_GEMV: {
       const uint64_t copy = ctx->rot++ % d->copies;
       const uint16_t* w = (const uint16_t*)d->a + copy * d->n * d->k;
-      e = launch_gemv_bf16(w, (const uint16_t*)d->b, (float*)d->out, d->n, d->k, s, e0, e1);
+      e = launch_gemv_bf16(w, (const uint16_t*)d->b, (float*)d->out, d->n, d->k, d->copies, s, e0, e1);
       break;
     }
     default: return set_err(CI_ERR_INVALID_ARG, "victim kind %d", d->kind);

@@ -149,3 +149,19 @@ def test_triad_victim_lengths(ctx, dev, n):
     for i in range(0, n, 1 << 28):
         x, y, z = (t[i:min(n, i + (1 << 28))] for t in (b, c, out))
         assert torch.equal(z, x + y * 3.0)     # two roundings in both
+
+
+# Rows that end within a round of 256 chunks; the whole matrix is beyond the
+# length from which weights are loaded non-temporally, its pieces are not.
+@pytest.mark.parametrize("n,k", [(16391, 8200), (66000, 2056), (1 << 20, 136)])
+def test_gemv_forms_agree(ctx, dev, n, k):
+    import torch
+    w = torch.from_numpy(oracle.f32_to_bf16(synth.uniform_f32(31, 1 << 22)).view(np.int16)).to(dev)
+    w = w.repeat(-(-n * k // w.numel()))[: n * k].reshape(n, k)
+    x = torch.from_numpy(oracle.f32_to_bf16(synth.uniform_f32(32, k)).view(np.int16)).to(dev)
+    y, z = (torch.full((n,), float("nan"), device=dev) for _ in range(2))
+    ctx.victim_run(ctx.gemv_desc(w, x, y, n, k))
+    for i in range(0, n, n // 4 + 1):
+        p = w[i:min(n, i + n // 4 + 1)]
+        ctx.victim_run(ctx.gemv_desc(p, x, z[i:i + len(p)], len(p), k))
+    assert torch.equal(y, z)
