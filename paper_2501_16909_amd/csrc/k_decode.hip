@@ -431,117 +431,179 @@ __global__ void __launch_bounds__(128) rope_append_kernel(const float* __restric
 }
 
 // -------------------------------------------------------------- attention
-// grid (chunks, n_kv, batch), block group * 64 (group = n_q / n_kv <= 16):
-// wave w handles query head kvh * group + w over positions t0 .. t0 + 63
-// of key/value head kvh.  The chunk's keys and values are staged in LDS
-// with 16-byte loads (rows padded to D/2 + 4 words); lane t scores position
-// t0 + t.  Output per (batch, head, chunk): {max, exp-sum, D unnormalised
-// outputs}; an empty chunk (t0 > pos) writes {-inf, 0, 0...}.
+// grid (chunks, n_kv, batch): a work-group takes positions t0 .. t0 + 63 of one
+// key/value head and all query heads of its group (n_q / n_kv <= 16), HB of
+// them per wave.  Keys go straight to LDS, 16 bytes per lane, the 16-byte chunk
+// c of row t at chunk c ^ (t & 15); lane t scores position t0 + t.  Values go
+// straight to registers, a row's words across the lanes.  The operand that all
+// lanes share, a query element or a position's weight, is one lane of a
+// register that holds 16 of them in each row of 16 lanes.  Sums run over
+// positions and dimensions in increasing order, whatever HB.  Output per
+// (batch, head, chunk): {max, exp-sum, D unnormalised outputs}; nothing for a
+// chunk beyond its sequence's end.
+// Long contexts are bound by reading the cache, short ones by one chunk's
+// chain of load, score, weight and sum.  Eight sequences of up to 8064
+// positions: 32 query and 8 key heads of 128 30.8 us (5.4 TB/s; 42.6 with keys
+// and values staged through registers to LDS and one head per wave), 32 key
+// heads 119 us (214), 16 and 8 of 256 65 us (170); one of 128 positions 4.2 us
+// (4.7).
+constexpr uint32_t kAttnChunk = 64;
+
+__device__ __forceinline__ void attn_load_lds(const uint8_t* g, uint8_t* l) {
+  __builtin_amdgcn_global_load_lds(g, l, 16, 0, 0);
+}
+
+// o += (lane 16 (l / 16) + I of p) * v, one rounding.  p must not have been
+// written by one of the two instructions before.
+template <int I>
+__device__ __forceinline__ void fma_row_lane(float& o, float p, float v) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(o) : "v"(p), "v"(v), "n"(I));
+}
+
+// A rounded product: it must not merge into the subtraction that follows.
+__device__ __forceinline__ float scaled(float s, float scale) {
+#pragma clang fp contract(off)
+  return s * scale;
+}
+
+// Value rows in registers, W = D / 128 words per lane each; rows past the
+// chunk's end read as zero (out of the buffer's range).
 template <int D>
-__global__ void __launch_bounds__(1024) attn_partial_kernel(const float* __restrict__ q,
-                                                            const uint16_t* __restrict__ kc,
-                                                            const uint16_t* __restrict__ vc,
-                                                            Positions pos,
-                                                            float* __restrict__ part, uint32_t nq,
-                                                            uint32_t nkv, uint32_t max_ctx,
-                                                            uint32_t nchunks, float scale) {
-  constexpr uint32_t kRow4 = D / 8;            // uint4 per cached row
-  constexpr uint32_t kPitch4 = kRow4 + 1;      // padded, in uint4
-  constexpr uint32_t kPitchW = 4 * kPitch4;    // in 32-bit words
-  constexpr uint32_t kWPL = D / 128;           // value words per lane
-  __shared__ uint4 ks[64 * kPitch4];
-  __shared__ uint4 vs[64 * kPitch4];
-  __shared__ float4 qs[16 * D / 4];
-  __shared__ float ps[16 * 64];
-  const uint32_t chunk = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-  const uint32_t group = blockDim.x >> 6, lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-  const uint32_t h = kvh * group + w;
-  const int32_t T = pos.at(b) + 1;
-  const uint32_t t0 = chunk * 64u;
-  float* dst = part + (((size_t)b * nq + h) * nchunks + chunk) * (D + 2);
-  if ((int32_t)t0 >= T) {
-    if (lane == 0) {
-      dst[0] = -INFINITY;
-      dst[1] = 0.0f;
-    }
-    for (uint32_t j = lane; j < D; j += 64) dst[2 + j] = 0.0f;
-    return;
-  }
-  // the query first (D/4 <= 64 float4: one per lane), so its load overlaps
-  // the chunk's
-  const float4* qh = reinterpret_cast<const float4*>(q + ((size_t)b * nq + h) * D);
-  const float4 qv = lane < D / 4 ? qh[lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  const size_t base = (((size_t)b * nkv + kvh) * max_ctx + t0) * D;
-  const uint4* k4 = reinterpret_cast<const uint4*>(kc + base);
-  const uint4* v4 = reinterpret_cast<const uint4*>(vc + base);
-  // rounds of four 16-byte loads per tensor per thread, all in flight
-  // before any is stored
-  constexpr uint32_t kTotal = 64 * kRow4;      // uint4 per tensor per chunk
-  for (uint32_t i0 = threadIdx.x; i0 < kTotal; i0 += 4 * blockDim.x) {
-    uint4 kk[4], vv[4];
+struct ValueRows {
+  static constexpr uint32_t W = D / 128, kRows = 32 / W;
+  uint32_t v[kRows][W];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t r0, uint32_t lane) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t i = i0 + u * blockDim.x;
-      const bool ok = i < kTotal && (int32_t)(t0 + i / kRow4) < T;
-      kk[u] = ok ? k4[i] : make_uint4(0, 0, 0, 0);
-      vv[u] = ok ? v4[i] : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t i = i0 + u * blockDim.x;
-      if (i < kTotal) {
-        const uint32_t t = i / kRow4, c = i - t * kRow4;
-        ks[t * kPitch4 + c] = kk[u];
-        vs[t * kPitch4 + c] = vv[u];
+    for (uint32_t r = 0; r < kRows; ++r) {
+      const uint32_t at = (r0 + r) * (D * 2);
+      if constexpr (W == 1) {
+        v[r][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + at, 0, 0);
+      } else {
+        const auto t = __builtin_amdgcn_raw_buffer_load_b64(rs, lane * 8 + at, 0, 0);
+        v[r][0] = t[0];
+        v[r][1] = t[1];
       }
     }
   }
-  if (lane < D / 4) qs[w * (D / 4) + lane] = qv;
-  __syncthreads();
-  float s = 0.0f;
-  const uint4* kr = ks + lane * kPitch4;
-  const float4* qw = qs + w * (D / 4);
-#pragma unroll 4
-  for (uint32_t c = 0; c < kRow4; ++c) {
-    const uint4 kw = kr[c];
-    const float4 qa = qw[2 * c], qb = qw[2 * c + 1];
-    s = fmaf(qa.x, bf_lo(kw.x), s);
-    s = fmaf(qa.y, bf_hi(kw.x), s);
-    s = fmaf(qa.z, bf_lo(kw.y), s);
-    s = fmaf(qa.w, bf_hi(kw.y), s);
-    s = fmaf(qb.x, bf_lo(kw.z), s);
-    s = fmaf(qb.y, bf_hi(kw.z), s);
-    s = fmaf(qb.z, bf_lo(kw.w), s);
-    s = fmaf(qb.w, bf_hi(kw.w), s);
-  }
-  const bool valid = (int32_t)(t0 + lane) < T;
-  s = valid ? s * scale : -INFINITY;
-  const float m = wave_max_f(s);        // finite: position t0 is valid
-  const float p = valid ? expf(s - m) : 0.0f;
-  const float l = wave_sum_f(p);
-  ps[w * 64 + lane] = p;
-  __syncthreads();
-  float o[2 * kWPL];
+  template <uint32_t R0, uint32_t R, int HB>
+  __device__ __forceinline__ void add(const float (&p)[HB][4], float (&o)[HB][2 * W]) const {
+    if constexpr (R < kRows) {
 #pragma unroll
-  for (uint32_t j = 0; j < 2 * kWPL; ++j) o[j] = 0.0f;
-  const uint32_t* vw32 = reinterpret_cast<const uint32_t*>(vs);
-#pragma unroll 4
-  for (uint32_t t = 0; t < 64; ++t) {
-    const float pt = ps[w * 64 + t];
+      for (uint32_t u = 0; u < W; ++u) {
+        const float lo = bf_lo(v[R][u]), hi = bf_hi(v[R][u]);
 #pragma unroll
-    for (uint32_t u = 0; u < kWPL; ++u) {
-      const uint32_t vw = vw32[t * kPitchW + lane + 64 * u];
-      o[2 * u] = fmaf(pt, bf_lo(vw), o[2 * u]);
-      o[2 * u + 1] = fmaf(pt, bf_hi(vw), o[2 * u + 1]);
+        for (uint32_t i = 0; i < HB; ++i) {
+          fma_row_lane<(R0 + R) % 16>(o[i][2 * u], p[i][(R0 + R) / 16], lo);
+          fma_row_lane<(R0 + R) % 16>(o[i][2 * u + 1], p[i][(R0 + R) / 16], hi);
+        }
+      }
+      if constexpr (R % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      add<R0, R + 1, HB>(p, o);
     }
   }
-  if (lane == 0) {
-    dst[0] = m;
-    dst[1] = l;
-  }
-  float2* d2 = reinterpret_cast<float2*>(dst + 2);
+};
+
+// s += q . k over the 16 dimensions of two 16-byte chunks; q: lane l of each
+// register holds dimension l % 16.
+template <int J, int HB>
+__device__ __forceinline__ void score_word(uint32_t kw, const float (&q)[HB], float (&s)[HB]) {
+  const float lo = bf_lo(kw), hi = bf_hi(kw);
 #pragma unroll
-  for (uint32_t u = 0; u < kWPL; ++u) d2[lane + 64 * u] = make_float2(o[2 * u], o[2 * u + 1]);
+  for (int i = 0; i < HB; ++i) fma_row_lane<J>(s[i], q[i], lo);
+#pragma unroll
+  for (int i = 0; i < HB; ++i) fma_row_lane<J + 1>(s[i], q[i], hi);
+}
+
+template <int HB>
+__device__ __forceinline__ void score_16(const uint4& a, const uint4& b, const float (&q)[HB], float (&s)[HB]) {
+  score_word<0, HB>(a.x, q, s);
+  score_word<2, HB>(a.y, q, s);
+  score_word<4, HB>(a.z, q, s);
+  score_word<6, HB>(a.w, q, s);
+  score_word<8, HB>(b.x, q, s);
+  score_word<10, HB>(b.y, q, s);
+  score_word<12, HB>(b.z, q, s);
+  score_word<14, HB>(b.w, q, s);
+}
+
+template <int D, int HB>
+__global__ void __launch_bounds__(1024 / HB) __attribute__((amdgpu_waves_per_eu(4)))
+attn_partial_kernel(const float* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
+                    Positions pos, float* __restrict__ part, uint32_t nq, uint32_t nkv, uint32_t max_ctx,
+                    uint32_t nchunks, float scale) {
+  using Rows = ValueRows<D>;
+  constexpr uint32_t kRow4 = D / 8;                       // 16-byte chunks per cached row
+  constexpr uint32_t kPieces = kAttnChunk * kRow4 / 64;   // 1 KiB each
+  __shared__ uint4 ks[kAttnChunk * kRow4];
+  const uint32_t chunk = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+  const uint32_t group = nq / nkv, waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t T = __builtin_amdgcn_readfirstlane(pos.at(b)) + 1u, t0 = chunk * kAttnChunk;
+  if (t0 >= T) return;
+  const uint32_t n = min(kAttnChunk, T - t0);
+  const size_t base = (((size_t)b * nkv + kvh) * max_ctx + t0) * D;
+  const uint8_t* kb = reinterpret_cast<const uint8_t*>(kc + base);
+  for (uint32_t i = w; i < kPieces; i += waves) {         // rows past the end repeat the last
+    const uint32_t at = i * 64 + lane, t = at / kRow4, c = (at % kRow4) ^ (t & 15u);
+    attn_load_lds(kb + (min(t, n - 1) * kRow4 + c) * 16, reinterpret_cast<uint8_t*>(ks) + i * 1024);
+  }
+  const uint32_t h0 = w * HB;
+  float qr[D / 16][HB];
+#pragma unroll
+  for (uint32_t i = 0; i < HB; ++i) {
+    const float* qh = q + ((size_t)b * nq + kvh * group + min(h0 + i, group - 1)) * D;
+#pragma unroll
+    for (uint32_t j = 0; j < D / 16; ++j) qr[j][i] = qh[16 * j + (lane & 15u)];
+  }
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vc + base), 0, n * (D * 2), 0x00027000);
+  Rows va, vn;
+  va.load(rs, 0, lane);
+  __builtin_amdgcn_s_waitcnt(0x0F70);                     // this wave's loads are in
+  __syncthreads();
+  vn.load(rs, Rows::kRows, lane);
+  float s[HB];
+#pragma unroll
+  for (uint32_t i = 0; i < HB; ++i) s[i] = 0.0f;
+#pragma unroll
+  for (uint32_t c = 0; c < kRow4; c += 2)
+    score_16<HB>(ks[lane * kRow4 + (c ^ (lane & 15u))], ks[lane * kRow4 + ((c + 1) ^ (lane & 15u))], qr[c / 2], s);
+  const bool valid = lane < n;
+  float m[HB], l[HB], p[HB][4], o[HB][2 * Rows::W];
+#pragma unroll
+  for (uint32_t i = 0; i < HB; ++i) {
+    s[i] = valid ? scaled(s[i], scale) : -INFINITY;
+    m[i] = wave_max_f(s[i]);
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < HB; ++i) {
+    const float e = valid ? expf(s[i] - m[i]) : 0.0f;
+    l[i] = wave_sum_f(e);
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) p[i][r] = __shfl(e, 16 * r + (lane & 15u), 64);
+#pragma unroll
+    for (uint32_t j = 0; j < 2 * Rows::W; ++j) o[i][j] = 0.0f;
+  }
+  va.template add<0, 0, HB>(p, o);
+  if constexpr (D == 256) va.load(rs, 2 * Rows::kRows, lane);
+  vn.template add<Rows::kRows, 0, HB>(p, o);
+  if constexpr (D == 256) {
+    vn.load(rs, 3 * Rows::kRows, lane);
+    va.template add<2 * Rows::kRows, 0, HB>(p, o);
+    vn.template add<3 * Rows::kRows, 0, HB>(p, o);
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < HB; ++i) {
+    if (h0 + i >= group) break;
+    float* dst = part + (((size_t)b * nq + kvh * group + h0 + i) * nchunks + chunk) * (D + 2);
+    if (lane == 0) {
+      dst[0] = m[i];
+      dst[1] = l[i];
+    }
+    float2* d2 = reinterpret_cast<float2*>(dst + 2) + lane * Rows::W;
+#pragma unroll
+    for (uint32_t u = 0; u < Rows::W; ++u) d2[u] = make_float2(o[i][2 * u], o[i][2 * u + 1]);
+  }
 }
 
 // grid (n_q, batch), block 256: merge the chunks of one head.  Thread t
@@ -704,14 +766,23 @@ hipError_t launch_attn_partial(const float* q, const uint16_t* kc, const uint16_
                                const Positions& pos, float* part, uint32_t batch, uint32_t nq,
                                uint32_t nkv, uint32_t d, uint32_t max_ctx, uint32_t nchunks,
                                uint32_t used_chunks, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const dim3 grid(used_chunks, nkv, batch), block(64 * (nq / nkv));
+  const dim3 grid(used_chunks, nkv, batch);
   const float scale = (float)(1.0 / sqrt((double)d));
+  const uint32_t group = nq / nkv;
+  auto go = [&](auto kernel, uint32_t hb) {
+    return xlaunch(kernel, grid, dim3(64 * ((group + hb - 1) / hb)), 0, s, e0, e1, q, kc, vc, pos, part, nq, nkv,
+                   max_ctx, nchunks, scale);
+  };
+  // Heads per wave.  One leaves the most waves, two unpack a key or value word
+  // once for both: 32 query and 8 key heads of 128, 512 work-groups 6.0 us with
+  // one (7.1), 1008 9.5 with one (8.2), 8064 35 (30.8).  At most four waves a
+  // work-group, as each reads all values through the L1: 16 heads per key head,
+  // 20 work-groups 9.2 us with one, 8.0 with two, 6.7 with four.
+  const uint32_t hb = group > 8 ? 4 : group > 4 || (group > 1 && used_chunks * nkv * batch > 512) ? 2 : 1;
   if (d == 128)
-    return xlaunch(attn_partial_kernel<128>, grid, block, 0, s, e0, e1, q, kc, vc, pos, part, nq, nkv,
-                   max_ctx, nchunks, scale);
+    return go(hb == 1 ? attn_partial_kernel<128, 1> : hb == 2 ? attn_partial_kernel<128, 2> : attn_partial_kernel<128, 4>, hb);
   if (d == 256)
-    return xlaunch(attn_partial_kernel<256>, grid, block, 0, s, e0, e1, q, kc, vc, pos, part, nq, nkv,
-                   max_ctx, nchunks, scale);
+    return go(hb == 1 ? attn_partial_kernel<256, 1> : hb == 2 ? attn_partial_kernel<256, 2> : attn_partial_kernel<256, 4>, hb);
   return hipErrorInvalidValue;
 }
 

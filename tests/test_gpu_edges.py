@@ -165,3 +165,31 @@ def test_gemv_forms_agree(ctx, dev, n, k):
         p = w[i:min(n, i + n // 4 + 1)]
         ctx.victim_run(ctx.gemv_desc(p, x, z[i:i + len(p)], len(p), k))
     assert torch.equal(y, z)
+
+
+# One, two and four heads per wave, with heads left over; chunks of one, some
+# and all positions.  What the caches hold past a sequence's end is not used.
+@pytest.mark.parametrize("d,nq,nkv,max_ctx,pos", [
+    (128, 3, 1, 130, [0, 62, 63, 64, 127, 129]), (128, 4, 4, 65, [64, 63]), (128, 10, 2, 200, [195, 30]),
+    (128, 13, 1, 200, [199, 128]), (128, 12, 4, 2048, [2047, 1030, 64, 1984, 5, 700, 2000, 1]),
+    (256, 3, 3, 100, [0, 95]), (256, 12, 2, 130, [128, 66]), (256, 15, 1, 200, [199, 15, 16]),
+    (256, 8, 4, 2100, [2099, 1030, 64, 1983, 15, 700, 2046, 2047])])
+def test_attention_edges(ctx, dev, d, nq, nkv, max_ctx, pos):
+    import torch
+    from oracle import decode as od
+    batch = len(pos)
+    q = synth.uniform_affine_f32(51, batch * nq * d, 3.0).reshape(batch, nq, d)
+    codes = [oracle.f32_to_bf16(synth.uniform_f32(52 + i, batch * nkv * max_ctx * d)).reshape(batch, nkv, max_ctx, d)
+             for i in range(2)]
+    for c in codes:
+        for b, p in enumerate(pos):
+            c[b, :, p + 1:] = 0x7FC0
+    k, v = (torch.from_numpy(c.view(np.int16)).to(dev) for c in codes)
+    out = ctx.attention_decode(torch.from_numpy(q).to(dev), k, v, pos, nq, nkv, d, max_ctx)
+    got = oracle.bf16_to_f64(out.cpu().numpy().view(np.uint16)).reshape(batch, nq, d)
+    for b, p in enumerate(pos):
+        kv, vv = (oracle.bf16_to_f64(c[b, :, :p + 1]) for c in codes)
+        want = od.attention_decode(q[b].astype(np.float64), kv, vv)
+        # FP32: sums of 64 terms per chunk, merged over the chunks; then one rounding to BF16
+        eps = (64 + (p // 64 + 1) + 8) * 2.0 ** -23 * np.max(np.abs(vv))
+        assert np.all(got[b] >= od.q_bf16(want - eps)) and np.all(got[b] <= od.q_bf16(want + eps))
