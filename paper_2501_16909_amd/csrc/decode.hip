@@ -166,6 +166,7 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* dpos, uint32_
   const uint16_t* wts = (const uint16_t*)d->weights;
   Positions pos{};
   pos.dev = dpos;
+  const bool stream = beyond_cache(L.weight_elems * 2);
 #define STEP(kind, call)                                                                       \
   do {                                                                                         \
     hipEvent_t e0_, e1_;                                                                       \
@@ -178,6 +179,7 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* dpos, uint32_
     const float* xres = l == 0 ? d->x_in : x;
     float* xo = l + 1 == c.layers ? d->x_out : x;
     GemvArgs q{};
+    q.stream = stream;
     q.w = wl + L.w_qkv;
     q.x = xres;
     q.g = wl + L.g_attn;
@@ -199,6 +201,7 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* dpos, uint32_
                                          W.nchunks, used, xs, e0_, e1_));
     STEP(CI_DK_ATTN_COMBINE, launch_attn_combine(part, pos, attn, B, c.n_q, dh, W.nchunks, xs, e0_, e1_));
     GemvArgs o{};
+    o.stream = stream;
     o.w = wl + L.w_o;
     o.v = attn;
     o.res = xres;
@@ -208,6 +211,7 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* dpos, uint32_
     o.batch = B;
     STEP(CI_DK_OPROJ, launch_gemv_fused(o, 0, kEpiPlain, xs, e0_, e1_));
     GemvArgs g{};
+    g.stream = stream;
     g.w = wl + L.w_gu;
     g.x = x;
     g.g = wl + L.g_mlp;
@@ -218,6 +222,7 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* dpos, uint32_
     g.batch = B;
     STEP(CI_DK_GATE_UP, launch_gemv_fused(g, 1, kEpiSilu, xs, e0_, e1_));
     GemvArgs dn{};
+    dn.stream = stream;
     dn.w = wl + L.w_down;
     dn.v = h;
     dn.res = x;
@@ -229,6 +234,7 @@ ci_status_t enqueue_step(const ci_decode_desc_t* d, const int32_t* dpos, uint32_
   }
   if (c.vocab) {
     GemvArgs lm{};
+    lm.stream = stream;
     lm.w = wts + L.w_lm;
     lm.x = d->x_out;
     lm.g = wts + L.g_final;
@@ -542,6 +548,7 @@ extern "C" ci_status_t ci_gemv_bf16_rows(ci_ctx_t* ctx, const uint16_t* w, const
   a.rows = rows;
   a.k = k;
   a.batch = batch;
+  a.stream = beyond_cache((uint64_t)rows * k * 2);
   HIPCHK(launch_gemv_fused(a, 0, kEpiPlain, xs, nullptr, ctx->ev[9]));
   return exec_end(ctx);
 }
@@ -562,6 +569,7 @@ extern "C" ci_status_t ci_fused_gemv(ci_ctx_t* ctx, const ci_gemv_args_t* in, vo
   g.rows = a.rows;
   g.k = a.k;
   g.batch = a.batch;
+  g.stream = beyond_cache((uint64_t)a.rows * a.k * 2);
   if (a.epilogue == CI_GEMV_PLAIN) {
     if (!a.out) return set_err(CI_ERR_INVALID_ARG, "ci_fused_gemv: NULL out");
     g.res = a.res;

@@ -71,6 +71,13 @@ __device__ __forceinline__ float dot8(uint4 w, uint4 x, float acc) {
   return acc;
 }
 
+// 16 bytes of each lane straight to LDS, lane l's to l + 16 * lane.
+__device__ __forceinline__ void load_lds_16(const void* g, void* l) {
+  __builtin_amdgcn_global_load_lds(g, l, 16, 0, 0);
+}
+
+constexpr int kWaitLoads = 0x0F70;     // s_waitcnt vmcnt(0)
+
 // ---------------------------------------------- arithmetic shared by paths
 // Sum of squares of x[0..n) by a 256-thread work-group: thread t takes the
 // float4s t, t + 256, ..., then the waves' sums are added in a fixed order.
@@ -146,125 +153,141 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const float* __restrict__ 
 constexpr int IN_BF16 = 0, IN_NORM = 1;
 constexpr int EPI_PLAIN = 0, EPI_SILU = 1, EPI_ROPE = 2;
 
-// The rows one wave computes at a time (a "unit"): PLAIN R consecutive rows;
-// SILU / ROPE one row pair (R = 2).  For ROPE the lane that writes vector b
-// (lane b) also carries the pair's cosine and sine.
-template <int R, int EPI>
-struct Unit {
-  uint32_t row[R];
-  bool live[R];
-  uint32_t jp;             // pair index (SILU / ROPE)
-  const uint4* wr[R];
-  float cs, sn;
-};
-
-template <int NB, int R, int EPI, bool kRope = true>
-__device__ __forceinline__ void map_unit(const GemvArgs& a, uint32_t unit, uint32_t lane, Unit<R, EPI>& u) {
-  if constexpr (EPI == EPI_PLAIN) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      u.row[r] = unit * R + r;
-      u.live[r] = u.row[r] < a.rows;
-    }
+// Sums of N values over the 64 lanes, lane l getting value l / (64 / N): the
+// butterfly of wave_sum_f for each of them, except that a lane group that holds
+// several values keeps half of them at every level.
+template <int N, int OFF = 32>
+__device__ __forceinline__ float wave_sums(const float (&f)[N], uint32_t lane) {
+  if constexpr (OFF == 0) {
+    return f[0];
+  } else if constexpr (N == 1) {
+    const float g[1] = {f[0] + __shfl_xor(f[0], OFF, 64)};
+    return wave_sums<1, OFF / 2>(g, lane);
   } else {
-    const uint32_t npairs = a.rows / 2;
-    u.jp = unit;
-    const bool ok = unit < npairs;
-    if constexpr (EPI == EPI_SILU) {
-      u.row[0] = unit;
-      u.row[1] = unit + npairs;
-    } else {
-      const uint32_t half = a.d / 2, head = unit / half, i = unit - head * half;
-      u.row[0] = head * a.d + i;
-      u.row[1] = u.row[0] + half;
-    }
-    u.live[0] = u.live[1] = ok;
-  }
+    float g[N / 2];
+    const bool up = lane & OFF;
 #pragma unroll
-  for (int r = 0; r < R; ++r)
-    u.wr[r] = reinterpret_cast<const uint4*>(a.w + (size_t)(u.live[r] ? u.row[r] : 0) * a.k);
-  u.cs = 1.0f;
-  u.sn = 0.0f;
-  if constexpr (EPI == EPI_ROPE && kRope) {
-    const uint32_t half = a.d / 2, head = u.jp / half;
-    if (u.live[0] && lane < a.batch && head < a.nq + a.nkv)
-      rope_cos_sin((uint32_t)a.pos[lane], u.jp - head * half, a.d, a.base, &u.cs, &u.sn);
+    for (int i = 0; i < N / 2; ++i)
+      g[i] = (up ? f[i + N / 2] : f[i]) + __shfl_xor(up ? f[i] : f[i + N / 2], OFF, 64);
+    return wave_sums<N / 2, OFF / 2>(g, lane);
   }
 }
 
-// 16-byte chunks c = 256 j + lane + 64 v (v < 4) of round j of the unit's rows.
-template <int R, int EPI>
-__device__ __forceinline__ void load_round(const Unit<R, EPI>& u, uint32_t j, uint32_t lane, uint32_t kc,
-                                           uint4 (&wv)[R][4]) {
+// The rows one wave computes at a time (a "unit"): PLAIN R consecutive rows;
+// SILU / ROPE R / 2 row pairs.  The sums come out of wave_sums in groups of
+// lanes: this lane's is that of row `r` of the unit and vector `b`.  For ROPE it
+// carries its pair's cosine and sine.
+template <int NB, int R, int EPI>
+struct Unit {
+  static constexpr uint32_t G = 64 / (NB * R);     // lanes per sum
+  uint32_t first;          // first row (PLAIN) or pair
+  const uint4* wr[R];
+  bool live[R];
+  float cs, sn;
+  static __device__ __forceinline__ uint32_t r(uint32_t lane) { return lane / G / NB; }
+  static __device__ __forceinline__ uint32_t b(uint32_t lane) { return lane / G % NB; }
+};
+
+template <int NB, int R, int EPI, bool kRope = true>
+__device__ __forceinline__ void map_unit(const GemvArgs& a, uint32_t unit, uint32_t lane, Unit<NB, R, EPI>& u) {
+  u.first = unit * (EPI == EPI_PLAIN ? R : R / 2);
+  const uint32_t npairs = a.rows / 2, half = a.d / 2;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    uint32_t row = u.first + r;
+    u.live[r] = row < a.rows;
+    if constexpr (EPI != EPI_PLAIN) {
+      const uint32_t jp = u.first + r / 2;
+      u.live[r] = jp < npairs;
+      if constexpr (EPI == EPI_SILU) row = r & 1 ? jp + npairs : jp;
+      else row = jp / half * a.d + jp % half + (r & 1 ? half : 0);
+    }
+    u.wr[r] = reinterpret_cast<const uint4*>(a.w + (size_t)(u.live[r] ? row : 0) * a.k);
+  }
+  if constexpr (EPI == EPI_ROPE && kRope) {
+    u.cs = 1.0f;
+    u.sn = 0.0f;
+    const uint32_t jp = u.first + u.r(lane) / 2, head = jp / half;
+    if (jp < npairs && u.b(lane) < a.batch && head < a.nq + a.nkv)
+      rope_cos_sin((uint32_t)a.pos[u.b(lane)], jp - head * half, a.d, a.base, &u.cs, &u.sn);
+  }
+}
+
+template <bool NTL>
+__device__ __forceinline__ uint4 load_weights(const uint4* p) {
+  if constexpr (NTL) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(t.x, t.y, t.z, t.w);
+  } else {
+    return *p;
+  }
+}
+
+// 16-byte chunks c = 64 (V j + v) + lane (v < V) of step j of the unit's rows.
+template <bool NTL, int NB, int R, int V, int EPI>
+__device__ __forceinline__ void load_step(const Unit<NB, R, EPI>& u, uint32_t j, uint32_t lane, uint32_t kc,
+                                          uint4 (&wv)[R][V]) {
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const uint32_t c = 256u * j + lane + 64u * v;
-      wv[r][v] = (u.live[r] && c < kc) ? u.wr[r][c] : make_uint4(0, 0, 0, 0);
+    for (int v = 0; v < V; ++v) {
+      const uint32_t c = 64u * (V * j + v) + lane;
+      wv[r][v] = (u.live[r] && c < kc) ? load_weights<NTL>(u.wr[r] + c) : make_uint4(0, 0, 0, 0);
     }
 }
 
 template <int NB, int R, int EPI>
-__device__ __forceinline__ void epilogue(const GemvArgs& a, const Unit<R, EPI>& u, uint32_t lane,
-                                         float (&acc)[R][NB]) {
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[r][b] = wave_sum_f(acc[r][b]);
+__device__ __forceinline__ void epilogue(const GemvArgs& a, const Unit<NB, R, EPI>& u, uint32_t lane,
+                                         float (&acc)[R * NB]) {
+  constexpr uint32_t G = Unit<NB, R, EPI>::G;
+  const float sum = wave_sums<R * NB>(acc, lane);
+  const uint32_t r = u.r(lane), b = u.b(lane);
+  bool mine = lane % G == 0 && b < a.batch;
   if constexpr (EPI == EPI_PLAIN) {
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-        if (lane == (uint32_t)(r * NB + b) && u.live[r] && (uint32_t)b < a.batch) {
-          const size_t o = (size_t)b * a.rows + u.row[r];
-          a.out[o] = (a.res ? a.res[o] : 0.0f) + acc[r][b];
-        }
-  } else if constexpr (EPI == EPI_SILU) {
-    const uint32_t f = a.rows / 2;
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-      if (lane == (uint32_t)b && u.live[0] && (uint32_t)b < a.batch)
-        a.h[(size_t)b * f + u.jp] = f32_to_bf16_rne(silu_mul_f(acc[0][b], acc[1][b]));
+    if (mine && u.first + r < a.rows) {
+      const size_t o = (size_t)b * a.rows + u.first + r;
+      a.out[o] = (a.res ? a.res[o] : 0.0f) + sum;
+    }
   } else {
-    const uint32_t half = a.d / 2, head = u.jp / half, i = u.jp - head * half;
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-      if (lane == (uint32_t)b && u.live[0] && (uint32_t)b < a.batch) {
-        const uint32_t pp = (uint32_t)a.pos[b];
-        const float x1 = acc[0][b], x2 = acc[1][b];
-        if (head < a.nq) {
-          float y1, y2;
-          rope_apply(x1, x2, u.cs, u.sn, &y1, &y2);
-          float* dst = a.q_out + ((size_t)b * a.nq + head) * a.d;
-          dst[i] = y1;
-          dst[i + half] = y2;
-        } else if (head < a.nq + a.nkv) {
-          float y1, y2;
-          rope_apply(x1, x2, u.cs, u.sn, &y1, &y2);
-          uint16_t* dst = a.kc + (((size_t)b * a.nkv + (head - a.nq)) * a.max_ctx + pp) * a.d;
-          dst[i] = f32_to_bf16_rne(y1);
-          dst[i + half] = f32_to_bf16_rne(y2);
-        } else {
-          uint16_t* dst = a.vc + (((size_t)b * a.nkv + (head - a.nq - a.nkv)) * a.max_ctx + pp) * a.d;
-          dst[i] = f32_to_bf16_rne(x1);
-          dst[i + half] = f32_to_bf16_rne(x2);
-        }
+    const float second = __shfl(sum, lane + NB * G, 64);     // of the pair's second row
+    const uint32_t jp = u.first + r / 2;
+    mine = mine && r % 2 == 0 && jp < a.rows / 2;
+    if constexpr (EPI == EPI_SILU) {
+      if (mine) a.h[(size_t)b * (a.rows / 2) + jp] = f32_to_bf16_rne(silu_mul_f(sum, second));
+    } else if (mine) {
+      const uint32_t half = a.d / 2, head = jp / half, i = jp - head * half;
+      const uint32_t pp = (uint32_t)a.pos[b];
+      float y1 = sum, y2 = second;
+      if (head < a.nq + a.nkv) rope_apply(sum, second, u.cs, u.sn, &y1, &y2);
+      if (head < a.nq) {
+        float* dst = a.q_out + ((size_t)b * a.nq + head) * a.d;
+        dst[i] = y1;
+        dst[i + half] = y2;
+      } else {
+        const bool key = head < a.nq + a.nkv;
+        const uint32_t h = head - a.nq - (key ? 0 : a.nkv);
+        uint16_t* dst = (key ? a.kc : a.vc) + (((size_t)b * a.nkv + h) * a.max_ctx + pp) * a.d;
+        dst[i] = f32_to_bf16_rne(y1);
+        dst[i + half] = f32_to_bf16_rne(y2);
       }
+    }
   }
 #pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[r][b] = 0.0f;
+  for (int i = 0; i < R * NB; ++i) acc[i] = 0.0f;
+}
+
+__device__ __forceinline__ uint2 norm4(const float4& x, float r, const uint2& g) {
+  return make_uint2(pack2(norm_bf16(x.x, r, bf_lo(g.x)), norm_bf16(x.y, r, bf_hi(g.x))),
+                    pack2(norm_bf16(x.z, r, bf_lo(g.y)), norm_bf16(x.w, r, bf_hi(g.y))));
 }
 
 // Stage chunks c0 .. c0 + nch - 1 of the NB vectors into LDS (BF16 input,
 // or FP32 input normalised with factors s_r and gain g); zeros for b >= batch.
-template <int NB, int IN>
+template <int NB, int TH, int IN>
 __device__ __forceinline__ void stage_tile(const GemvArgs& a, uint32_t c0, uint32_t nch, uint32_t tc,
                                            const float* s_r, uint4* xs) {
-  for (uint32_t i = threadIdx.x; i < NB * nch; i += 256) {
+  for (uint32_t i = threadIdx.x; i < NB * nch; i += TH) {
     const uint32_t b = i / nch, c = i - b * nch;
     uint4 val = make_uint4(0, 0, 0, 0);
     if (b < a.batch) {
@@ -274,125 +297,210 @@ __device__ __forceinline__ void stage_tile(const GemvArgs& a, uint32_t c0, uint3
         const float4* xp = reinterpret_cast<const float4*>(a.x + (size_t)b * a.k) + 2 * (c0 + c);
         const float4 x0 = xp[0], x1 = xp[1];
         const uint4 gg = reinterpret_cast<const uint4*>(a.g)[c0 + c];
-        const float r = s_r[b];
-        val.x = pack2(norm_bf16(x0.x, r, bf_lo(gg.x)), norm_bf16(x0.y, r, bf_hi(gg.x)));
-        val.y = pack2(norm_bf16(x0.z, r, bf_lo(gg.y)), norm_bf16(x0.w, r, bf_hi(gg.y)));
-        val.z = pack2(norm_bf16(x1.x, r, bf_lo(gg.z)), norm_bf16(x1.y, r, bf_hi(gg.z)));
-        val.w = pack2(norm_bf16(x1.z, r, bf_lo(gg.w)), norm_bf16(x1.w, r, bf_hi(gg.w)));
+        const uint2 lo = norm4(x0, s_r[b], make_uint2(gg.x, gg.y)), hi = norm4(x1, s_r[b], make_uint2(gg.z, gg.w));
+        val = make_uint4(lo.x, lo.y, hi.x, hi.y);
       }
     }
     xs[b * tc + c] = val;
   }
 }
 
+// Norm factors of the vectors, each by 256 threads in block_sumsq_256's order;
+// a vector of at most 4096 elements stays in registers and goes to LDS,
+// normalised, without a second read.  False: not staged.
+constexpr uint32_t kNormHeld = 4;             // float4s per thread
+
+template <int NB, int TH>
+__device__ __forceinline__ bool norm_vectors(const GemvArgs& a, uint32_t tc, float (*s_part)[4], float* s_r, uint4* xs) {
+  constexpr uint32_t G = TH / 256, Q = (NB + G - 1) / G;
+  const uint32_t t = threadIdx.x & 255u, g0 = threadIdx.x >> 8, n4 = a.k / 4;
+  const bool held = n4 <= 256 * kNormHeld && a.k / 8 <= tc;
+  float4 x[Q][kNormHeld];
+  uint2 gg[kNormHeld];
+  if (held) {
+#pragma unroll
+    for (uint32_t u = 0; u < kNormHeld; ++u) {
+      const uint32_t i = t + 256 * u;
+      gg[u] = i < n4 ? reinterpret_cast<const uint2*>(a.g)[i] : make_uint2(0, 0);
+#pragma unroll
+      for (uint32_t p = 0; p < Q; ++p) {
+        const uint32_t b = g0 + G * p;
+        x[p][u] = i < n4 && b < a.batch ? reinterpret_cast<const float4*>(a.x + (size_t)b * a.k)[i]
+                                        : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      }
+    }
+  }
+#pragma unroll
+  for (uint32_t p = 0; p < Q; ++p) {
+    const uint32_t b = g0 + G * p;
+    float ss = 0.0f;
+    auto add = [&](const float4& v) {
+      ss = fmaf(v.x, v.x, ss);
+      ss = fmaf(v.y, v.y, ss);
+      ss = fmaf(v.z, v.z, ss);
+      ss = fmaf(v.w, v.w, ss);
+    };
+    if (held) {
+#pragma unroll
+      for (uint32_t u = 0; u < kNormHeld; ++u)
+        if (t + 256 * u < n4) add(x[p][u]);
+    } else if (b < a.batch) {
+      for (uint32_t i = t; i < n4; i += 256) add(reinterpret_cast<const float4*>(a.x + (size_t)b * a.k)[i]);
+    }
+    ss = wave_sum_f(ss);
+    if ((t & 63u) == 0 && b < NB) s_part[b][t >> 6] = ss;
+  }
+  __syncthreads();
+  if (held) {
+#pragma unroll
+    for (uint32_t p = 0; p < Q; ++p) {
+      const uint32_t b = g0 + G * p;
+      if (b < NB) {
+        const float* sp = s_part[b];
+        const float r = b < a.batch ? rms_factor((sp[0] + sp[1]) + (sp[2] + sp[3]), a.k, a.eps) : 0.0f;
+        uint2* dst = reinterpret_cast<uint2*>(xs + b * tc);
+#pragma unroll
+        for (uint32_t u = 0; u < kNormHeld; ++u)
+          if (t + 256 * u < n4) dst[t + 256 * u] = norm4(x[p][u], r, gg[u]);
+      }
+    }
+    __syncthreads();
+  } else if (threadIdx.x < NB) {
+    const float* sp = s_part[threadIdx.x];
+    s_r[threadIdx.x] =
+        threadIdx.x < a.batch ? rms_factor((sp[0] + sp[1]) + (sp[2] + sp[3]), a.k, a.eps) : 0.0f;
+  }
+  return held;
+}
+
 // out = W x (rows of BF16 weights times NB vectors), FP32 accumulation.
-// Work-group: 4 waves.  K is walked in rounds of 256 16-byte chunks (lane l
-// takes chunks l, l+64, l+128, l+192 of a round: 1 KiB contiguous per row
-// per wave); the vectors are staged in LDS in tiles of TK elements (32 KiB),
-// once per work-group, read by all four waves.  TC is a multiple of 256, so
-// a round never straddles two tiles.  Each lane's products are summed in
-// increasing chunk order, then over the 64 lanes by a butterfly: the result
-// does not depend on NB, R or the grid.
-//   One tile (k <= TK): the grid is persistent; wave gw takes units gw,
-//     gw + 4 gridDim.x, ...; the next step's weights (next round, or round 0
-//     of the next unit) are loaded before the current step's products.
-//   Several tiles: one unit per wave, tiles staged in turn.
-template <int NB, int R, int IN, int EPI>
-__global__ void __launch_bounds__(256) gemv_fused_kernel(GemvArgs a, uint32_t units) {
-  constexpr uint32_t TK = 16384 / NB;
-  constexpr uint32_t TC = TK / 8;
+// Work-group: TH / 64 waves.  K is walked in steps of 64 V 16-byte chunks (V KiB
+// contiguous per row per wave); the vectors are staged in LDS in tiles of 128
+// bytes per thread, read by all waves of the work-group.  A tile is whole steps.
+// Each lane's products are summed in increasing chunk order, then over the 64
+// lanes by a butterfly: the result does not depend on NB, R, TH or the grid.
+//   One tile (k * NB * 2 <= 128 TH): the grid is persistent; wave gw takes units
+//     gw, gw + waves, ...; the next step's weights (next step, or step 0 of the
+//     next unit) are loaded before the current step's products.
+//   Several, BF16 input: one unit per wave; half a tile is filled straight from
+//     memory while the waves read the other half.
+//   Several, normalised input: one unit per wave, tiles staged in turn.
+// NTL: non-temporal weight loads.
+// What bounds it: memory for one to four vectors, the multiply-adds and the
+// unpacking of the vectors for eight.  Times, cold weights, one vector: 28672 x
+// 4096 with norm and SiLU 39 us (6.0 TB/s), 128256 x 4096 with norm 157 (6.7),
+// 4096 x 14336 20.6, 6144 x 4096 with norm and rotary embedding 13, 4096 x 4096
+// 8.1; before (staging waited for in turn, a butterfly and a store for each row
+// and vector, cached loads, eight vectors of 4096 in two tiles) 44, 178, 25, 15.5
+// and 9.4.  Four vectors: 44, 165, 25, 18 and 10.5 (56, 202, 32, 25 and 14.6);
+// eight: 55, 215, 34, 27 and 14 (152, 599, 51, 54 and 20).
+template <int NB, int R, int TH, int IN, int EPI, bool NTL>
+__global__ void __launch_bounds__(TH) gemv_fused_kernel(GemvArgs a, uint32_t units) {
+  constexpr int V = NB * R * 4 > 32 || (EPI == EPI_ROPE && NB == 4) ? 2 : 4;   // at most 128 registers where it matters
+  constexpr uint32_t TC = TH * 8 / NB;
+  static_assert(TC % (64 * V) == 0, "a tile must be whole steps");
   __shared__ uint4 xs[NB * TC];
-  __shared__ float s_part[4];
+  __shared__ float s_part[NB][4];
   __shared__ float s_r[NB];
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t gw = blockIdx.x * 4u + (threadIdx.x >> 6);
-  const uint32_t nwaves = gridDim.x * 4u;
+  const uint32_t gw = blockIdx.x * (TH / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t nwaves = gridDim.x * (TH / 64);
   const uint32_t kc = a.k / 8;
-  const uint32_t nrounds = (kc + 255) / 256;
-  float acc[R][NB];
+  const uint32_t nsteps = (kc + 64 * V - 1) / (64 * V);
+  float acc[R * NB];
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int i = 0; i < R * NB; ++i) acc[i] = 0.0f;
+  Unit<NB, R, EPI> cur;
+  uint4 wcur[R][V], wnext[R][V];
+  map_unit(a, gw, lane, cur);
+  load_step<NTL>(cur, 0, lane, kc, wcur);
+  bool staged = false;
+  if constexpr (IN == IN_NORM) staged = norm_vectors<NB, TH>(a, TC, s_part, s_r, xs);
+  auto multiply = [&](uint32_t j, uint32_t c0, uint32_t tc) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[r][b] = 0.0f;
-  Unit<R, EPI> cur;
-  uint4 wcur[R][4], wnext[R][4];
-  map_unit<NB, R, EPI>(a, gw, lane, cur);
-  load_round(cur, 0, lane, kc, wcur);
-  if constexpr (IN == IN_NORM) {
-#pragma unroll 1
-    for (uint32_t b = 0; b < (uint32_t)NB; ++b) {
-      float tot = 0.0f;
-      if (b < a.batch) tot = block_sumsq_256(a.x + (size_t)b * a.k, a.k, s_part);
-      if (threadIdx.x == 0) s_r[b] = b < a.batch ? rms_factor(tot, a.k, a.eps) : 0.0f;
-    }
-  }
-  if (kc <= TC) {
-    __syncthreads();
-    stage_tile<NB, IN>(a, 0, kc, TC, s_r, xs);
-    __syncthreads();
-    uint32_t unit = gw, j = 0;
-    while (unit < units) {
-      const bool wrap = j + 1 == nrounds;
-      const uint32_t nunit = wrap ? unit + nwaves : unit;
-      if (nunit < units) {
-        if (wrap) {
-          Unit<R, EPI> t;      // weights only: the rotary factors come with the unit itself
-          map_unit<NB, R, EPI, false>(a, nunit, lane, t);
-          load_round(t, 0, lane, kc, wnext);
-        } else {
-          load_round(cur, j + 1, lane, kc, wnext);
-        }
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const uint32_t c = 256u * j + lane + 64u * v;
-        if (c >= kc) break;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const uint4 xv = xs[b * TC + c];
-#pragma unroll
-          for (int r = 0; r < R; ++r) acc[r][b] = dot8(wcur[r][v], xv, acc[r][b]);
-        }
-      }
-      if (wrap) {
-        epilogue<NB, R, EPI>(a, cur, lane, acc);
-        map_unit<NB, R, EPI>(a, nunit, lane, cur);
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) wcur[r][v] = wnext[r][v];
-      unit = nunit;
-      j = wrap ? 0 : j + 1;
-    }
-    return;
-  }
-  for (uint32_t j = 0; j < nrounds; ++j) {
-    const uint32_t cr = 256u * j;          // first chunk of the round
-    const uint32_t c0 = cr - cr % TC;      // first chunk of its tile
-    if (cr == c0) {
-      __syncthreads();
-      stage_tile<NB, IN>(a, c0, min(TC, kc - c0), TC, s_r, xs);
-      __syncthreads();
-    }
-    if (j + 1 < nrounds) load_round(cur, j + 1, lane, kc, wnext);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const uint32_t c = cr + lane + 64u * v;
+    for (int v = 0; v < V; ++v) {
+      const uint32_t c = 64u * (V * j + v) + lane;
       if (c >= kc) break;
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const uint4 xv = xs[b * TC + (c - c0)];
+        const uint4 xv = xs[b * tc + (c - c0)];
 #pragma unroll
-        for (int r = 0; r < R; ++r) acc[r][b] = dot8(wcur[r][v], xv, acc[r][b]);
+        for (int r = 0; r < R; ++r) acc[r * NB + b] = dot8(wcur[r][v], xv, acc[r * NB + b]);
       }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) wcur[r][v] = wnext[r][v];
+      for (int v = 0; v < V; ++v) wcur[r][v] = wnext[r][v];
+  };
+  if (kc <= TC) {
+    if (!staged) {
+      __syncthreads();
+      stage_tile<NB, TH, IN>(a, 0, kc, TC, s_r, xs);
+      __syncthreads();
+    }
+    uint32_t unit = gw, j = 0;
+    while (unit < units) {
+      const bool wrap = j + 1 == nsteps;
+      const uint32_t nunit = wrap ? unit + nwaves : unit;
+      if (nunit < units) {
+        if (wrap) {
+          Unit<NB, R, EPI> t;      // weights only: the rotary factors come with the unit itself
+          map_unit<NB, R, EPI, false>(a, nunit, lane, t);
+          load_step<NTL>(t, 0, lane, kc, wnext);
+        } else {
+          load_step<NTL>(cur, j + 1, lane, kc, wnext);
+        }
+      }
+      multiply(j, 0, TC);
+      if (wrap) {
+        epilogue(a, cur, lane, acc);
+        map_unit(a, nunit, lane, cur);
+      }
+      unit = nunit;
+      j = wrap ? 0 : j + 1;
+    }
+    return;
   }
-  if (gw < units) epilogue<NB, R, EPI>(a, cur, lane, acc);
+  if constexpr (IN == IN_BF16) {
+    constexpr uint32_t TH2 = TC / 2;       // chunks of a half: one is filled while the other is read
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nhalf = (kc + TH2 - 1) / TH2;
+    auto fill = [&](uint32_t h) {
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t piece = w * 4 + i, b = piece / (TH2 / 64), c = piece % (TH2 / 64) * 64;
+        const uint4* src = reinterpret_cast<const uint4*>(a.v + (size_t)min(b, a.batch - 1) * a.k);
+        load_lds_16(src + min(h * TH2 + c + lane, kc - 1), xs + ((h & 1) * NB + b) * TH2 + c);
+      }
+    };
+    fill(0);
+    uint32_t j = 0;
+    for (uint32_t h = 0; h < nhalf; ++h) {
+      __builtin_amdgcn_s_waitcnt(kWaitLoads);   // this wave's part of the half is in
+      __syncthreads();
+      if (h + 1 < nhalf) fill(h + 1);
+      const uint32_t end = min(nsteps, (h + 1) * (TH2 / (64 * V)));
+      const uint32_t c0 = h * TH2 - (h & 1) * NB * TH2;    // xs index of chunk c: c - c0 (mod 2^32)
+      for (; j < end; ++j) {
+        if (j + 1 < nsteps) load_step<NTL>(cur, j + 1, lane, kc, wnext);
+        multiply(j, c0, TH2);
+      }
+    }
+    if (gw < units) epilogue(a, cur, lane, acc);
+    return;
+  }
+  for (uint32_t j = 0; j < nsteps; ++j) {
+    const uint32_t cr = 64u * V * j;       // first chunk of the step
+    const uint32_t c0 = cr - cr % TC;      // first chunk of its tile
+    if (cr == c0) {
+      __syncthreads();
+      stage_tile<NB, TH, IN>(a, c0, min(TC, kc - c0), TC, s_r, xs);
+      __syncthreads();
+    }
+    if (j + 1 < nsteps) load_step<NTL>(cur, j + 1, lane, kc, wnext);
+    multiply(j, c0, TC);
+  }
+  if (gw < units) epilogue(a, cur, lane, acc);
 }
 
 // ------------------------------------------------------------- RoPE + cache
@@ -448,10 +556,6 @@ __global__ void __launch_bounds__(128) rope_append_kernel(const float* __restric
 // heads 119 us (214), 16 and 8 of 256 65 us (170); one of 128 positions 4.2 us
 // (4.7).
 constexpr uint32_t kAttnChunk = 64;
-
-__device__ __forceinline__ void attn_load_lds(const uint8_t* g, uint8_t* l) {
-  __builtin_amdgcn_global_load_lds(g, l, 16, 0, 0);
-}
 
 // o += (lane 16 (l / 16) + I of p) * v, one rounding.  p must not have been
 // written by one of the two instructions before.
@@ -545,7 +649,7 @@ attn_partial_kernel(const float* __restrict__ q, const uint16_t* __restrict__ kc
   const uint8_t* kb = reinterpret_cast<const uint8_t*>(kc + base);
   for (uint32_t i = w; i < kPieces; i += waves) {         // rows past the end repeat the last
     const uint32_t at = i * 64 + lane, t = at / kRow4, c = (at % kRow4) ^ (t & 15u);
-    attn_load_lds(kb + (min(t, n - 1) * kRow4 + c) * 16, reinterpret_cast<uint8_t*>(ks) + i * 1024);
+    load_lds_16(kb + (min(t, n - 1) * kRow4 + c) * 16, ks + i * 64);
   }
   const uint32_t h0 = w * HB;
   float qr[D / 16][HB];
@@ -559,7 +663,7 @@ attn_partial_kernel(const float* __restrict__ q, const uint16_t* __restrict__ kc
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vc + base), 0, n * (D * 2), 0x00027000);
   Rows va, vn;
   va.load(rs, 0, lane);
-  __builtin_amdgcn_s_waitcnt(0x0F70);                     // this wave's loads are in
+  __builtin_amdgcn_s_waitcnt(kWaitLoads);                 // this wave's loads are in
   __syncthreads();
   vn.load(rs, Rows::kRows, lane);
   float s[HB];
@@ -683,49 +787,59 @@ __global__ void __launch_bounds__(256) silu_mul_kernel(const float* __restrict__
   }
 }
 
-// Work-groups of `kernel` (256 threads) that fit on the device at once:
-// the size of a persistent grid.
-uint32_t resident_wgs(const void* kernel) {
+// Work-groups of `kernel` that fit on the device at once: the size of a
+// persistent grid.
+uint32_t resident_wgs(const void* kernel, int threads) {
   int dev = 0, cus = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, 256, 0) != hipSuccess)
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess)
     return 256;
   return (uint32_t)std::max(1, cus * std::max(per, 1));
 }
 
-template <int NB, int R, int IN, int EPI>
+template <int NB, int R, int TH, int IN, int EPI, bool NTL>
 uint32_t resident_of() {
-  static const uint32_t n = resident_wgs(reinterpret_cast<const void*>(gemv_fused_kernel<NB, R, IN, EPI>));
+  static const uint32_t n = resident_wgs(reinterpret_cast<const void*>(gemv_fused_kernel<NB, R, TH, IN, EPI, NTL>), TH);
   return n;
 }
 
-template <int NB, int R, int IN, int EPI>
+template <int NB, int R, int TH, int IN, int EPI, bool NTL>
 hipError_t gemv_launch(const GemvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const uint32_t units = EPI == EPI_PLAIN ? (a.rows + R - 1) / R : a.rows / 2;
-  uint32_t grid = (units + 3) / 4;
-  const uint32_t tc = 2048 / NB;
-  if (a.k / 8 <= tc) grid = std::min(grid, resident_of<NB, R, IN, EPI>());
+  uint32_t grid = (units + TH / 64 - 1) / (TH / 64);
+  if (a.k / 8 <= TH * 8 / NB) grid = std::min(grid, resident_of<NB, R, TH, IN, EPI, NTL>());
   if (grid == 0) grid = 1;
-  return xlaunch(gemv_fused_kernel<NB, R, IN, EPI>, dim3(grid), dim3(256), 0, s, e0, e1, a, units);
+  return xlaunch(gemv_fused_kernel<NB, R, TH, IN, EPI, NTL>, dim3(grid), dim3(TH), 0, s, e0, e1, a, units);
 }
 
-template <int NB, int IN, int EPI>
+template <int NB, int IN, int EPI, bool NTL>
 hipError_t gemv_rows_r(const GemvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  // Eight waves share a staging, and twice the LDS: 2 x 28672 rows 39.9 us
+  // against 41.2 for four, 4 x 128256 165 against 179.  Four where the rotary
+  // factors' registers would leave a CU one work-group of eight (2 x 6144 rows
+  // 14.6 us against 16.7), and for one vector (1 x 28672 38.6 against 41.7).
+  constexpr int TH = NB == 1 || (NB == 2 && EPI == EPI_ROPE) ? 256 : 512;
   // plain rows: one row per wave while the resident grid still has a wave
   // for every row, two rows otherwise
   if constexpr (EPI == EPI_PLAIN) {
-    if (a.rows <= 4 * resident_of<NB, 1, IN, EPI>()) return gemv_launch<NB, 1, IN, EPI>(a, s, e0, e1);
+    if (a.rows <= TH / 64 * resident_of<NB, 1, TH, IN, EPI, NTL>())
+      return gemv_launch<NB, 1, TH, IN, EPI, NTL>(a, s, e0, e1);
   }
-  return gemv_launch<NB, 2, IN, EPI>(a, s, e0, e1);
+  return gemv_launch<NB, 2, TH, IN, EPI, NTL>(a, s, e0, e1);
+}
+
+template <int NB, int IN, int EPI>
+hipError_t gemv_stream(const GemvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  return a.stream ? gemv_rows_r<NB, IN, EPI, true>(a, s, e0, e1) : gemv_rows_r<NB, IN, EPI, false>(a, s, e0, e1);
 }
 
 template <int IN, int EPI>
 hipError_t gemv_nb(const GemvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (a.batch <= 1) return gemv_rows_r<1, IN, EPI>(a, s, e0, e1);
-  if (a.batch <= 2) return gemv_rows_r<2, IN, EPI>(a, s, e0, e1);
-  if (a.batch <= 4) return gemv_rows_r<4, IN, EPI>(a, s, e0, e1);
-  return gemv_rows_r<8, IN, EPI>(a, s, e0, e1);
+  if (a.batch <= 1) return gemv_stream<1, IN, EPI>(a, s, e0, e1);
+  if (a.batch <= 2) return gemv_stream<2, IN, EPI>(a, s, e0, e1);
+  if (a.batch <= 4) return gemv_stream<4, IN, EPI>(a, s, e0, e1);
+  return gemv_stream<8, IN, EPI>(a, s, e0, e1);
 }
 
 }  // namespace

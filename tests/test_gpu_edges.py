@@ -193,3 +193,41 @@ def test_attention_edges(ctx, dev, d, nq, nkv, max_ctx, pos):
         # FP32: sums of 64 terms per chunk, merged over the chunks; then one rounding to BF16
         eps = (64 + (p // 64 + 1) + 8) * 2.0 ** -23 * np.max(np.abs(vv))
         assert np.all(got[b] >= od.q_bf16(want - eps)) and np.all(got[b] <= od.q_bf16(want + eps))
+
+
+# One tile of the vectors, one chunk more, halves filled in turn with a short
+# last one; all vectors of a work-group present and some missing; normalised
+# vectors kept in registers (up to 4096 elements) and read twice.
+@pytest.mark.parametrize("batch", [1, 2, 3, 6, 8])
+@pytest.mark.parametrize("k", [8, 504, 4096, 4104, 8192, 8200, 16384, 16392, 20488])
+def test_gemv_rows_edges(ctx, dev, batch, k):
+    import torch
+    rows = 41
+    w = oracle.f32_to_bf16(synth.uniform_affine_f32(61, rows * k, k ** -0.5)).reshape(rows, k)
+    v = oracle.f32_to_bf16(synth.uniform_f32(62, batch * k)).reshape(batch, k)
+    tw, tv = (torch.from_numpy(a.view(np.int16)).to(dev) for a in (w, v))
+    out = ctx.gemv_bf16_rows(tw, tv)
+    fw, fv = oracle.bf16_to_f64(w), oracle.bf16_to_f64(v)
+    bound = oracle.accumulation_bound(k + 1, np.abs(fv) @ np.abs(fw).T, 2.0 ** -24)
+    assert np.all(np.abs(out.cpu().numpy() - fv @ fw.T) <= bound)
+    for b in range(batch):                 # whatever the batch, the same sums
+        assert torch.equal(out[b], ctx.gemv_bf16_rows(tw, tv[b:b + 1])[0])
+    x = torch.from_numpy(synth.uniform_affine_f32(63, batch * k, 2.0).reshape(batch, k)).to(dev)
+    g = torch.from_numpy(oracle.f32_to_bf16(synth.uniform_affine_f32(64, k, 0.25, 1.0)).view(np.int16)).to(dev)
+    fused = torch.empty_like(out)
+    ctx.fused_gemv(tw, "plain", x=x, g=g, eps=1e-5, out=fused)
+    assert torch.equal(fused, ctx.gemv_bf16_rows(tw, ctx.rmsnorm_bf16(x, g, 1e-5)))
+
+
+# Rows beyond the length from which weights are loaded non-temporally, a row
+# more than whole work-groups.
+@pytest.mark.parametrize("batch", [1, 2, 4, 8])
+@pytest.mark.parametrize("rows,k", [(33001, 4104), (8193, 16392)])
+def test_gemv_rows_forms_agree(ctx, dev, batch, rows, k):
+    import torch
+    w = torch.from_numpy(oracle.f32_to_bf16(synth.uniform_f32(31, 1 << 22)).view(np.int16)).to(dev)
+    w = w.repeat(-(-rows * k // w.numel()))[: rows * k].reshape(rows, k)
+    v = torch.from_numpy(oracle.f32_to_bf16(synth.uniform_f32(32, batch * k)).view(np.int16).reshape(batch, k)).to(dev)
+    whole = ctx.gemv_bf16_rows(w, v)
+    for i in range(0, rows, rows // 3 + 1):
+        assert torch.equal(whole[:, i:i + rows // 3 + 1], ctx.gemv_bf16_rows(w[i:i + rows // 3 + 1], v))
