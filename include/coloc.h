@@ -810,7 +810,9 @@ typedef struct ci_served {
  * arrival_s) arrive in real time; each is admitted FIFO (no bypass) when the
  * policy allows (ci_admit), its inputs are generated and its kernel launched
  * on a free slot stream, and it retires when its completion is observed.  The loop owns
- * one device arena of hbm_budget bytes for all request buffers.  out[i]
+ * one device arena of hbm_budget bytes for all request buffers; the context
+ * keeps it for the next run when it is at most a sixteenth of the device's
+ * memory and half of that is free, and ci_shutdown frees it.  out[i]
  * receives request i's record.  Synchronous; returns when all are done. */
 ci_status_t serve_run(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci_policy_t* p,
                       ci_served_t* out);

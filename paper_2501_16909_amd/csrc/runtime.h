@@ -4,6 +4,7 @@
 #include <array>
 #include <atomic>
 #include <map>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -50,6 +51,10 @@ struct ci_ctx {
   int32_t* dec_pos_dev = nullptr;
   std::vector<hipEvent_t> dec_ev;
   std::map<std::string, hipGraphExec_t> dec_graphs;   // captured decode steps
+  // serve_run's arena between two runs (serve.hip)
+  std::mutex arena_mu;
+  uint8_t* arena = nullptr;
+  uint64_t arena_bytes = 0;
 };
 
 struct ci_stressor {

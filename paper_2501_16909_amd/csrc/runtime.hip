@@ -282,6 +282,7 @@ extern "C" ci_status_t ci_shutdown(ci_ctx_t* ctx) {
   for (auto& ev : ctx->dec_ev)
     if (ev) (void)hipEventDestroy(ev);
   if (ctx->dec_pos_dev) (void)hipFree(ctx->dec_pos_dev);
+  if (ctx->arena) (void)hipFree(ctx->arena);
   delete ctx;
   return CI_OK;
 }

@@ -404,6 +404,46 @@ ci_status_t check_slot_queues(ci_ctx* ctx, const Background& bg, std::vector<hip
   return CI_OK;
 }
 
+// The arena outlives a run: the driver wipes memory that is given back before
+// it hands it out again, at about 35 GB/s, so a program that serves burst after
+// burst waits 28 ms per GiB of budget for it (8 GiB, 16 requests: 241 ms a run,
+// 6 ms with the arena kept).  A run takes the context's arena for itself, so
+// runs of several threads have one each; the last to end leaves its own there
+// unless one is there already.  Kept: at most a sixteenth of the device's
+// memory, and only where half of it is free; ci_shutdown frees it.
+struct ArenaMemory {
+  ci_ctx_t* ctx;
+  uint8_t* p = nullptr;
+  uint64_t bytes = 0;
+
+  explicit ArenaMemory(ci_ctx_t* c) : ctx(c) {
+    std::lock_guard<std::mutex> lk(ctx->arena_mu);
+    std::swap(p, ctx->arena);
+    std::swap(bytes, ctx->arena_bytes);
+  }
+  ~ArenaMemory() {
+    if (p) (void)hipFree(p);
+  }
+  hipError_t reserve(uint64_t need) {
+    if (p && bytes >= need) return hipSuccess;
+    if (p) (void)hipFree(p);
+    p = nullptr;
+    const hipError_t e = hipMalloc((void**)&p, need);
+    if (e != hipSuccess) p = nullptr;
+    bytes = p ? need : 0;
+    return e;
+  }
+  // the device is done with it
+  void keep() {
+    size_t free = 0, total = 0;
+    if (!p || hipMemGetInfo(&free, &total) != hipSuccess || bytes > total / 16 || free < total / 2) return;
+    std::lock_guard<std::mutex> lk(ctx->arena_mu);
+    if (ctx->arena) return;
+    std::swap(p, ctx->arena);
+    std::swap(bytes, ctx->arena_bytes);
+  }
+};
+
 ci_status_t serve_impl(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci_policy_t* p,
                        const Background* bg, ci_served_t* out) {
   if (!ctx || !p || n < 0 || (n && (!trace || !out)))
@@ -431,8 +471,9 @@ ci_status_t serve_impl(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci
   }
   if (ctx->active) return set_err(CI_ERR_BUSY, "serve_run: a stressor is running");
   HIPCHK(hipSetDevice(ctx->device));
-  uint8_t* arena_base = nullptr;
-  HIPCHK(hipMalloc((void**)&arena_base, p->hbm_budget));
+  ArenaMemory memory(ctx);
+  HIPCHK(memory.reserve(p->hbm_budget));
+  uint8_t* const arena_base = memory.p;
   // per-slot streams, events and checksum partials
   const int S = p->slots;
   std::vector<hipStream_t> streams(S, nullptr);
@@ -555,7 +596,7 @@ ci_status_t serve_impl(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci
     if (streams[s]) (void)hipStreamDestroy(streams[s]);
   }
   if (parts) (void)hipHostFree(parts);
-  (void)hipFree(arena_base);
+  if (st == CI_OK) memory.keep();
   return st;
 }
 

@@ -231,3 +231,33 @@ def test_gemv_rows_forms_agree(ctx, dev, batch, rows, k):
     whole = ctx.gemv_bf16_rows(w, v)
     for i in range(0, rows, rows // 3 + 1):
         assert torch.equal(whole[:, i:i + rows // 3 + 1], ctx.gemv_bf16_rows(w[i:i + rows // 3 + 1], v))
+
+
+# The serving arena kept between runs: reused, replaced by a larger one, taken
+# by one of two threads; given back with the context and beyond its bound.
+def test_serve_arena(dev):
+    import threading
+    import torch
+    from paper_2501_16909_amd import coloc
+    c = coloc.Context(0)
+    reqs = [dict(kind="triad", n=(1 << 20) + 7 * i, arrival_s=0.0, seed=800 + i) for i in range(3)]
+
+    def run(budget):
+        return [r["checksum_bits"] for r in c.serve(reqs, hbm_budget=budget, slots=2)]
+
+    free0 = torch.cuda.mem_get_info()[0]
+    want = run(64 << 20)
+    total = torch.cuda.mem_get_info()[1]
+    for budget in (32 << 20, 1 << 30, 64 << 20):
+        assert run(budget) == want
+    assert free0 - torch.cuda.mem_get_info()[0] <= 2 << 30
+    got = [None, None]
+    threads = [threading.Thread(target=lambda i=i: got.__setitem__(i, run((i + 1) << 30))) for i in range(2)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert got == [want, want]
+    held = torch.cuda.mem_get_info()[0]
+    assert run(total // 16 + (1 << 30)) == want       # replaces the kept one and is not kept itself
+    assert torch.cuda.mem_get_info()[0] >= held
+    c.close()
+    assert free0 - torch.cuda.mem_get_info()[0] <= 256 << 20
