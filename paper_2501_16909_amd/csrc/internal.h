@@ -101,6 +101,7 @@ hipError_t launch_gemm(int dtype, const void* a, const void* b, float* c, uint64
 hipError_t launch_gemv_bf16(const uint16_t* w, const uint16_t* x, float* y, uint64_t n,
                             uint64_t k, uint64_t copies, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_fill_uniform(float* dst, uint64_t n, uint64_t seed, hipStream_t s);
+hipError_t launch_fill_uniform_bf16(uint16_t* dst, uint64_t n, uint64_t seed, hipStream_t s);
 // decode step
 hipError_t launch_rmsnorm_bf16(const float* x, const uint16_t* g, uint16_t* y, uint32_t rows,
                                uint32_t n, float eps, hipStream_t s, hipEvent_t e0, hipEvent_t e1);

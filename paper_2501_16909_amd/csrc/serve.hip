@@ -129,8 +129,9 @@ class Arena {
 
 uint64_t elem_bytes(int dt) { return dt == CI_DT_F32 ? 4 : dt == CI_DT_BF16 ? 2 : 1; }
 
-// Bytes a request holds while it runs: operands, output and one FP32
-// staging buffer its inputs are drawn into before conversion.
+// Bytes a request holds while it runs: operands, output and, for BF16, room for
+// the larger operand in FP32, which admission counts and nothing uses: inputs
+// are drawn in BF16.
 uint64_t footprint(const ci_request_t& q) {
   auto al = [](uint64_t b) { return (b + 255) & ~255ull; };
   switch (q.kind) {
@@ -240,15 +241,12 @@ ci_status_t start_request(ci_ctx* ctx, const ci_request_t& q, uint8_t* base, hip
       uint8_t* A = p;
       uint8_t* B = A + al(q.m * q.k * e);
       float* C = (float*)(B + al(q.n * q.k * e));
-      float* stage = (float*)((uint8_t*)C + al(q.m * q.n * 4));
       if (q.dtype == CI_DT_F32) {
         HIPCHK(launch_fill_uniform((float*)A, q.m * q.k, q.seed, s));
         HIPCHK(launch_fill_uniform((float*)B, q.n * q.k, q.seed + 1, s));
       } else if (q.dtype == CI_DT_BF16) {
-        HIPCHK(launch_fill_uniform(stage, q.m * q.k, q.seed, s));
-        HIPCHK(launch_to_bf16(stage, q.m * q.k, (uint16_t*)A, s));
-        HIPCHK(launch_fill_uniform(stage, q.n * q.k, q.seed + 1, s));
-        HIPCHK(launch_to_bf16(stage, q.n * q.k, (uint16_t*)B, s));
+        HIPCHK(launch_fill_uniform_bf16((uint16_t*)A, q.m * q.k, q.seed, s));
+        HIPCHK(launch_fill_uniform_bf16((uint16_t*)B, q.n * q.k, q.seed + 1, s));
       } else {
         return set_err(CI_ERR_UNSUPPORTED, "serve: FP8 GEMM requests are not served");
       }
@@ -261,11 +259,8 @@ ci_status_t start_request(ci_ctx* ctx, const ci_request_t& q, uint8_t* base, hip
       uint16_t* W = (uint16_t*)p;
       uint16_t* x = (uint16_t*)(p + al(q.n * q.k * 2));
       float* y = (float*)((uint8_t*)x + al(q.k * 2));
-      float* stage = (float*)((uint8_t*)y + al(q.n * 4));
-      HIPCHK(launch_fill_uniform(stage, q.n * q.k, q.seed, s));
-      HIPCHK(launch_to_bf16(stage, q.n * q.k, W, s));
-      HIPCHK(launch_fill_uniform(stage, q.k, q.seed + 1, s));
-      HIPCHK(launch_to_bf16(stage, q.k, x, s));
+      HIPCHK(launch_fill_uniform_bf16(W, q.n * q.k, q.seed, s));
+      HIPCHK(launch_fill_uniform_bf16(x, q.k, q.seed + 1, s));
       d.a = W;
       d.b = x;
       d.out = y;

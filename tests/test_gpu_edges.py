@@ -261,3 +261,14 @@ def test_serve_arena(dev):
     assert torch.cuda.mem_get_info()[0] >= held
     c.close()
     assert free0 - torch.cuda.mem_get_info()[0] <= 256 << 20
+
+
+# Inputs of served requests whose element counts are not whole groups of four.
+def test_serve_input_remainders(ctx, dev):
+    import torch
+    reqs = [dict(kind="triad", n=n, arrival_s=0.0, seed=900 + 10 * n, out_copy=torch.empty(n, device=dev))
+            for n in (1, 2, 3, 4, 5, 1023, 4098)]
+    ctx.serve(reqs, hbm_budget=1 << 20, slots=3)
+    for q in reqs:
+        b, c = synth.uniform_f32(q["seed"], q["n"]), synth.uniform_f32(q["seed"] + 1, q["n"])
+        assert np.array_equal(q["out_copy"].cpu().numpy().view(np.uint32), oracle.triad_f32(b, c).view(np.uint32))
