@@ -79,20 +79,24 @@ __device__ __forceinline__ void load_lds_16(const void* g, void* l) {
 constexpr int kWaitLoads = 0x0F70;     // s_waitcnt vmcnt(0)
 
 // ---------------------------------------------- arithmetic shared by paths
-// Sum of squares of x[0..n) by a 256-thread work-group: thread t takes the
-// float4s t, t + 256, ..., then the waves' sums are added in a fixed order.
-// Uniform control flow required (barriers).
-__device__ float block_sumsq_256(const float* __restrict__ x, uint32_t n, float* s_part) {
+__device__ __forceinline__ float sumsq_of_thread(const float* __restrict__ x, uint32_t n, uint32_t t) {
   const float4* x4 = reinterpret_cast<const float4*>(x);
   float ss = 0.0f;
-  for (uint32_t i = threadIdx.x; i < n / 4; i += 256) {
+  for (uint32_t i = t; i < n / 4; i += 256) {
     const float4 v = x4[i];
     ss = fmaf(v.x, v.x, ss);
     ss = fmaf(v.y, v.y, ss);
     ss = fmaf(v.z, v.z, ss);
     ss = fmaf(v.w, v.w, ss);
   }
-  ss = wave_sum_f(ss);
+  return ss;
+}
+
+// Sum of squares of x[0..n) by a 256-thread work-group: thread t takes the
+// float4s t, t + 256, ..., then the waves' sums are added in a fixed order.
+// Uniform control flow required (barriers).
+__device__ float block_sumsq_256(const float* __restrict__ x, uint32_t n, float* s_part) {
+  const float ss = wave_sum_f(sumsq_of_thread(x, n, threadIdx.x));
   if ((threadIdx.x & 63u) == 0) s_part[threadIdx.x >> 6] = ss;
   __syncthreads();
   const float tot = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
@@ -188,7 +192,7 @@ struct Unit {
   static __device__ __forceinline__ uint32_t b(uint32_t lane) { return lane / G % NB; }
 };
 
-template <int NB, int R, int EPI, bool kRope = true>
+template <int NB, int R, int EPI>
 __device__ __forceinline__ void map_unit(const GemvArgs& a, uint32_t unit, uint32_t lane, Unit<NB, R, EPI>& u) {
   u.first = unit * (EPI == EPI_PLAIN ? R : R / 2);
   const uint32_t npairs = a.rows / 2, half = a.d / 2;
@@ -204,11 +208,15 @@ __device__ __forceinline__ void map_unit(const GemvArgs& a, uint32_t unit, uint3
     }
     u.wr[r] = reinterpret_cast<const uint4*>(a.w + (size_t)(u.live[r] ? row : 0) * a.k);
   }
-  if constexpr (EPI == EPI_ROPE && kRope) {
+}
+
+template <int NB, int R, int EPI>
+__device__ __forceinline__ void rope_factors(const GemvArgs& a, uint32_t lane, Unit<NB, R, EPI>& u) {
+  if constexpr (EPI == EPI_ROPE) {
     u.cs = 1.0f;
     u.sn = 0.0f;
-    const uint32_t jp = u.first + u.r(lane) / 2, head = jp / half;
-    if (jp < npairs && u.b(lane) < a.batch && head < a.nq + a.nkv)
+    const uint32_t half = a.d / 2, jp = u.first + u.r(lane) / 2, head = jp / half;
+    if (jp < a.rows / 2 && u.b(lane) < a.batch && head < a.nq + a.nkv)
       rope_cos_sin((uint32_t)a.pos[u.b(lane)], jp - head * half, a.d, a.base, &u.cs, &u.sn);
   }
 }
@@ -282,96 +290,103 @@ __device__ __forceinline__ uint2 norm4(const float4& x, float r, const uint2& g)
                     pack2(norm_bf16(x.z, r, bf_lo(g.y)), norm_bf16(x.w, r, bf_hi(g.y))));
 }
 
-// Stage chunks c0 .. c0 + nch - 1 of the NB vectors into LDS (BF16 input,
-// or FP32 input normalised with factors s_r and gain g); zeros for b >= batch.
-template <int NB, int TH, int IN>
-__device__ __forceinline__ void stage_tile(const GemvArgs& a, uint32_t c0, uint32_t nch, uint32_t tc,
+// Stage chunks c0 .. c0 + nch - 1 of the NB vectors into LDS, normalised with
+// factors s_r and gain g; zeros for b >= batch.
+template <int NB, int TH>
+__device__ __forceinline__ void stage_norm(const GemvArgs& a, uint32_t c0, uint32_t nch, uint32_t tc,
                                            const float* s_r, uint4* xs) {
   for (uint32_t i = threadIdx.x; i < NB * nch; i += TH) {
     const uint32_t b = i / nch, c = i - b * nch;
     uint4 val = make_uint4(0, 0, 0, 0);
     if (b < a.batch) {
-      if constexpr (IN == IN_BF16) {
-        val = reinterpret_cast<const uint4*>(a.v + (size_t)b * a.k)[c0 + c];
-      } else {
-        const float4* xp = reinterpret_cast<const float4*>(a.x + (size_t)b * a.k) + 2 * (c0 + c);
-        const float4 x0 = xp[0], x1 = xp[1];
-        const uint4 gg = reinterpret_cast<const uint4*>(a.g)[c0 + c];
-        const uint2 lo = norm4(x0, s_r[b], make_uint2(gg.x, gg.y)), hi = norm4(x1, s_r[b], make_uint2(gg.z, gg.w));
-        val = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      }
+      const float4* xp = reinterpret_cast<const float4*>(a.x + (size_t)b * a.k) + 2 * (c0 + c);
+      const float4 x0 = xp[0], x1 = xp[1];
+      const uint4 gg = reinterpret_cast<const uint4*>(a.g)[c0 + c];
+      const uint2 lo = norm4(x0, s_r[b], make_uint2(gg.x, gg.y)), hi = norm4(x1, s_r[b], make_uint2(gg.z, gg.w));
+      val = make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
     xs[b * tc + c] = val;
   }
 }
 
-// Norm factors of the vectors, each by 256 threads in block_sumsq_256's order;
-// a vector of at most 4096 elements stays in registers and goes to LDS,
-// normalised, without a second read.  False: not staged.
-constexpr uint32_t kNormHeld = 4;             // float4s per thread
-
+// What a thread holds of the vectors between asking for them and staging them,
+// so that the first weights can be asked for in between: a wave's loads return
+// in order, and the vectors come from the L2 long before weights from memory.
+// BF16: the whole tile, where one holds the vectors.
 template <int NB, int TH>
-__device__ __forceinline__ bool norm_vectors(const GemvArgs& a, uint32_t tc, float (*s_part)[4], float* s_r, uint4* xs) {
-  constexpr uint32_t G = TH / 256, Q = (NB + G - 1) / G;
-  const uint32_t t = threadIdx.x & 255u, g0 = threadIdx.x >> 8, n4 = a.k / 4;
-  const bool held = n4 <= 256 * kNormHeld && a.k / 8 <= tc;
-  float4 x[Q][kNormHeld];
-  uint2 gg[kNormHeld];
-  if (held) {
+struct HeldBf16 {
+  static constexpr uint32_t kChunks = 8, TC = TH * kChunks / NB;
+  uint4 x[kChunks];
+  __device__ __forceinline__ void load(const GemvArgs& a, uint32_t kc) {
 #pragma unroll
-    for (uint32_t u = 0; u < kNormHeld; ++u) {
+    for (uint32_t u = 0; u < kChunks; ++u) {
+      const uint32_t i = threadIdx.x + TH * u, b = i / TC, c = i % TC;
+      x[u] = c < kc && b < a.batch ? reinterpret_cast<const uint4*>(a.v + (size_t)b * a.k)[c] : make_uint4(0, 0, 0, 0);
+    }
+  }
+  __device__ __forceinline__ void stage(uint32_t kc, uint4* xs) const {
+#pragma unroll
+    for (uint32_t u = 0; u < kChunks; ++u) {
+      const uint32_t i = threadIdx.x + TH * u;
+      if (i % TC < kc) xs[i] = x[u];
+    }
+    __syncthreads();
+  }
+};
+
+// FP32: vectors of at most 4096 elements, 256 threads to a vector; they go to
+// LDS normalised without a second read.  The norms are block_sumsq_256's.
+template <int NB, int TH>
+struct HeldNorm {
+  static constexpr uint32_t kQuads = 4, G = TH / 256, Q = (NB + G - 1) / G;   // float4s per thread, vectors per 256
+  float4 x[Q][kQuads];
+  uint2 g[kQuads];
+  static __device__ __forceinline__ bool fits(const GemvArgs& a) { return a.k <= 4 * 256 * kQuads; }
+  __device__ __forceinline__ void load(const GemvArgs& a) {
+    const uint32_t t = threadIdx.x & 255u, g0 = threadIdx.x >> 8, n4 = a.k / 4;
+#pragma unroll
+    for (uint32_t u = 0; u < kQuads; ++u) {
       const uint32_t i = t + 256 * u;
-      gg[u] = i < n4 ? reinterpret_cast<const uint2*>(a.g)[i] : make_uint2(0, 0);
 #pragma unroll
       for (uint32_t p = 0; p < Q; ++p) {
         const uint32_t b = g0 + G * p;
         x[p][u] = i < n4 && b < a.batch ? reinterpret_cast<const float4*>(a.x + (size_t)b * a.k)[i]
                                         : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       }
+      g[u] = i < n4 ? reinterpret_cast<const uint2*>(a.g)[i] : make_uint2(0, 0);
     }
   }
+  __device__ __forceinline__ void stage(const GemvArgs& a, uint32_t tc, float (*s_part)[4], uint4* xs) const {
+    const uint32_t t = threadIdx.x & 255u, g0 = threadIdx.x >> 8, n4 = a.k / 4;
 #pragma unroll
-  for (uint32_t p = 0; p < Q; ++p) {
-    const uint32_t b = g0 + G * p;
-    float ss = 0.0f;
-    auto add = [&](const float4& v) {
-      ss = fmaf(v.x, v.x, ss);
-      ss = fmaf(v.y, v.y, ss);
-      ss = fmaf(v.z, v.z, ss);
-      ss = fmaf(v.w, v.w, ss);
-    };
-    if (held) {
+    for (uint32_t p = 0; p < Q; ++p) {
+      float ss = 0.0f;
 #pragma unroll
-      for (uint32_t u = 0; u < kNormHeld; ++u)
-        if (t + 256 * u < n4) add(x[p][u]);
-    } else if (b < a.batch) {
-      for (uint32_t i = t; i < n4; i += 256) add(reinterpret_cast<const float4*>(a.x + (size_t)b * a.k)[i]);
+      for (uint32_t u = 0; u < kQuads; ++u)
+        if (t + 256 * u < n4) {
+          ss = fmaf(x[p][u].x, x[p][u].x, ss);
+          ss = fmaf(x[p][u].y, x[p][u].y, ss);
+          ss = fmaf(x[p][u].z, x[p][u].z, ss);
+          ss = fmaf(x[p][u].w, x[p][u].w, ss);
+        }
+      ss = wave_sum_f(ss);
+      if ((t & 63u) == 0 && g0 + G * p < NB) s_part[g0 + G * p][t >> 6] = ss;
     }
-    ss = wave_sum_f(ss);
-    if ((t & 63u) == 0 && b < NB) s_part[b][t >> 6] = ss;
-  }
-  __syncthreads();
-  if (held) {
+    __syncthreads();
 #pragma unroll
     for (uint32_t p = 0; p < Q; ++p) {
       const uint32_t b = g0 + G * p;
-      if (b < NB) {
-        const float* sp = s_part[b];
-        const float r = b < a.batch ? rms_factor((sp[0] + sp[1]) + (sp[2] + sp[3]), a.k, a.eps) : 0.0f;
-        uint2* dst = reinterpret_cast<uint2*>(xs + b * tc);
+      if (b >= NB) break;
+      const float* sp = s_part[b];
+      const float r = b < a.batch ? rms_factor((sp[0] + sp[1]) + (sp[2] + sp[3]), a.k, a.eps) : 0.0f;
+      uint2* dst = reinterpret_cast<uint2*>(xs + b * tc);
 #pragma unroll
-        for (uint32_t u = 0; u < kNormHeld; ++u)
-          if (t + 256 * u < n4) dst[t + 256 * u] = norm4(x[p][u], r, gg[u]);
-      }
+      for (uint32_t u = 0; u < kQuads; ++u)
+        if (t + 256 * u < n4) dst[t + 256 * u] = norm4(x[p][u], r, g[u]);
     }
     __syncthreads();
-  } else if (threadIdx.x < NB) {
-    const float* sp = s_part[threadIdx.x];
-    s_r[threadIdx.x] =
-        threadIdx.x < a.batch ? rms_factor((sp[0] + sp[1]) + (sp[2] + sp[3]), a.k, a.eps) : 0.0f;
   }
-  return held;
-}
+};
 
 // out = W x (rows of BF16 weights times NB vectors), FP32 accumulation.
 // Work-group: TH / 64 waves.  K is walked in steps of 64 V 16-byte chunks (V KiB
@@ -389,10 +404,10 @@ __device__ __forceinline__ bool norm_vectors(const GemvArgs& a, uint32_t tc, flo
 // What bounds it: memory for one to four vectors, the multiply-adds and the
 // unpacking of the vectors for eight.  Times, cold weights, one vector: 28672 x
 // 4096 with norm and SiLU 39 us (6.0 TB/s), 128256 x 4096 with norm 157 (6.7),
-// 4096 x 14336 20.6, 6144 x 4096 with norm and rotary embedding 13, 4096 x 4096
-// 8.1; before (staging waited for in turn, a butterfly and a store for each row
+// 4096 x 14336 20, 6144 x 4096 with norm and rotary embedding 12.6, 4096 x 4096
+// 7.6; before (staging waited for in turn, a butterfly and a store for each row
 // and vector, cached loads, eight vectors of 4096 in two tiles) 44, 178, 25, 15.5
-// and 9.4.  Four vectors: 44, 165, 25, 18 and 10.5 (56, 202, 32, 25 and 14.6);
+// and 9.4.  Four vectors: 44, 167, 25, 18 and 9.2 (56, 202, 32, 25 and 14.6);
 // eight: 55, 215, 34, 27 and 14 (152, 599, 51, 54 and 20).
 template <int NB, int R, int TH, int IN, int EPI, bool NTL>
 __global__ void __launch_bounds__(TH) gemv_fused_kernel(GemvArgs a, uint32_t units) {
@@ -413,9 +428,48 @@ __global__ void __launch_bounds__(TH) gemv_fused_kernel(GemvArgs a, uint32_t uni
   Unit<NB, R, EPI> cur;
   uint4 wcur[R][V], wnext[R][V];
   map_unit(a, gw, lane, cur);
-  load_step<NTL>(cur, 0, lane, kc, wcur);
-  bool staged = false;
-  if constexpr (IN == IN_NORM) staged = norm_vectors<NB, TH>(a, TC, s_part, s_r, xs);
+  const bool single = kc <= TC;
+  auto first_weights = [&] {
+    __builtin_amdgcn_sched_barrier(0);
+    load_step<NTL>(cur, 0, lane, kc, wcur);
+    rope_factors(a, lane, cur);
+  };
+  if constexpr (IN == IN_BF16) {
+    if (single) {
+      HeldBf16<NB, TH> held;
+      held.load(a, kc);
+      first_weights();
+      held.stage(kc, xs);
+    } else {
+      first_weights();
+    }
+  } else if (single && HeldNorm<NB, TH>::fits(a)) {
+    HeldNorm<NB, TH> held;
+    held.load(a);
+    first_weights();
+    held.stage(a, TC, s_part, xs);
+  } else {
+    first_weights();
+#pragma unroll 1
+    for (uint32_t b = threadIdx.x >> 8; b < NB; b += TH / 256) {
+      const uint32_t t = threadIdx.x & 255u;
+      float ss = 0.0f;
+      if (b < a.batch) ss = sumsq_of_thread(a.x + (size_t)b * a.k, a.k, t);
+      ss = wave_sum_f(ss);
+      if ((t & 63u) == 0) s_part[b][t >> 6] = ss;
+    }
+    __syncthreads();
+    if (threadIdx.x < NB) {
+      const float* sp = s_part[threadIdx.x];
+      s_r[threadIdx.x] =
+          threadIdx.x < a.batch ? rms_factor((sp[0] + sp[1]) + (sp[2] + sp[3]), a.k, a.eps) : 0.0f;
+    }
+    __syncthreads();
+    if (single) {
+      stage_norm<NB, TH>(a, 0, kc, TC, s_r, xs);
+      __syncthreads();
+    }
+  }
   auto multiply = [&](uint32_t j, uint32_t c0, uint32_t tc) {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -433,12 +487,7 @@ __global__ void __launch_bounds__(TH) gemv_fused_kernel(GemvArgs a, uint32_t uni
 #pragma unroll
       for (int v = 0; v < V; ++v) wcur[r][v] = wnext[r][v];
   };
-  if (kc <= TC) {
-    if (!staged) {
-      __syncthreads();
-      stage_tile<NB, TH, IN>(a, 0, kc, TC, s_r, xs);
-      __syncthreads();
-    }
+  if (single) {
     uint32_t unit = gw, j = 0;
     while (unit < units) {
       const bool wrap = j + 1 == nsteps;
@@ -446,7 +495,7 @@ __global__ void __launch_bounds__(TH) gemv_fused_kernel(GemvArgs a, uint32_t uni
       if (nunit < units) {
         if (wrap) {
           Unit<NB, R, EPI> t;      // weights only: the rotary factors come with the unit itself
-          map_unit<NB, R, EPI, false>(a, nunit, lane, t);
+          map_unit(a, nunit, lane, t);
           load_step<NTL>(t, 0, lane, kc, wnext);
         } else {
           load_step<NTL>(cur, j + 1, lane, kc, wnext);
@@ -456,6 +505,7 @@ __global__ void __launch_bounds__(TH) gemv_fused_kernel(GemvArgs a, uint32_t uni
       if (wrap) {
         epilogue(a, cur, lane, acc);
         map_unit(a, nunit, lane, cur);
+        if (nunit < units) rope_factors(a, lane, cur);
       }
       unit = nunit;
       j = wrap ? 0 : j + 1;
@@ -494,7 +544,7 @@ __global__ void __launch_bounds__(TH) gemv_fused_kernel(GemvArgs a, uint32_t uni
     const uint32_t c0 = cr - cr % TC;      // first chunk of its tile
     if (cr == c0) {
       __syncthreads();
-      stage_tile<NB, TH, IN>(a, c0, min(TC, kc - c0), TC, s_r, xs);
+      stage_norm<NB, TH>(a, c0, min(TC, kc - c0), TC, s_r, xs);
       __syncthreads();
     }
     if (j + 1 < nsteps) load_step<NTL>(cur, j + 1, lane, kc, wnext);
@@ -787,20 +837,24 @@ __global__ void __launch_bounds__(256) silu_mul_kernel(const float* __restrict__
   }
 }
 
-// Work-groups of `kernel` that fit on the device at once: the size of a
-// persistent grid.
-uint32_t resident_wgs(const void* kernel, int threads) {
+// Work-groups of `kernel` that fit on the device at once, at most `most` on a
+// CU: the size of a persistent grid.
+uint32_t resident_wgs(const void* kernel, int threads, int most) {
   int dev = 0, cus = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess)
     return 256;
-  return (uint32_t)std::max(1, cus * std::max(per, 1));
+  return (uint32_t)std::max(1, cus * std::min(std::max(per, 1), most));
 }
 
 template <int NB, int R, int TH, int IN, int EPI, bool NTL>
 uint32_t resident_of() {
-  static const uint32_t n = resident_wgs(reinterpret_cast<const void*>(gemv_fused_kernel<NB, R, TH, IN, EPI, NTL>), TH);
+  // two rows a wave leave enough in flight with three groups of four waves:
+  // 28672 x 4096 39.3 us with three, 41.1 with four, 41.3 with two
+  constexpr int kMost = R == 2 && TH == 256 ? 3 : 32;
+  static const uint32_t n =
+      resident_wgs(reinterpret_cast<const void*>(gemv_fused_kernel<NB, R, TH, IN, EPI, NTL>), TH, kMost);
   return n;
 }
 
