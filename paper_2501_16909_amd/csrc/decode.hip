@@ -326,11 +326,12 @@ ci_status_t run_decode(ci_ctx* ctx, const ci_decode_desc_t* d, hipStream_t calle
   if (st != CI_OK) return st;
   volatile uint64_t* hr = ctx->hres;
   hr[0] = hr[1] = 0;
-  HIPCHK(xlaunch(begin_kernel, dim3(1), dim3(64), 0, xs, nullptr, nullptr, pos, c.batch, ctx->dec_pos_dev,
+  // The step's time runs from this kernel's end; where it ends with a launch of
+  // its own, that launch records the end (a marker in the stream costs 2-3 us).
+  HIPCHK(xlaunch(begin_kernel, dim3(1), dim3(64), 0, xs, nullptr, ctx->ev[7], pos, c.batch, ctx->dec_pos_dev,
                  (uint64_t*)&hr[0]));
   std::vector<int> kinds;
   if (graph) {
-    HIPCHK(hipEventRecord(ctx->ev[7], xs));
     HIPCHK(hipGraphLaunch(graph, xs));
     HIPCHK(hipEventRecord(ctx->ev[8], xs));
   } else if (timed) {
@@ -342,12 +343,12 @@ ci_status_t run_decode(ci_ctx* ctx, const ci_decode_desc_t* d, hipStream_t calle
     });
     if (st != CI_OK) return st;
   } else {
-    HIPCHK(hipEventRecord(ctx->ev[7], xs));
-    st = enqueue_step(d, ctx->dec_pos_dev, used, xs, [](int, hipEvent_t* a, hipEvent_t* b) {
-      *a = *b = nullptr;
+    uint32_t queued = 0;
+    st = enqueue_step(d, ctx->dec_pos_dev, used, xs, [&](int, hipEvent_t* a, hipEvent_t* b) {
+      *a = nullptr;
+      *b = ++queued == nk ? ctx->ev[8] : nullptr;
     });
     if (st != CI_OK) return st;
-    HIPCHK(hipEventRecord(ctx->ev[8], xs));
   }
   const float* res = c.vocab ? d->logits : d->x_out;
   const uint64_t len = (uint64_t)c.batch * (c.vocab ? c.vocab : c.hidden);
