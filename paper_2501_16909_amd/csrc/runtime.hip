@@ -19,6 +19,8 @@
 
 using namespace ci;
 
+std::atomic<int> Counted::live{0};
+
 // ------------------------------------------------------------------ errors
 namespace {
 thread_local std::string g_err;
@@ -1166,18 +1168,20 @@ ci_status_t ci::order_after(ci_ctx* ctx, hipStream_t caller, hipStream_t xs) {
 }
 
 // Run one victim on exec stream `xs` after the caller's queued work; fills
-// out (time, stamps, checksums).  Blocks until done.
-ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs,
+// out (time, stamps, checksums).  Blocks until done.  beside: the victim has
+// co-runners, or its time is compared with such a run's.
+ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs, bool beside,
                            ci_victim_result_t* out) {
   volatile uint64_t* hr = ctx->hres;
   hr[0] = hr[1] = 0;
   ci_status_t st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
-  // The victim's time runs from the stamp's end to its own, 0.5 us less than
-  // between a start and a stop event of its launch; that start event costs the
-  // host 16 us (three small launches and their wait 18 us, with it 36).
-  HIPCHK(launch_stamp((uint64_t*)&hr[0], xs, ctx->ev[7]));
-  st = launch_victim(ctx, d, xs, nullptr, ctx->ev[8]);
+  // A start event on the victim's launch costs the host 16 us (three small
+  // launches and their wait 36 us, without it 18).  Alone, the time can as well
+  // run from the stamp's end, 0.5 us less; beside other work the interval would
+  // include the dispatch behind it.
+  HIPCHK(launch_stamp((uint64_t*)&hr[0], xs, beside ? nullptr : ctx->ev[7]));
+  st = launch_victim(ctx, d, xs, beside ? ctx->ev[7] : nullptr, ctx->ev[8]);
   if (st != CI_OK) return st;
   const uint64_t len = victim_out_len(d);
   HIPCHK(launch_checksum_f32((const float*)d->out, len, ctx->sum_parts, (uint64_t*)&hr[1], xs, ctx->ev[9]));
@@ -1197,7 +1201,7 @@ extern "C" ci_status_t victim_run(ci_ctx_t* ctx, const ci_victim_desc_t* d, void
   ci_status_t st = check_victim(d);
   if (st != CI_OK) return st;
   HIPCHK(hipSetDevice(ctx->device));
-  return run_victim(ctx, d, (hipStream_t)stream, ctx->vstream, out);
+  return run_victim(ctx, d, (hipStream_t)stream, ctx->vstream, Counted::live != 0, out);
 }
 
 extern "C" ci_status_t victim_enqueue(ci_ctx_t* ctx, const ci_victim_desc_t* d, void* stream,
@@ -1321,7 +1325,7 @@ struct VictimRun {
   static ci_status_t call(void* p, hipStream_t vs, double* ns) {
     VictimRun* v = static_cast<VictimRun*>(p);
     ci_victim_result_t r;
-    const ci_status_t st = run_victim(v->ctx, v->d, v->caller, vs, &r);
+    const ci_status_t st = run_victim(v->ctx, v->d, v->caller, vs, true, &r);
     *ns = r.time_ns;
     return st;
   }
@@ -1397,7 +1401,7 @@ extern "C" ci_status_t measure_sensitivity(ci_ctx_t* ctx, const ci_victim_desc_t
         if (st != CI_OK) return st;
       }
       for (uint32_t w = 0; w < mo.warmups; ++w) {
-        st = run_victim(ctx, d, caller, vs, &r);
+        st = run_victim(ctx, d, caller, vs, true, &r);
         if (st != CI_OK) return st;
       }
       std::vector<double> ta, tc, ratio;
@@ -1410,13 +1414,13 @@ extern "C" ci_status_t measure_sensitivity(ci_ctx_t* ctx, const ci_victim_desc_t
         const bool col_first = rep & 1u;
         ci_victim_result_t ra, rc;
         if (!col_first) {
-          st = run_victim(ctx, d, caller, vs, &ra);
+          st = run_victim(ctx, d, caller, vs, true, &ra);
           if (st != CI_OK) return st;
         }
         ci_stressor_t* h = nullptr;
         st = stressor_launch(ctx, rs[i], xs[j], caller, &so, ws, ws_bytes, &h);
         if (st != CI_OK) return st;
-        ci_status_t vst = run_victim(ctx, d, caller, vs, &rc);
+        ci_status_t vst = run_victim(ctx, d, caller, vs, true, &rc);
         ci_stressor_report_t sr;
         const bool noop = h->noop;
         st = stressor_stop(h, &sr);
@@ -1427,7 +1431,7 @@ extern "C" ci_status_t measure_sensitivity(ci_ctx_t* ctx, const ci_victim_desc_t
           return st;
         }
         if (col_first) {
-          st = run_victim(ctx, d, caller, vs, &ra);
+          st = run_victim(ctx, d, caller, vs, true, &ra);
           if (st != CI_OK) return st;
         }
         if (!noop && rs[i] != CI_RES_DISPATCH) {
