@@ -38,7 +38,7 @@ inline hipError_t xlaunch(void (*kernel)(KArgs...), dim3 grid, dim3 block, uint3
 }
 // Each returns hipSuccess or the launch error.  `grid` work-groups.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
-hipError_t launch_stamp(uint64_t* slot, hipStream_t s, hipEvent_t e1 = nullptr);
+hipError_t launch_stamp(uint64_t* slot, hipStream_t s);
 // mix: CI_HBM_TRIAD / READ / COPY / WRITE (anything else: triad); chunk:
 // 16-byte accesses per lane and stream in one wave-chunk (1, 2 or 4)
 // strided: the read-only mix takes fixed per-wave strides instead of tickets
@@ -86,12 +86,14 @@ hipError_t launch_mfma_probe(int dtype, const void* a, const void* b, const floa
 struct SumPart {
   uint64_t bits;
   double sum;
+  uint64_t end;            // device clock as the work-group ends
 };
 constexpr uint32_t kSumParts = 1024;
 uint32_t checksum_parts(uint64_t n);
 hipError_t launch_checksum_f32(const float* x, uint64_t n, SumPart* parts, uint64_t* stamp, hipStream_t s,
                                hipEvent_t done);
-void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum);
+// end (optional): the device clock as the last work-group ended
+void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum, uint64_t* end = nullptr);
 hipError_t launch_to_bf16(const float* x, uint64_t n, uint16_t* out, hipStream_t s);
 // n > 0; part: kSumParts floats of device scratch; *amax (pinned) = max |x|
 hipError_t launch_quantize_fp8(const float* x, uint64_t n, float* part, float* amax, uint8_t* out,

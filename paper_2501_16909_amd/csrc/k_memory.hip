@@ -303,15 +303,18 @@ stream_stressor(KCtrl c, const float* __restrict__ b,
 // launches), so that every sweep reads the whole array however many
 // work-groups are resident: a loop over sweeps inside the kernel would let
 // resident waves re-read their own chunks from the L2 while the others wait.
-// What bounds it is memory.  A sweep takes one wave per chunk of 256 elements,
-// one 16-byte access per lane and stream: work-groups are dealt out in address
-// order as others end, so the chip works on a narrow window of each stream,
-// and every wave has its loads in flight from its start.  2^28 elements:
-// 474 us (6.8 TB/s) against 595 us for 2048 work-groups that stride over the
-// array with four accesses per lane (2^20: 7.0 and 7.3 us).
-// NTL: non-temporal loads, for operands that no cache can hold.
-// The in-kernel form is the loop over sweeps: every wave sweeps its own chunks
-// of 1024 elements (U = 4) `passes` times.
+// What bounds it is memory.  Operands that no cache can hold (NTL: loaded
+// non-temporally) take one wave per chunk of 256 elements, one 16-byte access
+// per lane and stream: work-groups are dealt out in address order as others
+// end, so the chip works on a narrow window of each stream, and every wave has
+// its loads in flight from its start: 2^28 elements 474 us (6.8 TB/s) against
+// 595 us for the form below.
+// Others (U = 4, and the in-kernel form, which sweeps its own chunks `passes`
+// times) take eight work-groups per CU that stride over chunks of 1024 elements:
+// 2^24 elements 29 us, 28 with a wave per chunk; but those hold every wave slot
+// for the whole sweep, which is what a co-running kernel meets (a GEMV beside
+// sweeps of 2^24 elements takes 2.5-2.6 times its time, 1.5-1.7 times beside
+// short work-groups), so the sweep keeps them where it has nothing to gain.
 template <int U, bool NTL>
 __global__ void __launch_bounds__(256) triad_victim(const float* __restrict__ b,
                                                     const float* __restrict__ c,
@@ -442,8 +445,8 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
                  (uint8_t*)p + n16 * 16, ntail);
 }
 
-hipError_t launch_stamp(uint64_t* slot, hipStream_t s, hipEvent_t e1) {
-  return xlaunch(stamp_kernel, dim3(1), dim3(64), 0, s, nullptr, e1, slot);
+hipError_t launch_stamp(uint64_t* slot, hipStream_t s) {
+  return xlaunch(stamp_kernel, dim3(1), dim3(64), 0, s, nullptr, nullptr, slot);
 }
 
 hipError_t launch_stream_stressor(const KCtrl& c, uint32_t mix, uint32_t chunk, const float* b,
@@ -487,27 +490,24 @@ hipError_t launch_stream_stressor(const KCtrl& c, uint32_t mix, uint32_t chunk, 
 #undef CI_STREAM_LAUNCH_F
 }
 
-// Non-temporal loads from 384 MiB of operands and result on: the Infinity
-// Cache holds 256 MiB.  A sweep and a read of its result, repeated: 2^24
-// elements 43 us cached, 49 non-temporal; 2^24.5 58 and 63; 2^25 (the line) 85
-// and 83; 2^25.5 123 and 114; 2^28 720 and 681.  Non-temporal stores too: 2^25
-// 91 us, 2^26 173 against 156.
+// A wave per chunk and non-temporal loads from 384 MiB of operands and result
+// on: the Infinity Cache holds 256 MiB.  A sweep and a read of its result,
+// repeated: 2^24 elements 45 us in the strided form, 49 in the other; 2^24.5 59
+// and 63; 2^25 (the line) 84 and 83; 2^25.5 128 and 114; 2^28 805 and 681.
 constexpr uint64_t kTriadStream = 1ull << 25;
 
 hipError_t launch_triad_victim(const float* b, const float* c, float* a, uint64_t n,
                                uint32_t passes, bool in_kernel, uint32_t num_cus, hipStream_t s,
                                hipEvent_t e0, hipEvent_t e1) {
-  const dim3 threads(kTriadThreads);
-  if (in_kernel) {
-    const uint32_t grid = (uint32_t)std::min<uint64_t>((n + 4095) / 4096, (uint64_t)num_cus * 8);
-    return xlaunch(triad_victim<4, false>, dim3(grid), threads, 0, s, e0, e1, b, c, a, n, passes);
-  }
+  const bool strided = in_kernel || n < kTriadStream;
   // work-items of a launch are 32 bits: beyond 2^32 elements waves take several chunks
-  const dim3 grid((uint32_t)std::min<uint64_t>((n + 1023) / 1024, 1u << 22));
-  const auto kernel = n < kTriadStream ? triad_victim<1, false> : triad_victim<1, true>;
-  for (uint32_t p = 0; p < passes; ++p) {
-    const hipError_t e = xlaunch(kernel, grid, threads, 0, s, p == 0 ? e0 : nullptr,
-                                 p + 1 == passes ? e1 : nullptr, b, c, a, n, 1u);
+  const uint64_t grid = strided ? std::min<uint64_t>((n + 4095) / 4096, (uint64_t)num_cus * 8)
+                                : std::min<uint64_t>((n + 1023) / 1024, 1u << 22);
+  const auto kernel = strided ? triad_victim<4, false> : triad_victim<1, true>;
+  const uint32_t launches = in_kernel ? 1 : passes;
+  for (uint32_t p = 0; p < launches; ++p) {
+    const hipError_t e = xlaunch(kernel, dim3((uint32_t)grid), dim3(kTriadThreads), 0, s, p == 0 ? e0 : nullptr,
+                                 p + 1 == launches ? e1 : nullptr, b, c, a, n, in_kernel ? passes : 1u);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

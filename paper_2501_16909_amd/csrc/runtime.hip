@@ -1168,20 +1168,24 @@ ci_status_t ci::order_after(ci_ctx* ctx, hipStream_t caller, hipStream_t xs) {
 }
 
 // Run one victim on exec stream `xs` after the caller's queued work; fills
-// out (time, stamps, checksums).  Blocks until done.  beside: the victim has
-// co-runners, or its time is compared with such a run's.
-ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs, bool beside,
+// out (time, stamps, checksums).  Blocks until done.
+// A start event on the victim's launch costs the host 16 us and the stamp
+// before it 3 (three small launches and their wait 36 us, a marker and two
+// launches 17).  So the time runs from a marker in the stream to the victim's
+// end, 0.5 us less than the launch's own, and the begin stamp is the device
+// clock at the end of the checksum kernel, less the events' time from the
+// marker to there.  exact: the launch's own start event and a stamp; beside a
+// stressor the time from the marker includes up to 1.5 us of dispatch, and the
+// queue-pair check took that for slowed queues.
+ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs, bool exact,
                            ci_victim_result_t* out) {
   volatile uint64_t* hr = ctx->hres;
   hr[0] = hr[1] = 0;
   ci_status_t st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
-  // A start event on the victim's launch costs the host 16 us (three small
-  // launches and their wait 36 us, without it 18).  Alone, the time can as well
-  // run from the stamp's end, 0.5 us less; beside other work the interval would
-  // include the dispatch behind it.
-  HIPCHK(launch_stamp((uint64_t*)&hr[0], xs, beside ? nullptr : ctx->ev[7]));
-  st = launch_victim(ctx, d, xs, beside ? ctx->ev[7] : nullptr, ctx->ev[8]);
+  if (exact) HIPCHK(launch_stamp((uint64_t*)&hr[0], xs));
+  else HIPCHK(hipEventRecord(ctx->ev[7], xs));
+  st = launch_victim(ctx, d, xs, exact ? ctx->ev[7] : nullptr, ctx->ev[8]);
   if (st != CI_OK) return st;
   const uint64_t len = victim_out_len(d);
   HIPCHK(launch_checksum_f32((const float*)d->out, len, ctx->sum_parts, (uint64_t*)&hr[1], xs, ctx->ev[9]));
@@ -1189,9 +1193,16 @@ ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t c
   float ms = 0.0f;
   HIPCHK(hipEventElapsedTime(&ms, ctx->ev[7], ctx->ev[8]));
   out->time_ns = (double)ms * 1e6;
-  out->t_begin = hr[0];
   out->t_end = hr[1];
-  checksum_total(ctx->sum_parts, len, &out->checksum_bits, &out->sum_f64);
+  uint64_t end = 0;
+  checksum_total(ctx->sum_parts, len, &out->checksum_bits, &out->sum_f64, &end);
+  if (exact) {
+    out->t_begin = hr[0];
+  } else {
+    HIPCHK(hipEventElapsedTime(&ms, ctx->ev[7], ctx->ev[9]));
+    const uint64_t ticks = (uint64_t)((double)ms * ctx->info.wall_clock_khz);
+    out->t_begin = std::min<uint64_t>(end > ticks ? end - ticks : 0, out->t_end);
+  }
   return CI_OK;
 }
 
