@@ -133,11 +133,11 @@ __device__ __forceinline__ void tile_of(uint32_t bid, uint32_t nbm, uint32_t nbn
 }
 
 // General tile kernel: a work-group of four waves (2 x 2, each TM/2 x TN/2)
-// owns a TM x TN tile of C, two K-stages in LDS.  A stage is two halves of
+// owns a TM x TN tile of C, SL K-stages in LDS (2 or 4).  A stage is two halves of
 // k-steps with a fragment buffer each: while one half multiplies, the other's
 // fragments are read, across stage boundaries too.  One barrier per stage:
 // after it the next stage is in LDS and the finished one's slot takes the
-// stage after.  LDS per work-group is 32, 48 or 64 KiB, so two to five share a
+// stage SL on.  With two, LDS per work-group is 32, 48 or 64 KiB, so two to five share a
 // CU and cover each other's barriers and load latency; a third slot instead of
 // the second work-group was slower (BF16 4096^3 166 against 135 us).
 // What bounds it: at one work-group per CU the chain of load, barrier and
@@ -148,7 +148,7 @@ __device__ __forceinline__ void tile_of(uint32_t bid, uint32_t nbm, uint32_t nbn
 // Rows past the edge repeat the last one and feed outputs that are not
 // stored; in a short last stage, chunks past its end repeat its last one and
 // the fragments there are zeroed.
-template <int DT, int TM, int TN>
+template <int DT, int TM, int TN, int SL>
 __global__ void __launch_bounds__(256, TM * TN >= 128 * 128 ? 2 : 1)
 gemm_tile_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, float* __restrict__ C, uint32_t M,
                  uint32_t N, uint32_t K, float scale) {
@@ -176,7 +176,7 @@ gemm_tile_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, f
     src[o] = (o < OA ? A : B) + g * rowBytes + lane_chunk(lane, r) * 16u;
   }
   auto issue = [&](uint32_t st) {
-    uint8_t* slot = smem + (st & 1u) * kSlot;
+    uint8_t* slot = smem + (st % SL) * kSlot;
     if (st + 1 == nst && rem < kStage) {
 #pragma unroll
       for (int o = 0; o < OPS; ++o) {
@@ -201,7 +201,7 @@ gemm_tile_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, f
   typename F::T fa[2][NS][IN], fb[2][NS][JN];
   auto read_ks = [&](uint32_t st, auto half, int s) {
     constexpr int b = decltype(half)::value;
-    const uint8_t* slot = smem + (st & 1u) * kSlot;
+    const uint8_t* slot = smem + (st % SL) * kSlot;
     const uint32_t kb = b * (kStage / 2) + fk + s * F::kStep;
 #pragma unroll
     for (int i = 0; i < IN; ++i) fa[b][s][i] = F::ld(slot, wm * (TM / 2) + i * 32 + frow, kb);
@@ -217,10 +217,13 @@ gemm_tile_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, f
   };
   using H0 = std::integral_constant<int, 0>;
   using H1 = std::integral_constant<int, 1>;
-  issue(0);
-  __builtin_amdgcn_s_waitcnt(wait_vm(0));
+#pragma unroll
+  for (uint32_t q = 0; q < SL; ++q)
+    if (q < nst) issue(q);
+  if (nst >= SL) __builtin_amdgcn_s_waitcnt(wait_vm((SL - 1) * OPS));
+  else __builtin_amdgcn_s_waitcnt(wait_vm(0));
   __builtin_amdgcn_s_barrier();
-  if (nst > 1) issue(1);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int s = 0; s < NS; ++s) read_ks(0, H0{}, s);
   uint32_t st = 0;
@@ -232,13 +235,14 @@ gemm_tile_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, f
     }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(kWaitLds);     // this wave's reads of the slot are done
-    __builtin_amdgcn_s_waitcnt(wait_vm(0));   // its part of stage st + 1 has landed
+    if (st + SL <= nst) __builtin_amdgcn_s_waitcnt(wait_vm((SL - 2) * OPS));   // its part of stage st + 1 has landed
+    else __builtin_amdgcn_s_waitcnt(wait_vm(0));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       read_ks(st + 1, H0{}, s);
-      if (s == NS - 1 && st + 2 < nst) issue(st + 2);
+      if (s == NS - 1 && st + SL < nst) issue(st + SL);
       mma_ks(H1{}, s);
     }
   }
@@ -704,14 +708,22 @@ constexpr TileCost kCost32[2][4] = {{{18.7f, 9.0f}, {37.5f, 4.0f}, {70.0f, 8.0f}
                                     {{19.4f, 8.0f}, {36.0f, 10.0f}, {66.0f, 10.0f}, {250.0f, 2.0f}}};
 constexpr uint64_t kBigMaxRow = 1u << 23;   // row bytes whose tile offsets fit 32 bits
 
-int tile_choice(bool f32, bool whole_lines, uint64_t m, uint64_t n, bool big_ok) {
-  const TileCost* t = (f32 ? kCost32 : kCost16)[whole_lines ? 0 : 1];
+// Four slots instead of two where a work-group has its CU for itself and BF16's
+// short stages leave a load little to hide behind: 2048^3 in tiles of 128 x 128
+// 23.0 us (27.1 with two), 1792^3 19.3 (24.1), 1024^3 in tiles of 64 x 64 6.8
+// (7.6).  FP32 and FP8 gain nothing (1024^3 29.0 both, 4.8 and 5.0), nor does a
+// CU with several work-groups (BF16 2304^3 42.7 against 35.5).
+bool four_slots(int dtype, uint64_t tiles) { return dtype == CI_DT_BF16 && tiles <= kCus; }
+
+int tile_choice(int dtype, bool whole_lines, uint64_t m, uint64_t n, bool big_ok) {
+  const TileCost* t = (dtype == CI_DT_F32 ? kCost32 : kCost16)[whole_lines ? 0 : 1];
   int best = 0;
   float cost = 0.0f;
   bool prev_over = false;   // the best so far is beyond what a launch can hold
   for (int i = 0; i < (big_ok ? 4 : 3); ++i) {
     const uint64_t tiles = ((m + kTileM[i] - 1) / kTileM[i]) * ((n + kTileN[i] - 1) / kTileN[i]);
-    const float c = (float)((tiles + kCus - 1) / kCus) * t[i].u + t[i].v;
+    float c = (float)((tiles + kCus - 1) / kCus) * t[i].u + t[i].v;
+    if (i == 2 && four_slots(dtype, tiles)) c = whole_lines ? 11.3f : 12.6f;
     const bool fits = tiles * (i < 3 ? 256 : 512) < (1ull << 32);   // a launch's work-items are 32 bits
     if (i == 0 || (fits && c <= cost) || prev_over) {
       best = i;
@@ -741,11 +753,16 @@ template <int DT>
 hipError_t launch_gemm_dt(const GemmCall& g) {
   const uint64_t row = (uint64_t)g.k * Op<DT>::kElem;
   constexpr bool f32 = DT == CI_DT_F32;
+  constexpr int kFour = DT == CI_DT_BF16 ? 4 : 2;
   const bool big_ok = g.m >= kBig && g.n >= kBig && row <= kBigMaxRow;
-  switch (tile_choice(f32, row % kStage == 0, g.m, g.n, big_ok)) {
-    case 0: return launch_tiles(gemm_tile_kernel<DT, 64, 64>, 64, 64, 256, 2 * 128 * kStage, g);
-    case 1: return launch_tiles(gemm_tile_kernel<DT, 128, 64>, 128, 64, 256, 2 * 192 * kStage, g);
-    case 2: return launch_tiles(gemm_tile_kernel<DT, 128, 128>, 128, 128, 256, 2 * 256 * kStage, g);
+  auto small = [&](auto two, auto four, uint32_t tm, uint32_t tn) {
+    const bool f = four_slots(DT, (uint64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn));
+    return launch_tiles(f ? four : two, tm, tn, 256, (f ? 4 : 2) * (tm + tn) * kStage, g);
+  };
+  switch (tile_choice(DT, row % kStage == 0, g.m, g.n, big_ok)) {
+    case 0: return small(gemm_tile_kernel<DT, 64, 64, 2>, gemm_tile_kernel<DT, 64, 64, kFour>, 64, 64);
+    case 1: return launch_tiles(gemm_tile_kernel<DT, 128, 64, 2>, 128, 64, 256, 2 * 192 * kStage, g);
+    case 2: return small(gemm_tile_kernel<DT, 128, 128, 2>, gemm_tile_kernel<DT, 128, 128, kFour>, 128, 128);
     default: break;
   }
   // Every tile at once or not: bands of 8 tile rows when it is (BF16 4096^3
