@@ -708,25 +708,14 @@ constexpr TileCost kCost32[2][4] = {{{18.7f, 9.0f}, {37.5f, 4.0f}, {70.0f, 8.0f}
                                     {{19.4f, 8.0f}, {36.0f, 10.0f}, {66.0f, 10.0f}, {250.0f, 2.0f}}};
 constexpr uint64_t kBigMaxRow = 1u << 23;   // row bytes whose tile offsets fit 32 bits
 
-// Four slots instead of two where a work-group has its CU for itself and BF16's
-// short stages leave a load little to hide behind: 2048^3 in tiles of 128 x 128
-// 23.0 us (27.1 with two), 1792^3 19.3 (24.1), 1024^3 in tiles of 64 x 64 6.8
-// (7.6).  FP32 gains in tiles of 128 x 128 (2048^3 144 us, 151 with two) and not
-// in smaller ones (1024^3 29.0 both), FP8 nothing (1024^3 4.8 and 5.0), nor does
-// a CU with several work-groups (BF16 2304^3 42.7 against 35.5).
-constexpr bool can_use_four(int dtype, uint32_t tile) {
-  return dtype == CI_DT_BF16 || (dtype == CI_DT_F32 && tile == 128);
-}
-
-int tile_choice(int dtype, bool whole_lines, uint64_t m, uint64_t n, bool big_ok) {
-  const TileCost* t = (dtype == CI_DT_F32 ? kCost32 : kCost16)[whole_lines ? 0 : 1];
+int tile_choice(bool f32, bool whole_lines, uint64_t m, uint64_t n, bool big_ok) {
+  const TileCost* t = (f32 ? kCost32 : kCost16)[whole_lines ? 0 : 1];
   int best = 0;
   float cost = 0.0f;
   bool prev_over = false;   // the best so far is beyond what a launch can hold
   for (int i = 0; i < (big_ok ? 4 : 3); ++i) {
     const uint64_t tiles = ((m + kTileM[i] - 1) / kTileM[i]) * ((n + kTileN[i] - 1) / kTileN[i]);
-    float c = (float)((tiles + kCus - 1) / kCus) * t[i].u + t[i].v;
-    if (i == 2 && dtype == CI_DT_BF16 && tiles <= kCus) c = whole_lines ? 11.3f : 12.6f;     // four slots
+    const float c = (float)((tiles + kCus - 1) / kCus) * t[i].u + t[i].v;
     const bool fits = tiles * (i < 3 ? 256 : 512) < (1ull << 32);   // a launch's work-items are 32 bits
     if (i == 0 || (fits && c <= cost) || prev_over) {
       best = i;
@@ -757,18 +746,21 @@ hipError_t launch_gemm_dt(const GemmCall& g) {
   const uint64_t row = (uint64_t)g.k * Op<DT>::kElem;
   constexpr bool f32 = DT == CI_DT_F32;
   const bool big_ok = g.m >= kBig && g.n >= kBig && row <= kBigMaxRow;
-  auto square = [&](auto tile) {
-    constexpr uint32_t T = decltype(tile)::value;
-    if constexpr (can_use_four(DT, T)) {
-      if ((uint64_t)((g.m + T - 1) / T) * ((g.n + T - 1) / T) <= kCus)
-        return launch_tiles(gemm_tile_kernel<DT, T, T, 4>, T, T, 256, 4 * 2 * T * kStage, g);
+  switch (tile_choice(f32, row % kStage == 0, g.m, g.n, big_ok)) {
+    case 0: {
+      // Four slots instead of two where a BF16 tile has its CU to itself and its
+      // short stages leave a load little to hide behind: 1024^3 6.8 us, 7.6 with
+      // two; FP32 29.0 both, FP8 4.8 and 5.0.  Tiles of 128 x 128 would gain more
+      // (BF16 2048^3 23.0 us, 27.1; FP32 144, 151), but their 128 KiB shut out
+      // co-runners that hold 64 KiB of LDS, as the LDS stressor does.
+      if constexpr (DT == CI_DT_BF16) {
+        if ((uint64_t)((g.m + 63) / 64) * ((g.n + 63) / 64) <= kCus)
+          return launch_tiles(gemm_tile_kernel<DT, 64, 64, 4>, 64, 64, 256, 4 * 128 * kStage, g);
+      }
+      return launch_tiles(gemm_tile_kernel<DT, 64, 64, 2>, 64, 64, 256, 2 * 128 * kStage, g);
     }
-    return launch_tiles(gemm_tile_kernel<DT, T, T, 2>, T, T, 256, 2 * 2 * T * kStage, g);
-  };
-  switch (tile_choice(DT, row % kStage == 0, g.m, g.n, big_ok)) {
-    case 0: return square(std::integral_constant<uint32_t, 64>{});
     case 1: return launch_tiles(gemm_tile_kernel<DT, 128, 64, 2>, 128, 64, 256, 2 * 192 * kStage, g);
-    case 2: return square(std::integral_constant<uint32_t, 128>{});
+    case 2: return launch_tiles(gemm_tile_kernel<DT, 128, 128, 2>, 128, 128, 256, 2 * 256 * kStage, g);
     default: break;
   }
   // Every tile at once or not: bands of 8 tile rows when it is (BF16 4096^3
