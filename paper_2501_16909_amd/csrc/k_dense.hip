@@ -803,4 +803,32 @@ hipError_t launch_gemv_bf16(const uint16_t* w, const uint16_t* x, float* y, uint
   return xlaunch(cached ? gemv_bf16_kernel<false> : gemv_bf16_kernel<true>, dim3((uint32_t)g), dim3(256), 0, s, e0, e1, w, x, y, n, k);
 }
 
+namespace {
+
+template <int DT>
+hipError_t preload_gemm() {
+  hipError_t e[5] = {preload(gemm_tile_kernel<DT, 64, 64, 2>), preload(gemm_tile_kernel<DT, 128, 64, 2>),
+                     preload(gemm_tile_kernel<DT, 128, 128, 2>), hipSuccess, hipSuccess};
+  if constexpr (DT == CI_DT_F32) {
+    e[3] = preload(gemm256f_kernel<4>);
+    e[4] = preload(gemm256f_kernel<8>);
+  } else {
+    e[3] = preload(gemm256d_kernel<DT, true>);
+    e[4] = preload(gemm256d_kernel<DT, false>);
+  }
+  for (const hipError_t x : e)
+    if (x != hipSuccess) return x;
+  return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t preload_dense() {
+  for (const hipError_t e : {preload_gemm<CI_DT_F32>(), preload_gemm<CI_DT_BF16>(), preload_gemm<CI_DT_FP8E4M3>(),
+                             preload(gemm_tile_kernel<CI_DT_BF16, 64, 64, 4>), preload(gemv_bf16_kernel<false>),
+                             preload(gemv_bf16_kernel<true>)})
+    if (e != hipSuccess) return e;
+  return hipSuccess;
+}
+
 }  // namespace ci

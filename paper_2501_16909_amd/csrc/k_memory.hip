@@ -496,6 +496,11 @@ hipError_t launch_stream_stressor(const KCtrl& c, uint32_t mix, uint32_t chunk, 
 // and 63; 2^25 (the line) 84 and 83; 2^25.5 128 and 114; 2^28 805 and 681.
 constexpr uint64_t kTriadStream = 1ull << 25;
 
+hipError_t preload_triad_victim() {
+  const hipError_t e = preload(triad_victim<4, false>);
+  return e == hipSuccess ? preload(triad_victim<1, true>) : e;
+}
+
 hipError_t launch_triad_victim(const float* b, const float* c, float* a, uint64_t n,
                                uint32_t passes, bool in_kernel, uint32_t num_cus, hipStream_t s,
                                hipEvent_t e0, hipEvent_t e1) {
