@@ -364,8 +364,7 @@ typedef struct ci_victim_desc {
 #define CI_VICTIM_TRIAD_IN_KERNEL 1u
 
 typedef struct ci_victim_result {
-  double time_ns;          /* launch time from HIP events (while this process  */
-                           /* runs no stressor, from a marker before it)       */
+  double time_ns;          /* launch time from HIP events                      */
   uint64_t checksum_bits;  /* sum of the output's 32-bit patterns mod 2^64     */
   double sum_f64;          /* FP64 sum of the output (fixed reduction order)   */
   uint64_t t_begin;        /* device clock just before / after the victim      */

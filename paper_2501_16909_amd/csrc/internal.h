@@ -37,7 +37,7 @@ inline hipError_t xlaunch(void (*kernel)(KArgs...), dim3 grid, dim3 block, uint3
                             e0, e1, 0);
 }
 // Loads a kernel's code, which its first launch would otherwise do between a
-// timed call's marker and the kernel (2 ms for a module, 10 us for a kernel).
+// timed call's begin stamp and the kernel (2 ms for a module, 10 us for a kernel).
 template <typename Kernel>
 inline hipError_t preload(Kernel kernel) {
   hipFuncAttributes a;
@@ -95,14 +95,12 @@ hipError_t launch_mfma_probe(int dtype, const void* a, const void* b, const floa
 struct SumPart {
   uint64_t bits;
   double sum;
-  uint64_t end;            // device clock as the work-group ends
 };
 constexpr uint32_t kSumParts = 1024;
 uint32_t checksum_parts(uint64_t n);
 hipError_t launch_checksum_f32(const float* x, uint64_t n, SumPart* parts, uint64_t* stamp, hipStream_t s,
                                hipEvent_t done);
-// end (optional): the device clock as the last work-group ended
-void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum, uint64_t* end = nullptr);
+void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum);
 hipError_t launch_to_bf16(const float* x, uint64_t n, uint16_t* out, hipStream_t s);
 // n > 0; part: kSumParts floats of device scratch; *amax (pinned) = max |x|
 hipError_t launch_quantize_fp8(const float* x, uint64_t n, float* part, float* amax, uint8_t* out,

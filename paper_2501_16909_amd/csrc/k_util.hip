@@ -73,7 +73,6 @@ __global__ void __launch_bounds__(kSumThreads) checksum_kernel(const float* __re
   if (threadIdx.x == 0) {
     parts[blockIdx.x].bits = (sb[0] + sb[1]) + (sb[2] + sb[3]);
     parts[blockIdx.x].sum = (ss[0] + ss[1]) + (ss[2] + ss[3]);
-    parts[blockIdx.x].end = dev_now();
   }
 }
 
@@ -288,16 +287,14 @@ hipError_t launch_checksum_f32(const float* x, uint64_t n, SumPart* parts, uint6
   return xlaunch(checksum_kernel, dim3(np), dim3(kSumThreads), 0, s, nullptr, done, x, n, len, parts, stamp);
 }
 
-void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum, uint64_t* end) {
+void checksum_total(const volatile SumPart* parts, uint64_t n, uint64_t* bits, double* sum) {
   const uint32_t np = checksum_parts(n);
-  uint64_t b = 0, last = 0;
+  uint64_t b = 0;
   double t = 0.0;
   for (uint32_t i = 0; i < np; ++i) {
     b += parts[i].bits;
     t += parts[i].sum;
-    if (parts[i].end > last) last = parts[i].end;
   }
-  if (end) *end = last;
   *bits = b;
   *sum = t;
 }

@@ -57,16 +57,7 @@ struct ci_ctx {
   uint64_t arena_bytes = 0;
 };
 
-// How many there are in the process.
-struct Counted {
-  static std::atomic<int> live;
-  Counted() { ++live; }
-  ~Counted() { --live; }
-  Counted(const Counted&) = delete;
-};
-
 struct ci_stressor {
-  Counted counted;
   ci_ctx* ctx = nullptr;
   ci_resource_t r = CI_RES_HBM;
   float intensity = 0.0f;
@@ -130,7 +121,7 @@ ci_status_t launch_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t s,
                           hipEvent_t e1);
 // Orders `xs` after the work already queued on `caller` (NULL: no ordering).
 ci_status_t order_after(ci_ctx* ctx, hipStream_t caller, hipStream_t xs);
-ci_status_t run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs, bool exact,
+ci_status_t run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs,
                        ci_victim_result_t* out);
 // Fetches, once per device, the device address of the static scratch array
 // that ci_attention_decode_noalloc works in; call with `device` current.

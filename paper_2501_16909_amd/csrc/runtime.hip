@@ -19,8 +19,6 @@
 
 using namespace ci;
 
-std::atomic<int> Counted::live{0};
-
 // ------------------------------------------------------------------ errors
 namespace {
 thread_local std::string g_err;
@@ -1173,25 +1171,22 @@ ci_status_t ci::order_after(ci_ctx* ctx, hipStream_t caller, hipStream_t xs) {
 
 // Run one victim on exec stream `xs` after the caller's queued work; fills
 // out (time, stamps, checksums).  Blocks until done.
-// A start event on the victim's launch costs the host 16 us and the stamp
-// before it 3 (three small launches and their wait 36 us, a marker and two
-// launches 17).  So the time runs from a marker in the stream to the victim's
-// end, 0.5 us less than the launch's own, and the begin stamp is the device
-// clock at the end of the checksum kernel, less the events' time from the
-// marker to there.  ci_init loads the kernels, so no code is loaded between
-// marker and launch (20 000 triads of 2^20: median 4.5 us, 99.9 % below 12; with
-// start events 5.1 and 13.4).  exact: the launch's own start event and a stamp; beside a
-// stressor the time from the marker includes up to 1.5 us of dispatch, and the
-// queue-pair check took that for slowed queues.
-ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs, bool exact,
+// The start event costs the host 16 us of a call and the stamp 3 (three small
+// launches and their wait 36 us, a marker and two launches 17), and neither can
+// go: a marker in the stream is passed at once, so that the victim's wait for a
+// co-runner's wave slots, or for a host thread that is preempted before the
+// launch, would count as its time (2^20 elements beside queued sweeps: 19.8 us
+// from a marker, 11.0 from the start event; alone 4.5 and 5.0).  What co-runs
+// may be a stressor, another stream's kernels or another process's: the library
+// cannot tell, so every run is timed the same way.
+ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs,
                            ci_victim_result_t* out) {
   volatile uint64_t* hr = ctx->hres;
   hr[0] = hr[1] = 0;
   ci_status_t st = order_after(ctx, caller, xs);
   if (st != CI_OK) return st;
-  if (exact) HIPCHK(launch_stamp((uint64_t*)&hr[0], xs));
-  else HIPCHK(hipEventRecord(ctx->ev[7], xs));
-  st = launch_victim(ctx, d, xs, exact ? ctx->ev[7] : nullptr, ctx->ev[8]);
+  HIPCHK(launch_stamp((uint64_t*)&hr[0], xs));
+  st = launch_victim(ctx, d, xs, ctx->ev[7], ctx->ev[8]);
   if (st != CI_OK) return st;
   const uint64_t len = victim_out_len(d);
   HIPCHK(launch_checksum_f32((const float*)d->out, len, ctx->sum_parts, (uint64_t*)&hr[1], xs, ctx->ev[9]));
@@ -1199,16 +1194,9 @@ ci_status_t ci::run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t c
   float ms = 0.0f;
   HIPCHK(hipEventElapsedTime(&ms, ctx->ev[7], ctx->ev[8]));
   out->time_ns = (double)ms * 1e6;
+  out->t_begin = hr[0];
   out->t_end = hr[1];
-  uint64_t end = 0;
-  checksum_total(ctx->sum_parts, len, &out->checksum_bits, &out->sum_f64, &end);
-  if (exact) {
-    out->t_begin = hr[0];
-  } else {
-    HIPCHK(hipEventElapsedTime(&ms, ctx->ev[7], ctx->ev[9]));
-    const uint64_t ticks = (uint64_t)((double)ms * ctx->info.wall_clock_khz);
-    out->t_begin = std::min<uint64_t>(end > ticks ? end - ticks : 0, out->t_end);
-  }
+  checksum_total(ctx->sum_parts, len, &out->checksum_bits, &out->sum_f64);
   return CI_OK;
 }
 
@@ -1218,7 +1206,7 @@ extern "C" ci_status_t victim_run(ci_ctx_t* ctx, const ci_victim_desc_t* d, void
   ci_status_t st = check_victim(d);
   if (st != CI_OK) return st;
   HIPCHK(hipSetDevice(ctx->device));
-  return run_victim(ctx, d, (hipStream_t)stream, ctx->vstream, Counted::live != 0, out);
+  return run_victim(ctx, d, (hipStream_t)stream, ctx->vstream, out);
 }
 
 extern "C" ci_status_t victim_enqueue(ci_ctx_t* ctx, const ci_victim_desc_t* d, void* stream,
@@ -1342,7 +1330,7 @@ struct VictimRun {
   static ci_status_t call(void* p, hipStream_t vs, double* ns) {
     VictimRun* v = static_cast<VictimRun*>(p);
     ci_victim_result_t r;
-    const ci_status_t st = run_victim(v->ctx, v->d, v->caller, vs, true, &r);
+    const ci_status_t st = run_victim(v->ctx, v->d, v->caller, vs, &r);
     *ns = r.time_ns;
     return st;
   }
@@ -1418,7 +1406,7 @@ extern "C" ci_status_t measure_sensitivity(ci_ctx_t* ctx, const ci_victim_desc_t
         if (st != CI_OK) return st;
       }
       for (uint32_t w = 0; w < mo.warmups; ++w) {
-        st = run_victim(ctx, d, caller, vs, true, &r);
+        st = run_victim(ctx, d, caller, vs, &r);
         if (st != CI_OK) return st;
       }
       std::vector<double> ta, tc, ratio;
@@ -1431,13 +1419,13 @@ extern "C" ci_status_t measure_sensitivity(ci_ctx_t* ctx, const ci_victim_desc_t
         const bool col_first = rep & 1u;
         ci_victim_result_t ra, rc;
         if (!col_first) {
-          st = run_victim(ctx, d, caller, vs, true, &ra);
+          st = run_victim(ctx, d, caller, vs, &ra);
           if (st != CI_OK) return st;
         }
         ci_stressor_t* h = nullptr;
         st = stressor_launch(ctx, rs[i], xs[j], caller, &so, ws, ws_bytes, &h);
         if (st != CI_OK) return st;
-        ci_status_t vst = run_victim(ctx, d, caller, vs, true, &rc);
+        ci_status_t vst = run_victim(ctx, d, caller, vs, &rc);
         ci_stressor_report_t sr;
         const bool noop = h->noop;
         st = stressor_stop(h, &sr);
@@ -1448,7 +1436,7 @@ extern "C" ci_status_t measure_sensitivity(ci_ctx_t* ctx, const ci_victim_desc_t
           return st;
         }
         if (col_first) {
-          st = run_victim(ctx, d, caller, vs, true, &ra);
+          st = run_victim(ctx, d, caller, vs, &ra);
           if (st != CI_OK) return st;
         }
         if (!noop && rs[i] != CI_RES_DISPATCH) {
