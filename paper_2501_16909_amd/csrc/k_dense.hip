@@ -690,13 +690,20 @@ namespace {
 // per K = 1024 to all four tilings on 81 square shapes from 512 to 8192:
 //   BF16, whole lines  64 x 64: 512^3 4.6, 1024^3 7.4, 1536^3 16; 128 x 64:
 //              2048^3 26 (64 x 64 28, 128 x 128 27); 128 x 128: 2560^3 41 (59,
-//              54; 256 x 256 59), 4352^3 188 (204); 256 x 256: 3328^3 80 (94),
-//              5120^3 248 (290), 8192^3 880 (1060);
+//              54; 256 x 256 59), 4352^3 188 (204); 256 x 256: 5120^3 248
+//              (290), 8192^3 880 (1060);
 //   BF16, others  128 x 128: 2488^3 46 (85, 76; 256 x 256 71); 256 x 256:
-//              3080^3 89 (154, 109, 114), 8184^3 930 (2940, 1760, 1250);
+//              8184^3 930 (2940, 1760, 1250);
 //   FP32       64 x 64: 1024^3 29 (128 x 64 48), 3072^3 534 (573, 643; 256 x
 //              256 785), 4004^3 990 with 256 x 256 (1067 with 128 x 128).
 // FP8 follows BF16 at half the time.
+// 256 x 256 is offered only where its tiles are a CU's worth each or more (sides
+// from about 3841): its 128 KiB of LDS shut out co-runners that hold more than
+// 31 KiB.  Below that line it would take BF16 3328^3 from 99 to 74 us and FP32
+// 3712^3 from 910 to 894, but a victim beside the LDS stressor on every CU, 2.5
+// to 4 times its time with smaller tiles, would wait for the stressor to end.
+// Two work-groups of 128 x 128 share a CU, so BF16's and FP8's fourth round
+// rides on the third (3456^3, three rounds, 104 us; 3520^3, four, 103).
 struct TileCost {
   float u, v;
 };
@@ -715,7 +722,9 @@ int tile_choice(bool f32, bool whole_lines, uint64_t m, uint64_t n, bool big_ok)
   bool prev_over = false;   // the best so far is beyond what a launch can hold
   for (int i = 0; i < (big_ok ? 4 : 3); ++i) {
     const uint64_t tiles = ((m + kTileM[i] - 1) / kTileM[i]) * ((n + kTileN[i] - 1) / kTileN[i]);
-    const float c = (float)((tiles + kCus - 1) / kCus) * t[i].u + t[i].v;
+    float rounds = (float)((tiles + kCus - 1) / kCus);
+    if (i == 2 && !f32 && rounds == 4.0f) rounds = 3.25f;
+    const float c = rounds * t[i].u + t[i].v;
     const bool fits = tiles * (i < 3 ? 256 : 512) < (1ull << 32);   // a launch's work-items are 32 bits
     if (i == 0 || (fits && c <= cost) || prev_over) {
       best = i;
@@ -745,7 +754,8 @@ template <int DT>
 hipError_t launch_gemm_dt(const GemmCall& g) {
   const uint64_t row = (uint64_t)g.k * Op<DT>::kElem;
   constexpr bool f32 = DT == CI_DT_F32;
-  const bool big_ok = g.m >= kBig && g.n >= kBig && row <= kBigMaxRow;
+  const uint64_t big_tiles = (uint64_t)((g.m + kBig - 1) / kBig) * ((g.n + kBig - 1) / kBig);
+  const bool big_ok = g.m >= kBig && g.n >= kBig && big_tiles >= kCus && row <= kBigMaxRow;
   switch (tile_choice(f32, row % kStage == 0, g.m, g.n, big_ok)) {
     case 0: {
       // Four slots instead of two where a BF16 tile has its CU to itself and its
@@ -766,7 +776,7 @@ hipError_t launch_gemm_dt(const GemmCall& g) {
   // Every tile at once or not: bands of 8 tile rows when it is (BF16 4096^3
   // 114 us against 116 with FAR), of 4 with FAR otherwise (8192^3 881 against
   // 926 us, FP8 412 against 465).
-  const bool far = (uint64_t)((g.m + kBig - 1) / kBig) * ((g.n + kBig - 1) / kBig) > kCus;
+  const bool far = big_tiles > kCus;
   if constexpr (f32) {
     const uint32_t lds = kRingStages * kDSlot;
     return far ? launch_tiles(gemm256f_kernel<4>, kBig, kBig, 512, lds, g)

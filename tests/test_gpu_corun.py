@@ -67,3 +67,24 @@ def test_victim_window_is_stamped(ctx, dev):
         before, after = ticks.cpu().tolist()
         assert before <= r.t_begin <= r.t_end <= after
         assert (r.t_end - r.t_begin) * 1e6 / ctx.info.wall_clock_khz >= r.time_ns
+
+
+# GEMMs of fewer than 256 tiles of 256 x 256 leave room on their CUs for a
+# work-group that holds 64 KiB of LDS, and the largest of them for the cache
+# stressor's waves: the slowdown beside such a work-group on every CU is that
+# of sharing the CU (2 to 5), not the stressor's lifetime (100 ms, a hundred
+# times the longest of these kernels).
+@pytest.mark.parametrize("dtype,n", [("bf16", 2048), ("bf16", 2888), ("bf16", 3328), ("bf16", 3840), ("fp8", 3328),
+                                     ("fp8", 3712), ("f32", 3072), ("f32", 3584)])
+def test_gemm_shares_cus_with_lds_holders(ctx, dev, dtype, n):
+    import synth
+    import torch
+    x = torch.randn((n, n), device=dev)
+    a = {"f32": lambda: x, "bf16": lambda: x.to(torch.bfloat16).view(torch.int16),
+         "fp8": lambda: x.to(torch.float8_e4m3fn).view(torch.uint8)}[dtype]()
+    d = ctx.gemm_desc(a, a.clone(), torch.empty((n, n), device=dev), dtype, n, n, n, 1.0, 1.0)
+    win = torch.from_numpy(synth.u32(7, 8192).view(np.int32)).to(dev)
+    l1 = torch.zeros(4096, dtype=torch.int32, device=dev)
+    for res, opts in (("lds", dict(src0=win)), ("occupancy", dict(knob=64)), ("vl1d", dict(src0=l1, n=4096))):
+        cell, = ctx.measure_sensitivity(d, [res], [opts], [1.0], reps=3, warmups=1, deadline_ms=100)
+        assert cell["slowdown"] < 15, (res, cell["slowdown"])
