@@ -354,9 +354,10 @@ gemm256d_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, fl
   };
   // touched per stage: 32 rows of A (its panel is shared by the 8 tiles of a
   // band's row that run together) and 64 of B (shared by 4), waves 0-3 and 4-7
-  const uint8_t* far = wid < 4 ? baseA : baseB;
   const uint32_t far_n = wid < 4 ? 8u : 16u;
-  const uint32_t far_o = ((wid < 4 ? (tn & 7u) * 32u : (tm & 3u) * 64u) + (wid & 3u) * far_n + min(lane, far_n - 1)) * rowBytes;
+  const uint32_t far_row = (wid < 4 ? (tn & 7u) * 32u : (tm & 3u) * 64u) + (wid & 3u) * far_n;
+  const uint8_t* far = (wid < 4 ? baseA : baseB) + (uint64_t)far_row * rowBytes;
+  const uint32_t far_o = min(lane, far_n - 1) * rowBytes;
   auto touch = [&](uint32_t st) {
     if constexpr (FAR)
       __builtin_amdgcn_global_load_lds(far + min(st * kStage, rowBytes - 16u) + far_o, smem + 2 * kBigSlot, 4, 0, 0);
@@ -713,7 +714,10 @@ constexpr TileCost kCost16[2][4] = {{{2.95f, 2.0f}, {4.4f, 3.6f}, {8.2f, 4.6f}, 
                                     {{5.2f, 0.5f}, {7.1f, 4.0f}, {10.4f, 2.5f}, {29.5f, 0.5f}}};
 constexpr TileCost kCost32[2][4] = {{{18.7f, 9.0f}, {37.5f, 4.0f}, {70.0f, 8.0f}, {250.0f, 2.0f}},
                                     {{19.4f, 8.0f}, {36.0f, 10.0f}, {66.0f, 10.0f}, {250.0f, 2.0f}}};
-constexpr uint64_t kBigMaxRow = 1u << 23;   // row bytes whose tile offsets fit 32 bits
+// Row bytes for which the offsets of a lane fit 32 bits (63 rows and 112 bytes
+// at the most): 256 tiles of longer rows do not fit the device.  4096^2 with
+// BF16 rows of 2^23 + 128 bytes take 128 ms, 264 with tiles of 128 x 128.
+constexpr uint64_t kBigMaxRow = 1u << 26;
 
 int tile_choice(bool f32, bool whole_lines, uint64_t m, uint64_t n, bool big_ok) {
   const TileCost* t = (f32 ? kCost32 : kCost16)[whole_lines ? 0 : 1];

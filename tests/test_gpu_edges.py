@@ -272,3 +272,23 @@ def test_serve_input_remainders(ctx, dev):
     for q in reqs:
         b, c = synth.uniform_f32(q["seed"], q["n"]), synth.uniform_f32(q["seed"] + 1, q["n"])
         assert np.array_equal(q["out_copy"].cpu().numpy().view(np.uint32), oracle.triad_f32(b, c).view(np.uint32))
+
+
+# Rows of 8 and 16 MiB and a bit: the lane offsets of the largest tiles, their
+# early touches (more tiles than CUs) and the ragged last stage.  The first and
+# last rows against the small tiles, which add in the same order.
+@pytest.mark.parametrize("dtype,m,kb", [("f32", 3900, (1 << 23) + 16), ("bf16", 4100, (1 << 24) + 144)])
+def test_gemm_long_rows(ctx, dev, dtype, m, kb):
+    import torch
+    k = kb // {"f32": 4, "bf16": 2}[dtype]
+    if torch.cuda.mem_get_info()[0] < m * kb + (4 << 30):
+        pytest.skip("not enough free device memory")
+    x = torch.empty((m, k), dtype={"f32": torch.float32, "bf16": torch.bfloat16}[dtype], device=dev).normal_()
+    a = x if dtype == "f32" else x.view(torch.int16)
+    out, part = torch.empty((m, m), device=dev), torch.empty((200, m), device=dev)
+    ctx.victim_run(ctx.gemm_desc(a, a, out, dtype, m, m, k, 1.0, 1.0))
+    for rows in (slice(0, 200), slice(m - 200, m)):
+        ctx.victim_run(ctx.gemm_desc(a[rows], a, part, dtype, 200, m, k, 1.0, 1.0))
+        assert torch.equal(out[rows], part)
+    del x, a
+    torch.cuda.empty_cache()
