@@ -1159,11 +1159,23 @@ ci_status_t ci::launch_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_
 // record and the cross-queue wait cost about 10 us of a call (47 us against
 // 37 us for three small launches and their synchronisation), the query under
 // one.  Nothing makes `caller` wait afterwards: every call that orders itself
-// here returns only when its work has finished.
+// here returns only when its work has finished.  So a stream under capture is
+// refused, and before the query, which would end the capture.  An error of the
+// query (a capture elsewhere in this thread, in which no call may wait) refuses
+// the call too.  The query does not mind whose stream it is; a stream of another
+// device goes the way of the record, which refuses it.
 ci_status_t ci::order_after(ci_ctx* ctx, hipStream_t caller, hipStream_t xs) {
   if (!caller) return CI_OK;
-  if (hipStreamQuery(caller) == hipSuccess) return CI_OK;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  HIPCHK(hipStreamIsCapturing(caller, &capture));
+  if (capture != hipStreamCaptureStatusNone)
+    return set_err(CI_ERR_HIP, "the stream is being captured: a call that waits for its own work cannot be recorded");
+  hipDevice_t dev = -1;
+  const hipError_t idle = hipStreamQuery(caller);
+  if (idle == hipSuccess && hipStreamGetDevice(caller, &dev) == hipSuccess && dev == ctx->device) return CI_OK;
   (void)hipGetLastError();  // not ready: nothing for a later call to find
+  if (idle != hipSuccess && idle != hipErrorNotReady)
+    return set_err(CI_ERR_HIP, "hipStreamQuery: %s", hipGetErrorString(idle));
   HIPCHK(hipEventRecord(ctx->ev[6], caller));
   HIPCHK(hipStreamWaitEvent(xs, ctx->ev[6], 0));
   return CI_OK;

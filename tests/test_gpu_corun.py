@@ -1,7 +1,12 @@
 """Victims beside work the library does not start itself: the time they
 report, the work-groups that fit beside them, and what they wait for."""
+import ctypes as C
+
 import numpy as np
 import pytest
+
+import oracle
+import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -77,7 +82,6 @@ def test_victim_window_is_stamped(ctx, dev):
 @pytest.mark.parametrize("dtype,n", [("bf16", 2048), ("bf16", 2888), ("bf16", 3328), ("bf16", 3840), ("fp8", 3328),
                                      ("fp8", 3712), ("f32", 3072), ("f32", 3584)])
 def test_gemm_shares_cus_with_lds_holders(ctx, dev, dtype, n):
-    import synth
     import torch
     x = torch.randn((n, n), device=dev)
     a = {"f32": lambda: x, "bf16": lambda: x.to(torch.bfloat16).view(torch.int16),
@@ -88,3 +92,109 @@ def test_gemm_shares_cus_with_lds_holders(ctx, dev, dtype, n):
     for res, opts in (("lds", dict(src0=win)), ("occupancy", dict(knob=64)), ("vl1d", dict(src0=l1, n=4096))):
         cell, = ctx.measure_sensitivity(d, [res], [opts], [1.0], reps=3, warmups=1, deadline_ms=100)
         assert cell["slowdown"] < 15, (res, cell["slowdown"])
+
+
+# ------------------------------------------------ the caller's stream
+def _calls(ctx, dev):
+    """One call of each way into the library that takes a stream: name -> function
+    of the stream, giving its output."""
+    import torch
+    d = _triad(ctx, dev, 1 << 20)
+    w = torch.from_numpy(oracle.f32_to_bf16(synth.uniform_f32(1, 64 * 512)).view(np.int16)).to(dev).view(64, 512)
+    v = w[:2].contiguous()
+    q = torch.rand((1, 4, 128), device=dev)
+    kv = w.reshape(1, 2, 128, 128)
+    out = torch.empty((1, 512), dtype=torch.int16, device=dev)
+
+    def on(s, f):
+        old, ctx.stream = ctx.stream, s
+        try:
+            return f()
+        finally:
+            ctx.stream = old
+
+    return {"victim": lambda s: ctx.victim_run(d, stream=s).checksum_bits,
+            "gemv_rows": lambda s: on(s, lambda: ctx.gemv_bf16_rows(w, v).clone()),
+            "attention": lambda s: on(s, lambda: ctx.attention_decode_noalloc(q, kv, kv, [100], 4, 2, 128, 128, out).clone())}
+
+
+@pytest.mark.parametrize("name", ["victim", "gemv_rows", "attention"])
+def test_captured_streams_are_refused(ctx, dev, monkeypatch, name):
+    """A call that waits for its work cannot be part of a capture: on the
+    capturing stream it is refused, and the capture and later calls go on.
+    Beside a relaxed capture, calls on other streams work."""
+    import torch
+    from paper_2501_16909_amd import coloc
+    call = _calls(ctx, dev)[name]
+    hip = coloc.load_library()       # its dependencies' symbols too
+    begin, end = hip.hipStreamBeginCapture, hip.hipStreamEndCapture
+    begin.argtypes, end.argtypes = [C.c_void_p, C.c_int], [C.c_void_p, C.POINTER(C.c_void_p)]
+    other = torch.cuda.Stream(device=dev)
+    want = call(other)
+    torch.cuda.synchronize()
+    monkeypatch.setattr(ctx, "_sync_torch", lambda: None)    # waits, which a capture forbids
+    for mode, same in ((1, True), (2, True), (2, False)):    # thread-local, relaxed
+        raw, graph = C.c_void_p(), C.c_void_p()
+        assert hip.hipStreamCreateWithFlags(C.byref(raw), 1) == 0
+        side = torch.cuda.ExternalStream(raw.value, device=dev)
+        assert begin(raw, mode) == 0
+        try:
+            if same:
+                with pytest.raises(coloc.CiError):
+                    call(side)
+            else:
+                call(other)
+        finally:
+            ended = end(raw, C.byref(graph))
+        got = call(side if same else other)
+        assert hip.hipStreamDestroy(raw) == 0
+        assert ended == 0 and hip.hipGraphDestroy(graph) == 0
+        assert torch.equal(got, want) if torch.is_tensor(want) else got == want
+
+
+@pytest.mark.parametrize("name", ["victim", "gemv_rows"])
+def test_calls_wait_for_the_callers_stream(ctx, dev, name):
+    """Operands that a busy stream is still to write: the call given that
+    stream reads them written."""
+    import torch
+    n = 1 << 20
+    sweep = _triad(ctx, dev, 1 << 26)
+    side = torch.cuda.Stream(device=dev)
+    new = torch.rand(n, device=dev)
+    old = torch.zeros_like(new)
+    if name == "victim":
+        c, out = torch.rand(n, device=dev), torch.empty(n, device=dev)
+        d = ctx.triad_desc(old, c, out)
+        ctx.victim_run(d)
+    else:
+        w = torch.ones((64, 512), device=dev).to(torch.bfloat16).view(torch.int16)
+        v, new = old[:512].to(torch.bfloat16).view(1, 512), new[:512].to(torch.bfloat16).view(1, 512)
+        out = torch.empty((1, 64), device=dev)
+        ctx.gemv_bf16_rows(w, v.view(torch.int16), out=out)
+    assert not torch.equal(new, old if name == "victim" else v)
+    torch.cuda.synchronize()
+    ctx.victim_enqueue(sweep, side, 200)              # about 30 ms
+    with torch.cuda.stream(side):
+        (old if name == "victim" else v).copy_(new)
+    assert not side.query()
+    if name == "victim":
+        ctx.victim_run(d, stream=side)
+        want = oracle.triad_f32(new.cpu().numpy(), c.cpu().numpy())
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    else:
+        keep, ctx.stream = ctx.stream, side
+        try:
+            ctx.gemv_bf16_rows(w, v.view(torch.int16), out=out)
+        finally:
+            ctx.stream = keep
+        total = float(new.double().sum())             # 512 products in FP32
+        assert np.all(np.abs(out.cpu().numpy() - total) <= 512 * 2.0 ** -24 * total)
+
+
+def test_stream_of_another_device_is_refused(ctx, dev):
+    import torch
+    from paper_2501_16909_amd import coloc
+    if torch.cuda.device_count() < 2:
+        pytest.skip("needs two GPUs")
+    with pytest.raises(coloc.CiError):
+        ctx.victim_run(_triad(ctx, dev, 1 << 20), stream=torch.cuda.Stream(device=1))
