@@ -607,12 +607,77 @@ __global__ void __launch_bounds__(128) rope_append_kernel(const float* __restric
 // (4.7).
 constexpr uint32_t kAttnChunk = 64;
 
-// o += (lane 16 (l / 16) + I of p) * v, one rounding.  p must not have been
-// written by one of the two instructions before.
-template <int I>
-__device__ __forceinline__ void fma_row_lane(float& o, float p, float v) {
-  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(o) : "v"(p), "v"(v), "n"(I));
+// Multiply-adds with one lane of each row of 16 as an operand, one rounding
+// each: %[o] += (lane 16 (l / 16) + %[l] of %[p]) * %[v].  Such an instruction
+// must not follow within two wait states of the one that writes its %[p], and
+// the compiler, which pads its own, does not look into assembly: a copy, a
+// reload or an accumulator read may stand right before it.  So each statement
+// begins with the wait itself and holds every multiply-add of four words; none
+// of them writes a %[p].  (One instruction a statement and no wait: eight
+// sequences of up to 8064 positions 32.3 us, 32.2 with it; one of 1000 6.3 and
+// 5.8.)
+#define CI_FMA(o, p, v, l) \
+  "\n\tv_fmac_f32_dpp %[" o "], %[" p "], %[" v "] row_newbcast:%[" l "] row_mask:0xf bank_mask:0xf"
+#define CI_WORDS(w) \
+  [x0] "v"(bf_lo(w[0])), [y0] "v"(bf_hi(w[0])), [x1] "v"(bf_lo(w[1])), [y1] "v"(bf_hi(w[1])), \
+  [x2] "v"(bf_lo(w[2])), [y2] "v"(bf_hi(w[2])), [x3] "v"(bf_lo(w[3])), [y3] "v"(bf_hi(w[3]))
+
+// s[i] += sum over j of (lane L + j of q[i]) * element j of the four words.
+#define CI_S1(v, l) CI_FMA("s0", "q0", v, l)
+#define CI_S2(v, l) CI_S1(v, l) CI_FMA("s1", "q1", v, l)
+#define CI_S4(v, l) CI_S2(v, l) CI_FMA("s2", "q2", v, l) CI_FMA("s3", "q3", v, l)
+#define CI_SCORE(S) \
+  "s_nop 1" S("x0", "l0") S("y0", "l1") S("x1", "l2") S("y1", "l3") S("x2", "l4") S("y2", "l5") S("x3", "l6") S("y3", "l7")
+template <int L, int HB>
+__device__ __forceinline__ void score_8(const uint32_t (&w)[4], const float (&q)[HB], float (&s)[HB]) {
+  static_assert(HB == 1 || HB == 2 || HB == 4, "heads of a wave");
+#define CI_LANES \
+  [l0] "n"(L), [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3), [l4] "n"(L + 4), [l5] "n"(L + 5), [l6] "n"(L + 6), [l7] "n"(L + 7)
+  if constexpr (HB == 1)
+    asm(CI_SCORE(CI_S1) : [s0] "+&v"(s[0]) : [q0] "v"(q[0]), CI_WORDS(w), CI_LANES);
+  else if constexpr (HB == 2)
+    asm(CI_SCORE(CI_S2) : [s0] "+&v"(s[0]), [s1] "+&v"(s[1]) : [q0] "v"(q[0]), [q1] "v"(q[1]), CI_WORDS(w), CI_LANES);
+  else
+    asm(CI_SCORE(CI_S4)
+        : [s0] "+&v"(s[0]), [s1] "+&v"(s[1]), [s2] "+&v"(s[2]), [s3] "+&v"(s[3])
+        : [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), CI_WORDS(w), CI_LANES);
+#undef CI_LANES
 }
+
+// a[i], b[i] += sum over j of (lane L + j of p[i]) * the halves of word j.
+#define CI_A1(j) CI_FMA("a0", "p0", "x" #j, "l" #j) CI_FMA("b0", "p0", "y" #j, "l" #j)
+#define CI_A2(j) CI_A1(j) CI_FMA("a1", "p1", "x" #j, "l" #j) CI_FMA("b1", "p1", "y" #j, "l" #j)
+#define CI_A4(j) \
+  CI_A2(j) CI_FMA("a2", "p2", "x" #j, "l" #j) CI_FMA("b2", "p2", "y" #j, "l" #j) \
+  CI_FMA("a3", "p3", "x" #j, "l" #j) CI_FMA("b3", "p3", "y" #j, "l" #j)
+#define CI_ADD(A) "s_nop 1" A(0) A(1) A(2) A(3)
+template <int L, int HB>
+__device__ __forceinline__ void add_4(const uint32_t (&w)[4], const float (&p)[HB], float (&a)[HB], float (&b)[HB]) {
+  static_assert(HB == 1 || HB == 2 || HB == 4, "heads of a wave");
+#define CI_LANES [l0] "n"(L), [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3)
+  if constexpr (HB == 1)
+    asm(CI_ADD(CI_A1) : [a0] "+&v"(a[0]), [b0] "+&v"(b[0]) : [p0] "v"(p[0]), CI_WORDS(w), CI_LANES);
+  else if constexpr (HB == 2)
+    asm(CI_ADD(CI_A2)
+        : [a0] "+&v"(a[0]), [b0] "+&v"(b[0]), [a1] "+&v"(a[1]), [b1] "+&v"(b[1])
+        : [p0] "v"(p[0]), [p1] "v"(p[1]), CI_WORDS(w), CI_LANES);
+  else
+    asm(CI_ADD(CI_A4)
+        : [a0] "+&v"(a[0]), [b0] "+&v"(b[0]), [a1] "+&v"(a[1]), [b1] "+&v"(b[1]), [a2] "+&v"(a[2]), [b2] "+&v"(b[2]),
+          [a3] "+&v"(a[3]), [b3] "+&v"(b[3])
+        : [p0] "v"(p[0]), [p1] "v"(p[1]), [p2] "v"(p[2]), [p3] "v"(p[3]), CI_WORDS(w), CI_LANES);
+#undef CI_LANES
+}
+#undef CI_ADD
+#undef CI_A4
+#undef CI_A2
+#undef CI_A1
+#undef CI_SCORE
+#undef CI_S4
+#undef CI_S2
+#undef CI_S1
+#undef CI_WORDS
+#undef CI_FMA
 
 // A rounded product: it must not merge into the subtraction that follows.
 __device__ __forceinline__ float scaled(float s, float scale) {
@@ -639,45 +704,27 @@ struct ValueRows {
       }
     }
   }
+  // o[2 u], o[2 u + 1]: of word u, per head; p[r]: the weights of rows 16 r .. + 15
   template <uint32_t R0, uint32_t R, int HB>
-  __device__ __forceinline__ void add(const float (&p)[HB][4], float (&o)[HB][2 * W]) const {
+  __device__ __forceinline__ void add(const float (&p)[4][HB], float (&o)[2 * W][HB]) const {
     if constexpr (R < kRows) {
 #pragma unroll
       for (uint32_t u = 0; u < W; ++u) {
-        const float lo = bf_lo(v[R][u]), hi = bf_hi(v[R][u]);
-#pragma unroll
-        for (uint32_t i = 0; i < HB; ++i) {
-          fma_row_lane<(R0 + R) % 16>(o[i][2 * u], p[i][(R0 + R) / 16], lo);
-          fma_row_lane<(R0 + R) % 16>(o[i][2 * u + 1], p[i][(R0 + R) / 16], hi);
-        }
+        const uint32_t w[4] = {v[R][u], v[R + 1][u], v[R + 2][u], v[R + 3][u]};
+        add_4<(R0 + R) % 16, HB>(w, p[(R0 + R) / 16], o[2 * u], o[2 * u + 1]);
       }
-      if constexpr (R % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-      add<R0, R + 1, HB>(p, o);
+      __builtin_amdgcn_sched_barrier(0);
+      add<R0, R + 4, HB>(p, o);
     }
   }
 };
 
 // s += q . k over the 16 dimensions of two 16-byte chunks; q: lane l of each
 // register holds dimension l % 16.
-template <int J, int HB>
-__device__ __forceinline__ void score_word(uint32_t kw, const float (&q)[HB], float (&s)[HB]) {
-  const float lo = bf_lo(kw), hi = bf_hi(kw);
-#pragma unroll
-  for (int i = 0; i < HB; ++i) fma_row_lane<J>(s[i], q[i], lo);
-#pragma unroll
-  for (int i = 0; i < HB; ++i) fma_row_lane<J + 1>(s[i], q[i], hi);
-}
-
 template <int HB>
 __device__ __forceinline__ void score_16(const uint4& a, const uint4& b, const float (&q)[HB], float (&s)[HB]) {
-  score_word<0, HB>(a.x, q, s);
-  score_word<2, HB>(a.y, q, s);
-  score_word<4, HB>(a.z, q, s);
-  score_word<6, HB>(a.w, q, s);
-  score_word<8, HB>(b.x, q, s);
-  score_word<10, HB>(b.y, q, s);
-  score_word<12, HB>(b.z, q, s);
-  score_word<14, HB>(b.w, q, s);
+  score_8<0, HB>({a.x, a.y, a.z, a.w}, q, s);
+  score_8<8, HB>({b.x, b.y, b.z, b.w}, q, s);
 }
 
 template <int D, int HB>
@@ -723,7 +770,7 @@ attn_partial_kernel(const float* __restrict__ q, const uint16_t* __restrict__ kc
   for (uint32_t c = 0; c < kRow4; c += 2)
     score_16<HB>(ks[lane * kRow4 + (c ^ (lane & 15u))], ks[lane * kRow4 + ((c + 1) ^ (lane & 15u))], qr[c / 2], s);
   const bool valid = lane < n;
-  float m[HB], l[HB], p[HB][4], o[HB][2 * Rows::W];
+  float m[HB], l[HB], p[4][HB], o[2 * Rows::W][HB];
 #pragma unroll
   for (uint32_t i = 0; i < HB; ++i) {
     s[i] = valid ? scaled(s[i], scale) : -INFINITY;
@@ -734,9 +781,9 @@ attn_partial_kernel(const float* __restrict__ q, const uint16_t* __restrict__ kc
     const float e = valid ? expf(s[i] - m[i]) : 0.0f;
     l[i] = wave_sum_f(e);
 #pragma unroll
-    for (uint32_t r = 0; r < 4; ++r) p[i][r] = __shfl(e, 16 * r + (lane & 15u), 64);
+    for (uint32_t r = 0; r < 4; ++r) p[r][i] = __shfl(e, 16 * r + (lane & 15u), 64);
 #pragma unroll
-    for (uint32_t j = 0; j < 2 * Rows::W; ++j) o[i][j] = 0.0f;
+    for (uint32_t j = 0; j < 2 * Rows::W; ++j) o[j][i] = 0.0f;
   }
   va.template add<0, 0, HB>(p, o);
   if constexpr (D == 256) va.load(rs, 2 * Rows::kRows, lane);
@@ -756,7 +803,7 @@ attn_partial_kernel(const float* __restrict__ q, const uint16_t* __restrict__ kc
     }
     float2* d2 = reinterpret_cast<float2*>(dst + 2) + lane * Rows::W;
 #pragma unroll
-    for (uint32_t u = 0; u < Rows::W; ++u) d2[u] = make_float2(o[i][2 * u], o[i][2 * u + 1]);
+    for (uint32_t u = 0; u < Rows::W; ++u) d2[u] = make_float2(o[2 * u][i], o[2 * u + 1][i]);
   }
 }
 
