@@ -118,6 +118,10 @@ ci_status_t ci_init(int device, ci_ctx_t** out);
 /* Destroy a context; stops nothing: every stressor must be stopped first
  * (CI_ERR_BUSY otherwise).  NULL is a no-op. */
 ci_status_t ci_shutdown(ci_ctx_t* ctx);
+/* Give back the device memory that the context keeps between calls: the arena
+ * of the last serve_run, which the next one would otherwise reuse.  Waits for
+ * the device's running work.  CI_ERR_INVALID_ARG on NULL. */
+ci_status_t ci_release_memory(ci_ctx_t* ctx);
 const char* ci_last_error(void);
 ci_status_t ci_device_info(ci_ctx_t* ctx, ci_device_info_t* out);
 
@@ -811,8 +815,10 @@ typedef struct ci_served {
  * policy allows (ci_admit), its inputs are generated and its kernel launched
  * on a free slot stream, and it retires when its completion is observed.  The loop owns
  * one device arena of hbm_budget bytes for all request buffers; the context
- * keeps it for the next run when it is at most a sixteenth of the device's
- * memory and half of that is free, and ci_shutdown frees it.  out[i]
+ * keeps it for the next run (unless that one's budget is under a quarter of it)
+ * when it is at most a sixteenth of the device's memory and half of that is
+ * free.  ci_release_memory and ci_shutdown give it back, and so does any
+ * allocation of this library that finds no memory.  out[i]
  * receives request i's record.  Synchronous; returns when all are done. */
 ci_status_t serve_run(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci_policy_t* p,
                       ci_served_t* out);

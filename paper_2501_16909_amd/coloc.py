@@ -182,6 +182,7 @@ class DecodeCell(C.Structure):
 EXPORTS = {
     "ci_init": ([C.c_int, C.POINTER(C.c_void_p)], C.c_int),
     "ci_shutdown": ([C.c_void_p], C.c_int),
+    "ci_release_memory": ([C.c_void_p], C.c_int),
     "ci_last_error": ([], C.c_char_p),
     "ci_device_info": ([C.c_void_p, C.POINTER(DeviceInfo)], C.c_int),
     "ci_peak_for": ([C.c_void_p, C.c_int, C.POINTER(C.c_double)], C.c_int),
@@ -418,6 +419,10 @@ class Context:
         if self.handle:
             _check(load_library().ci_shutdown(self.handle))
             self.handle = None
+
+    def release_memory(self):
+        """Give back the device memory kept between calls (the serving arena)."""
+        _check(load_library().ci_release_memory(self.handle))
 
     def __enter__(self):
         return self

@@ -13,8 +13,10 @@
 #include <cstring>
 #include <deque>
 #include <map>
+#include <mutex>
 #include <string>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -130,8 +132,9 @@ class Arena {
 uint64_t elem_bytes(int dt) { return dt == CI_DT_F32 ? 4 : dt == CI_DT_BF16 ? 2 : 1; }
 
 // Bytes a request holds while it runs: operands, output and, for BF16, room for
-// the larger operand in FP32, which admission counts and nothing uses: inputs
-// are drawn in BF16.
+// the larger operand in FP32.  Inputs are drawn in BF16 and nothing uses that
+// room; it counts so that a budget admits, refuses and queues the requests that
+// it always did.
 uint64_t footprint(const ci_request_t& q) {
   auto al = [](uint64_t b) { return (b + 255) & ~255ull; };
   switch (q.kind) {
@@ -149,6 +152,26 @@ uint64_t footprint(const ci_request_t& q) {
 
 uint64_t out_words(const ci_request_t& q) { return q.kind == CI_VICTIM_GEMM ? q.m * q.n : q.n; }
 
+// Kept arenas (ArenaMemory): the contexts that hold one.  The lock guards
+// every context's arena and arena_bytes; neither object is ever destroyed.
+std::mutex& arena_mu() {
+  static std::mutex* m = new std::mutex;
+  return *m;
+}
+std::vector<ci_ctx*>& arena_holders() {
+  static auto* v = new std::vector<ci_ctx*>;
+  return *v;
+}
+
+uint8_t* take_arena(ci_ctx* ctx, uint64_t* bytes) {
+  std::lock_guard<std::mutex> lk(arena_mu());
+  auto& h = arena_holders();
+  h.erase(std::remove(h.begin(), h.end(), ctx), h.end());
+  if (bytes) *bytes = ctx->arena_bytes;
+  ctx->arena_bytes = 0;
+  return std::exchange(ctx->arena, nullptr);
+}
+
 struct Running {
   int idx = -1;
   uint64_t off = 0, bytes = 0;
@@ -157,6 +180,41 @@ struct Running {
 };
 
 }  // namespace
+
+void ci::drop_arena(ci_ctx* ctx) {
+  if (uint8_t* p = take_arena(ctx, nullptr)) (void)hipFree(p);
+}
+
+hipError_t ci::device_alloc(void** p, size_t n) {
+  *p = nullptr;
+  hipError_t e = hipMalloc(p, n);
+  int dev = -1;
+  if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess) {
+    (void)hipGetLastError();
+    std::vector<uint8_t*> kept;
+    {
+      std::lock_guard<std::mutex> lk(arena_mu());
+      for (ci_ctx* c : arena_holders()) {
+        if (c->device != dev) continue;
+        kept.push_back(std::exchange(c->arena, nullptr));
+        c->arena_bytes = 0;
+      }
+      auto& h = arena_holders();
+      h.erase(std::remove_if(h.begin(), h.end(), [](ci_ctx* c) { return !c->arena; }), h.end());
+    }
+    for (uint8_t* a : kept) (void)hipFree(a);
+    if (!kept.empty()) e = hipMalloc(p, n);
+  }
+  if (e != hipSuccess) *p = nullptr;
+  return e;
+}
+
+extern "C" ci_status_t ci_release_memory(ci_ctx_t* ctx) {
+  if (!ctx) return set_err(CI_ERR_INVALID_ARG, "ci_release_memory: NULL context");
+  HIPCHK(hipSetDevice(ctx->device));
+  drop_arena(ctx);
+  return CI_OK;
+}
 
 extern "C" ci_status_t ci_predict_slowdown(const ci_profile_t* victim,
                                            const ci_profile_t* const* corunners, int nco,
@@ -402,29 +460,23 @@ ci_status_t check_slot_queues(ci_ctx* ctx, const Background& bg, std::vector<hip
 // The arena outlives a run: the driver wipes memory that is given back before
 // it hands it out again, at about 35 GB/s, so a program that serves burst after
 // burst waits 28 ms per GiB of budget for it (8 GiB, 16 requests: 241 ms a run,
-// 6 ms with the arena kept).  A run takes the context's arena for itself, so
-// runs of several threads have one each; the last to end leaves its own there
-// unless one is there already.  Kept: at most a sixteenth of the device's
-// memory, and only where half of it is free; ci_shutdown frees it.
+// 4 ms with the arena kept).  Kept: at most a sixteenth of the device's memory,
+// only where half of it is free, and not for a run whose budget is less than a
+// quarter of it.  ci_release_memory and ci_shutdown give it back, and so does
+// any allocation of the library on that device that finds no memory.
 struct ArenaMemory {
   ci_ctx_t* ctx;
   uint8_t* p = nullptr;
   uint64_t bytes = 0;
 
-  explicit ArenaMemory(ci_ctx_t* c) : ctx(c) {
-    std::lock_guard<std::mutex> lk(ctx->arena_mu);
-    std::swap(p, ctx->arena);
-    std::swap(bytes, ctx->arena_bytes);
-  }
+  explicit ArenaMemory(ci_ctx_t* c) : ctx(c) { p = take_arena(ctx, &bytes); }
   ~ArenaMemory() {
     if (p) (void)hipFree(p);
   }
   hipError_t reserve(uint64_t need) {
-    if (p && bytes >= need) return hipSuccess;
+    if (p && bytes >= need && bytes / 4 <= need) return hipSuccess;
     if (p) (void)hipFree(p);
-    p = nullptr;
-    const hipError_t e = hipMalloc((void**)&p, need);
-    if (e != hipSuccess) p = nullptr;
+    const hipError_t e = device_alloc((void**)&p, need);
     bytes = p ? need : 0;
     return e;
   }
@@ -432,10 +484,11 @@ struct ArenaMemory {
   void keep() {
     size_t free = 0, total = 0;
     if (!p || hipMemGetInfo(&free, &total) != hipSuccess || bytes > total / 16 || free < total / 2) return;
-    std::lock_guard<std::mutex> lk(ctx->arena_mu);
+    std::lock_guard<std::mutex> lk(arena_mu());
     if (ctx->arena) return;
     std::swap(p, ctx->arena);
     std::swap(bytes, ctx->arena_bytes);
+    arena_holders().push_back(ctx);
   }
 };
 
