@@ -817,8 +817,7 @@ typedef struct ci_served {
  * one device arena of hbm_budget bytes for all request buffers; the context
  * keeps it for the next run (unless that one's budget is under a quarter of it)
  * when it is at most a sixteenth of the device's memory and half of that is
- * free.  ci_release_memory and ci_shutdown give it back, and so does any
- * allocation of this library that finds no memory.  out[i]
+ * free; ci_release_memory and ci_shutdown give it back.  out[i]
  * receives request i's record.  Synchronous; returns when all are done. */
 ci_status_t serve_run(ci_ctx_t* ctx, const ci_request_t* trace, int n, const ci_policy_t* p,
                       ci_served_t* out);

@@ -89,7 +89,7 @@ ci_decode_layout_t layout_of(const ci_decode_config_t& c) {
 }
 
 ci_status_t ensure_decode_state(ci_ctx* ctx, size_t nevents) {
-  if (!ctx->dec_pos_dev) HIPCHK(device_alloc((void**)&ctx->dec_pos_dev, 256));
+  if (!ctx->dec_pos_dev) HIPCHK(hipMalloc((void**)&ctx->dec_pos_dev, 256));
   while (ctx->dec_ev.size() < nevents) {
     hipEvent_t e = nullptr;
     HIPCHK(hipEventCreate(&e));

@@ -4,6 +4,7 @@
 #include <array>
 #include <atomic>
 #include <map>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -50,7 +51,8 @@ struct ci_ctx {
   int32_t* dec_pos_dev = nullptr;
   std::vector<hipEvent_t> dec_ev;
   std::map<std::string, hipGraphExec_t> dec_graphs;   // captured decode steps
-  // serve_run's arena between two runs (serve.hip, under its lock)
+  // serve_run's arena between two runs (serve.hip)
+  std::mutex arena_mu;
   uint8_t* arena = nullptr;
   uint64_t arena_bytes = 0;
 };
@@ -121,9 +123,6 @@ ci_status_t launch_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t s,
 ci_status_t order_after(ci_ctx* ctx, hipStream_t caller, hipStream_t xs);
 ci_status_t run_victim(ci_ctx* ctx, const ci_victim_desc_t* d, hipStream_t caller, hipStream_t xs,
                        ci_victim_result_t* out);
-// hipMalloc on the current device; where that finds no memory, once more after
-// giving back the arenas that contexts of this device keep between runs.
-hipError_t device_alloc(void** p, size_t n);
 // Gives back the arena that ctx keeps, if any.
 void drop_arena(ci_ctx* ctx);
 // Fetches, once per device, the device address of the static scratch array

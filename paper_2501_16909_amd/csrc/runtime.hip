@@ -205,8 +205,8 @@ extern "C" ci_status_t ci_init(int device, ci_ctx_t** out) {
   }
   memset((void*)ctx->host, 0, sizeof(HostCtrl));
   memset((void*)ctx->hres, 0, 64 * sizeof(uint64_t));
-  if (device_alloc((void**)&ctx->amax_part, kSumParts * sizeof(float)) != hipSuccess ||
-      device_alloc((void**)&ctx->probe_buf, 65536 * sizeof(uint32_t)) != hipSuccess) {
+  if (hipMalloc((void**)&ctx->amax_part, kSumParts * sizeof(float)) != hipSuccess ||
+      hipMalloc((void**)&ctx->probe_buf, 65536 * sizeof(uint32_t)) != hipSuccess) {
     ci_shutdown(ctx);
     return set_err(CI_ERR_OOM, "ci_init: device scratch");
   }

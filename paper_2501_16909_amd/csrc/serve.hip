@@ -152,21 +152,9 @@ uint64_t footprint(const ci_request_t& q) {
 
 uint64_t out_words(const ci_request_t& q) { return q.kind == CI_VICTIM_GEMM ? q.m * q.n : q.n; }
 
-// Kept arenas (ArenaMemory): the contexts that hold one.  The lock guards
-// every context's arena and arena_bytes; neither object is ever destroyed.
-std::mutex& arena_mu() {
-  static std::mutex* m = new std::mutex;
-  return *m;
-}
-std::vector<ci_ctx*>& arena_holders() {
-  static auto* v = new std::vector<ci_ctx*>;
-  return *v;
-}
-
+// The arena that ctx keeps (ArenaMemory), which it then no longer does.
 uint8_t* take_arena(ci_ctx* ctx, uint64_t* bytes) {
-  std::lock_guard<std::mutex> lk(arena_mu());
-  auto& h = arena_holders();
-  h.erase(std::remove(h.begin(), h.end(), ctx), h.end());
+  std::lock_guard<std::mutex> lk(ctx->arena_mu);
   if (bytes) *bytes = ctx->arena_bytes;
   ctx->arena_bytes = 0;
   return std::exchange(ctx->arena, nullptr);
@@ -183,30 +171,6 @@ struct Running {
 
 void ci::drop_arena(ci_ctx* ctx) {
   if (uint8_t* p = take_arena(ctx, nullptr)) (void)hipFree(p);
-}
-
-hipError_t ci::device_alloc(void** p, size_t n) {
-  *p = nullptr;
-  hipError_t e = hipMalloc(p, n);
-  int dev = -1;
-  if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess) {
-    (void)hipGetLastError();
-    std::vector<uint8_t*> kept;
-    {
-      std::lock_guard<std::mutex> lk(arena_mu());
-      for (ci_ctx* c : arena_holders()) {
-        if (c->device != dev) continue;
-        kept.push_back(std::exchange(c->arena, nullptr));
-        c->arena_bytes = 0;
-      }
-      auto& h = arena_holders();
-      h.erase(std::remove_if(h.begin(), h.end(), [](ci_ctx* c) { return !c->arena; }), h.end());
-    }
-    for (uint8_t* a : kept) (void)hipFree(a);
-    if (!kept.empty()) e = hipMalloc(p, n);
-  }
-  if (e != hipSuccess) *p = nullptr;
-  return e;
 }
 
 extern "C" ci_status_t ci_release_memory(ci_ctx_t* ctx) {
@@ -462,8 +426,7 @@ ci_status_t check_slot_queues(ci_ctx* ctx, const Background& bg, std::vector<hip
 // burst waits 28 ms per GiB of budget for it (8 GiB, 16 requests: 241 ms a run,
 // 4 ms with the arena kept).  Kept: at most a sixteenth of the device's memory,
 // only where half of it is free, and not for a run whose budget is less than a
-// quarter of it.  ci_release_memory and ci_shutdown give it back, and so does
-// any allocation of the library on that device that finds no memory.
+// quarter of it.  ci_release_memory and ci_shutdown give it back.
 struct ArenaMemory {
   ci_ctx_t* ctx;
   uint8_t* p = nullptr;
@@ -476,7 +439,9 @@ struct ArenaMemory {
   hipError_t reserve(uint64_t need) {
     if (p && bytes >= need && bytes / 4 <= need) return hipSuccess;
     if (p) (void)hipFree(p);
-    const hipError_t e = device_alloc((void**)&p, need);
+    p = nullptr;
+    const hipError_t e = hipMalloc((void**)&p, need);
+    if (e != hipSuccess) p = nullptr;
     bytes = p ? need : 0;
     return e;
   }
@@ -484,11 +449,10 @@ struct ArenaMemory {
   void keep() {
     size_t free = 0, total = 0;
     if (!p || hipMemGetInfo(&free, &total) != hipSuccess || bytes > total / 16 || free < total / 2) return;
-    std::lock_guard<std::mutex> lk(arena_mu());
+    std::lock_guard<std::mutex> lk(ctx->arena_mu);
     if (ctx->arena) return;
     std::swap(p, ctx->arena);
     std::swap(bytes, ctx->arena_bytes);
-    arena_holders().push_back(ctx);
   }
 };
 
