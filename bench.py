@@ -2180,7 +2180,7 @@ def run_reference_summary(args):
 
 def run_gemm_counter_summary(args):
     """Counters of `--config gemm-counters` (three BF16 4096^3 launches of
-    the ring kernel) from one rocprofv3 --pmc database (--dbs): writes
+    256 x 256 tiles) from one rocprofv3 --pmc database (--dbs): writes
     profiles/gemm_bf16_4096_counters.md."""
     ds = [d for d in _pmc_dispatches(args.dbs[0]) if d["name"].startswith("gemm256d_kernel<")]
     if not ds:
@@ -2189,14 +2189,14 @@ def run_gemm_counter_summary(args):
     # launches, matched by launch order
     extra = [[d for d in _pmc_dispatches(db) if d["name"].startswith("gemm256d_kernel<")] for db in args.dbs[1:]]
     cmd = "\n".join(c.strip() for c in args.cmd) if args.cmd else "(not given)"
-    L = ["# Hardware counters of the GEMM victim (BF16, M = N = K = 4096, ring kernel)", "",
+    L = ["# Hardware counters of the GEMM victim (BF16, M = N = K = 4096, 256 x 256 tiles)", "",
          "Commands (repository root, one MI355X; one counter group per run), then the summary:", "", "```", cmd,
          f"python3 bench.py --config gemm-counter-summary --dbs {' '.join(args.dbs)}", "```", "",
          f"`bench.py --config gemm-counters` launches the BF16 4096³ GEMM three times (`{ds[0]['name']}`, "
          f"{ds[0]['grid'] // ds[0]['wg']} work-groups of {ds[0]['wg']} threads). Derived: active time = "
          "GRBM_GUI_ACTIVE / 8 XCDs / 2.4 GHz; MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES over active cycles x 1024 "
          "SIMDs; LDS B/clk/CU = SQ_INSTS_LDS x 1 KiB (each a 64-lane `ds_read_b128`) over active cycles x 256 "
-         "CUs (ring fills by `global_load_lds` come on top, about 15 B/clk/CU); waits as fractions of "
+         "CUs (the fills by `global_load_lds` come on top, about 15 B/clk/CU); waits as fractions of "
          "SQ_WAVE_CYCLES.", "",
          "| launch | duration us (profiled) | active us | MFMA busy | LDS read B/clk/CU | waiting | "
          "waiting on LDS | LDS bank conflicts | LDS instructions | waves |",

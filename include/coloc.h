@@ -704,7 +704,9 @@ ci_status_t ci_silu_mul_bf16(ci_ctx_t* ctx, const float* gu, uint32_t batch, uin
  * 8064), and for every argument ci_attention_decode rejects.
  * Every call on one GPU shares that GPU's array and leaves its contents
  * behind (nothing in it needs clearing: each call rewrites what it reads);
- * calls that overlap on one GPU, from any context or stream, race. */
+ * calls that overlap on one GPU, from any context or stream, race.  Like every
+ * call that returns when its work is done, it cannot be part of a capture
+ * itself: CI_ERR_HIP, and the capture goes on, when `stream` is captured. */
 #define CI_NOALLOC_PART_BYTES (16ull << 20)
 ci_status_t ci_attention_decode_noalloc(ci_ctx_t* ctx, const float* q, const uint16_t* k_cache,
                                         const uint16_t* v_cache, const int32_t* pos, uint32_t batch,

@@ -614,8 +614,8 @@ constexpr uint32_t kAttnChunk = 64;
 // reload or an accumulator read may stand right before it.  So each statement
 // begins with the wait itself and holds every multiply-add of four words; none
 // of them writes a %[p].  (One instruction a statement and no wait: eight
-// sequences of up to 8064 positions 32.3 us, 32.2 with it; one of 1000 6.3 and
-// 5.8.)
+// sequences of up to 8064 positions 32.3 us, 32.2 with it; four of up to 1000
+// 6.3 and 5.8.)
 #define CI_FMA(o, p, v, l) \
   "\n\tv_fmac_f32_dpp %[" o "], %[" p "], %[" v "] row_newbcast:%[" l "] row_mask:0xf bank_mask:0xf"
 #define CI_WORDS(w) \

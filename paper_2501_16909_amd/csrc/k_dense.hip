@@ -141,9 +141,9 @@ __device__ __forceinline__ void tile_of(uint32_t bid, uint32_t nbm, uint32_t nbn
 // CU and cover each other's barriers and load latency; a third slot instead of
 // the second work-group was slower (BF16 4096^3 166 against 135 us).
 // What bounds it: at one work-group per CU the chain of load, barrier and
-// fragment read of every stage (BF16 512^3: 4.7 us against 10.6 us for the
-// register-staged 128 x 128 kernel it replaces, 1024^3 7.5 against 18.2); with
-// several, the matrix core (FP32 1416 x 1402 x 1416 65 against 115 us, where
+// fragment read of every stage (BF16 512^3: 5.8 us against 12.7 us for the
+// register-staged 128 x 128 kernel it replaces, 1024^3 9.1 against 20.5); with
+// several, the matrix core (FP32 1416 x 1402 x 1416 67 against 118 us, where
 // 132 tiles of 128 x 128 left half the CUs idle; floor 36 us).
 // Rows past the edge repeat the last one and feed outputs that are not
 // stored; in a short last stage, chunks past its end repeat its last one and
@@ -301,11 +301,12 @@ gemm_tile_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, f
 // What bounds it: with random operands the part lowers its clock under MFMA
 // load (1.6-1.9 GHz measured in the loop), and the loop with its loads left out
 // runs 8192^3 BF16 in 737 us; with them a phase takes 705 clocks instead of
-// 566, the load path being shared with the fragment reads.  BF16 8192^3
-// 880 us (1250 TF; 1005-1110 us for the one-group ring before it), FP8
-// 412 us (2670 TF; 500-610), BF16 4096^3 114-120 us (128-146).
+// 566, the load path being shared with the fragment reads.  On a part that
+// other work has not warmed, against the one-group ring before it: BF16 8192^3
+// 828 us (1330 TF; 970), FP8 397 (2770 TF; 483), BF16 4096^3 110 (128); after
+// seconds of load BF16 8192^3 takes 920 us (1200 TF), FP8 485.
 // At most 192 registers per wave and 129 KiB of LDS, so that two 64-register
-// stressor waves per SIMD and their LDS still fit beside it.
+// stressor waves per SIMD and up to 31 KiB of LDS still fit beside it.
 constexpr uint32_t kBig = 256;
 constexpr uint32_t kBigOp = kBig * kStage;          // one operand of a stage
 constexpr uint32_t kBigSlot = 2 * kBigOp;
@@ -479,8 +480,8 @@ gemm256d_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, fl
 // TF; tiles of 128 x 128 take 1130 us).  Its MFMAs are four times as long as
 // BF16's for the same bytes, so neither loads nor barriers weigh enough for the
 // alternating groups of the other types (1237 us).
-// Four slots of 32 KiB: 128 KiB of the CU's 160 KiB, leaving 32 KiB for a
-// co-resident stressor work-group.
+// Four slots of 32 KiB: 128 KiB of the CU's 160 KiB, leaving 31 KiB (LDS is
+// given out in pieces of 1280 bytes) for a co-resident stressor work-group.
 constexpr int kRingStages = 4;
 constexpr int kDStage = 64;                         // K bytes per stage per row
 constexpr int kDOperand = kBig * kDStage;           // one operand, one stage (16 KiB)
@@ -621,9 +622,10 @@ __global__ void __launch_bounds__(512, 1) gemm256f_kernel(const uint8_t* __restr
 // GEMV: wave w handles rows w, w + W, ...; lane l reads 16-byte chunks
 // l, l + 64, ... of the row (8 BF16 each), four chunks in flight, and keeps
 // an FP32 running sum; the 64 partial sums are combined by a fixed butterfly.
-// Memory bounds it: 8192 x 8192 25.3 us (5.3 TB/s), 16384 x 16384 86 us (6.2
+// Memory bounds it: 8192 x 8192 23.5 us (5.7 TB/s), 16384 x 16384 84 us (6.4
 // TB/s); eight chunks in flight, two or four rows a wave and loads that run
-// ahead over rows are no faster (25-32 and 84-109 us).
+// ahead over rows are no faster (25-32 and 84-109 us where this form took 25
+// and 86).
 // NTL: non-temporal weight loads, for matrices that no cache can hold.
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -763,10 +765,10 @@ hipError_t launch_gemm_dt(const GemmCall& g) {
   switch (tile_choice(f32, row % kStage == 0, g.m, g.n, big_ok)) {
     case 0: {
       // Four slots instead of two where a BF16 tile has its CU to itself and its
-      // short stages leave a load little to hide behind: 1024^3 6.8 us, 7.6 with
-      // two; FP32 29.0 both, FP8 4.8 and 5.0.  Tiles of 128 x 128 would gain more
-      // (BF16 2048^3 23.0 us, 27.1; FP32 144, 151), but their 128 KiB shut out
-      // co-runners that hold 64 KiB of LDS, as the LDS stressor does.
+      // short stages leave a load little to hide behind: 1024^3 9.1 us, 9.8 with
+      // two, 512^3 6.0 and 6.2; FP32 the same with both, FP8 0.2 us apart.  Tiles
+      // of 128 x 128 would gain more (BF16 2048^3 15 %, FP32 5 %), but their 128
+      // KiB shut out co-runners that hold 64 KiB of LDS, as the LDS stressor does.
       if constexpr (DT == CI_DT_BF16) {
         if ((uint64_t)((g.m + 63) / 64) * ((g.n + 63) / 64) <= kCus)
           return launch_tiles(gemm_tile_kernel<DT, 64, 64, 4>, 64, 64, 256, 4 * 128 * kStage, g);
@@ -805,9 +807,9 @@ hipError_t launch_gemm(int dtype, const void* a, const void* b, float* c, uint64
 }
 
 // Non-temporal weight loads when the copies that the launches rotate over are
-// more than the 256 MiB Infinity Cache: 3 x 8192^2 25.3 us against 27.0, one
-// 16384^2 86 against 94; below it the cache serves: 3 x 5888^2 16.0 us against
-// 17.7, one 8192^2 22.7 against 23.8.
+// more than the 256 MiB Infinity Cache: 3 x 8192^2 23.5 us against 25.9, one
+// 16384^2 84 against 93; below it the cache serves: 3 x 5888^2 14.4 us against
+// 16.5, one 8192^2 21.5 against 22.0.
 hipError_t launch_gemv_bf16(const uint16_t* w, const uint16_t* x, float* y, uint64_t n, uint64_t k,
                             uint64_t copies, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   uint64_t g = (n + 3) / 4;   // one wave per row, four waves per work-group

@@ -307,11 +307,13 @@ stream_stressor(KCtrl c, const float* __restrict__ b,
 // non-temporally) take one wave per chunk of 256 elements, one 16-byte access
 // per lane and stream: work-groups are dealt out in address order as others
 // end, so the chip works on a narrow window of each stream, and every wave has
-// its loads in flight from its start: 2^28 elements 474 us (6.8 TB/s) against
-// 595 us for the form below.
+// its loads in flight from its start: 2^28 elements 485 us (6.6 TB/s) against
+// 600 us for the form below.  Beside a stressor that holds most wave slots its
+// short work-groups queue for the rest: 2^27 elements beside the L2 stressor on
+// every CU 25 times their time alone, 6 in the form below.
 // Others (U = 4, and the in-kernel form, which sweeps its own chunks `passes`
 // times) take eight work-groups per CU that stride over chunks of 1024 elements:
-// 2^24 elements 29 us, 28 with a wave per chunk; but those hold every wave slot
+// 2^24 elements 31 us, 30 with a wave per chunk; but those hold every wave slot
 // for the whole sweep, which is what a co-running kernel meets (a GEMV beside
 // sweeps of 2^24 elements takes 2.5-2.6 times its time, 1.5-1.7 times beside
 // short work-groups), so the sweep keeps them where it has nothing to gain.
